@@ -168,7 +168,10 @@ typedef struct {
    * launch's return to the routing records being seen (host_route_us: the
    * host waits for the device to reach and finish the router), and from
    * there to the FFN launch's return (host_decide_us: the statistics, slot
-   * decisions, on-demand copies and FFN enqueue on the critical path) */
+   * decisions, on-demand copies and FFN enqueue on the critical path).  A
+   * layer whose experts all hold a slot, with no copy in flight, has its FFN
+   * enqueued behind the router, which names the slots on the device: it adds
+   * nothing to host_decide_us */
   double host_route_us;
   double host_decide_us;
 } spp_run_stats;

@@ -30,6 +30,8 @@ struct RouterArgs {
                         // single-wave tails (polled instead of a completion counter), or nullptr
   int32_t* topk;        // [B, K]
   float* gates;         // [B, K]
+  const int32_t* slot_tab;  // [n] slot of each expert, or nullptr (the host decides the slots)
+  int32_t* sel;         // [B, K] slot_tab[topk] (written when slot_tab is given)
   float* s;             // [n]
   // host records (pinned, host-mapped; device-visible addresses) or nullptr:
   // 8-byte words (seq << 32) | payload, each written by one store, so the
@@ -47,7 +49,11 @@ struct RouterArgs {
 };
 
 struct FfnArgs {
-  const void* blob[kMaxWork];  // expert blobs (slot or shared expert)
+  const void* blob[kMaxWork];  // expert blobs (slot or shared expert); items d < nsel come from sel instead
+  const int32_t* sel;          // [nsel] slots of the routed experts, read on the device (nullptr: none)
+  const uint8_t* slots;        // slot pool: slot j at slots + j * stride
+  uint64_t stride;
+  int nsel;
   int32_t gate_idx[kMaxWork];  // index into gates, or -1 for weight 1
   int nW;
   int I, D;
@@ -129,6 +135,8 @@ struct CopyList {
   uint64_t n16;
 };
 hipError_t launch_h2d_copies(const CopyList& list, int wgs, hipStream_t st);
+// dst[i] = src[i], i < n, on the stream (src is read before the call returns).
+hipError_t launch_set_table(int32_t* dst, const int32_t* src, int n, hipStream_t st);
 hipError_t launch_spin(uint64_t ticks, uint32_t max_iter, hipStream_t st);
 // Batch-1 FFN launch over `nunits` (expert, unit) pairs: units per workgroup
 // (*upw) so that about `target_wgs` workgroups share the work; returns the grid.

@@ -10,6 +10,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstdint>
@@ -351,6 +352,7 @@ __device__ __forceinline__ void select_topk(const RouterArgs& a, const uint64_t*
       const float gk = v / sum;
       a.topk[idx] = e;
       a.gates[idx] = gk;
+      if (a.slot_tab) a.sel[idx] = a.slot_tab[e];
       s_zsel[tid] = gk;  // each lane rewrites only its own entry
     }
   }
@@ -519,6 +521,12 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
     }
   }
 
+  // slots of this lane's experts, for the workgroup that may select
+  int slt[EPL ? EPL : 1];
+#pragma unroll
+  for (int q = 0; q < (EPL ? EPL : 1); ++q)
+    slt[q] = EPL && !adapter_wg && wave == 0 && a.slot_tab ? a.slot_tab[min(lane + 64 * q, n - 1)] : 0;
+
   float xv[NCH][V];
   if (a.u) {
     load_row_f32<T, NCH, FULL>(a.u, lane, nch, xv);
@@ -626,10 +634,17 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
       const float m0 = lane_value(zsel, 0);
       const float v = on ? expf(zsel - m0) : 0.f;
       const float sum = wave_sum(v);
+      int slot = 0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int t = __shfl(slt[q], isel & 63);
+        slot = q == (isel >> 6) ? t : slot;
+      }
       if (on) {
         const float gk = v / sum;
         a.topk[lane] = isel;
         a.gates[lane] = gk;
+        if (a.slot_tab) a.sel[lane] = slot;
         if (a.route_rec) {
           st_record(a.route_rec + lane, a.seq, static_cast<uint32_t>(isel));
           st_record(a.gate_rec + lane, a.seq, __float_as_uint(gk));
@@ -872,6 +887,7 @@ __global__ __launch_bounds__(64) void router_select_wave_kernel(RouterArgs a) {
       gk = v / sum;
       a.topk[b * a.K + lane] = isel;
       a.gates[b * a.K + lane] = gk;
+      if (a.slot_tab) a.sel[b * a.K + lane] = a.slot_tab[isel];
     }
   }
   auto records = [&]() {
@@ -955,6 +971,13 @@ __global__ __launch_bounds__(64) void router_select_wave_kernel(RouterArgs a) {
 constexpr int kFfnWaves = 4;
 constexpr int kFfnThreads = 64 * kFfnWaves;
 
+// Blob of work item d (wave-uniform): the slot that the router launch named
+// for a routed expert, or the address the host gave.
+__device__ __forceinline__ const void* work_blob(const FfnArgs& a, int d) {
+  if (d < a.nsel) return a.slots + static_cast<uint64_t>(static_cast<uint32_t>(a.sel[d])) * a.stride;
+  return a.blob[d];
+}
+
 template <int NCH>
 constexpr int ffn_upp() {
   return NCH <= 3 ? 4 : (NCH == 4 ? 3 : (NCH == 5 ? 2 : 1));
@@ -997,7 +1020,7 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_units_kernel(FfnArgs a) {
       if (uu < u1) {  // wave-uniform
         const int d = uu / I;
         const int i = uu - d * I;
-        const T* base = reinterpret_cast<const T*>(a.blob[d]) + static_cast<size_t>(i) * unit_elems;
+        const T* base = reinterpret_cast<const T*>(work_blob(a, d)) + static_cast<size_t>(i) * unit_elems;
         load_chunks<NCH, FULL, true>(base, lane, nch, rg[p]);
         load_chunks<NCH, FULL, true>(base + D, lane, nch, ru[p]);
         load_chunks<NCH, FULL, true>(base + 2 * D, lane, nch, rd[p]);
@@ -1142,7 +1165,7 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
     const int u = ub + wave;
     const int uc = u < total ? u : total - 1;  // wave-uniform
     const int d = uc / I;
-    const T* base = reinterpret_cast<const T*>(a.blob[d]) + static_cast<size_t>(uc - d * I) * unit_elems;
+    const T* base = reinterpret_cast<const T*>(work_blob(a, d)) + static_cast<size_t>(uc - d * I) * unit_elems;
     load_chunks<NCH, FULL, true>(base, lane, nch, rg[r]);
     load_chunks<NCH, FULL, true>(base + D, lane, nch, ru[r]);
     const int gi = a.gate_idx[d];
@@ -1152,7 +1175,7 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
       const int v = ub + w2;
       const int vc = v < total ? v : total - 1;  // wave-uniform
       const int d2 = vc / I;
-      const T* dbase = reinterpret_cast<const T*>(a.blob[d2]) + static_cast<size_t>(vc - d2 * I) * unit_elems + 2 * D;
+      const T* dbase = reinterpret_cast<const T*>(work_blob(a, d2)) + static_cast<size_t>(vc - d2 * I) * unit_elems + 2 * D;
 #pragma unroll
       for (int s = 0; s < DS; ++s) {
         const int c = c0 + lane + 64 * s;
@@ -1351,7 +1374,7 @@ __device__ __forceinline__ void q4_pass_loads(const FfnArgs& a, int ub, int ustr
     const int uc = uu < u1 ? uu : u1 - 1;  // wave-uniform
     const int d = uc / I;
     const int i = uc - d * I;
-    const uint8_t* base = reinterpret_cast<const uint8_t*>(a.blob[d]) + static_cast<size_t>(i) * unit_bytes;
+    const uint8_t* base = reinterpret_cast<const uint8_t*>(work_blob(a, d)) + static_cast<size_t>(i) * unit_bytes;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int blk = (FULLQ || lane + 64 * q < nblk) ? lane + 64 * q : 0;
@@ -2223,6 +2246,14 @@ __global__ __launch_bounds__(256) void h2d_copy_kernel(CopyList a) {
   }
 }
 
+constexpr int kTableChunk = 512;
+struct TableArg {
+  int32_t v[kTableChunk];
+};
+__global__ __launch_bounds__(256) void set_table_kernel(TableArg t, int32_t* dst, int n) {
+  for (int i = threadIdx.x; i < n; i += 256) dst[i] = t.v[i];
+}
+
 __global__ void spin_kernel(uint64_t ticks, uint32_t max_iter) {
   const uint64_t t0 = wall_clock64();
   for (uint32_t it = 0; it < max_iter; ++it) {
@@ -2470,6 +2501,18 @@ hipError_t launch_h2d_copies(const CopyList& list, int wgs, hipStream_t st) {
   if (list.n == 0 || list.n16 == 0) return hipSuccess;
   hipLaunchKernelGGL(h2d_copy_kernel, dim3(wgs), dim3(256), 0, st, list);
   return hipGetLastError();
+}
+
+hipError_t launch_set_table(int32_t* dst, const int32_t* src, int n, hipStream_t st) {
+  if (!dst || !src || n < 1) return hipErrorInvalidValue;
+  for (int i0 = 0; i0 < n; i0 += kTableChunk) {
+    TableArg t{};
+    const int m = std::min(n - i0, kTableChunk);
+    std::copy(src + i0, src + i0 + m, t.v);
+    hipLaunchKernelGGL(set_table_kernel, dim3(1), dim3(256), 0, st, t, dst + i0, m);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_spin(uint64_t ticks, uint32_t max_iter, hipStream_t st) {

@@ -18,7 +18,12 @@ int32_t SlotPolicy::lowest_empty() const {
 
 void SlotPolicy::put(int32_t slot, int32_t e) {
   const int32_t old = slot_expert_[slot];
-  if (old != kEmpty) expert_slot_[old] = kEmpty;
+  if (old != kEmpty) {
+    expert_slot_[old] = kEmpty;
+    --available_;
+  }
+  if (expert_slot_[e] == kEmpty) ++available_;
+  ++version_;
   slot_expert_[slot] = e;
   expert_slot_[e] = slot;
 }
@@ -46,10 +51,14 @@ bool SlotPolicy::set_table(const int32_t* experts, const int64_t* stamps, std::s
     seen[e] = 1;
   }
   std::fill(expert_slot_.begin(), expert_slot_.end(), kEmpty);
+  available_ = 0;
+  ++version_;
   for (int32_t j = 0; j < S_; ++j) {
     slot_expert_[j] = experts[j];
     slot_stamp_[j] = stamps ? stamps[j] : 0;
-    if (experts[j] != kEmpty) expert_slot_[experts[j]] = j;
+    if (experts[j] == kEmpty) continue;
+    expert_slot_[experts[j]] = j;
+    ++available_;
   }
   return true;
 }

@@ -31,6 +31,11 @@ class SlotPolicy {
   int32_t n() const { return n_; }
   int32_t slot_of(int32_t e) const { return expert_slot_[e]; }
   bool available(int32_t e) const { return expert_slot_[e] != kEmpty; }
+  // every expert of the layer holds a slot
+  bool all_available() const { return available_ == n_; }
+  const std::vector<int32_t>& expert_slots() const { return expert_slot_; }
+  // changes whenever the expert -> slot mapping does
+  uint64_t version() const { return version_; }
   const std::vector<int32_t>& slot_experts() const { return slot_expert_; }
   const std::vector<int64_t>& slot_stamps() const { return slot_stamp_; }
 
@@ -64,6 +69,8 @@ class SlotPolicy {
   void put(int32_t slot, int32_t e);
 
   int32_t S_, n_;
+  int32_t available_ = 0;
+  uint64_t version_ = 1;
   std::vector<int32_t> slot_expert_;
   std::vector<int64_t> slot_stamp_;
   std::vector<int32_t> expert_slot_;

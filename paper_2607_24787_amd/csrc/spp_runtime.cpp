@@ -37,6 +37,7 @@ spp_status fail(spp_status s, const std::string& m) {
 constexpr int kEvStart = 0, kEvRouted = 1, kEvWaitA = 2, kEvWaitB = 3, kEvFfnBegin = 4, kEvFfnEnd = 5, kEvEnd = 6,
               kEvLoaded = 7;  // after the on-demand loads enqueued on the compute stream, before the copy waits
 constexpr int kNumEv = 8;
+constexpr uint32_t kRecSets = 2;  // a decode step runs at most one layer ahead of its records
 
 // Events recorded on the compute stream by default end with a system-scope
 // release (an L2 writeback) that stalls the stream for 10-20 us after kernels
@@ -80,6 +81,8 @@ struct LayerState {
   std::vector<int32_t> pending_prefetch;  // prefetched for this layer, not yet executed
   std::vector<int32_t> prev_T;            // routing of this layer at its last call [B*K]
   std::vector<float> prev_g;              // and its gates
+  int32_t* slot_tab = nullptr;            // device copy of the expert -> slot table [n] (owned by the context)
+  uint64_t slot_tab_version = 0;          // the policy version it holds (0: none)
 };
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -101,13 +104,16 @@ struct spp_ctx {
   float* x_dev = nullptr;      // [maxB, D] router input
   float* zbuf = nullptr;       // [maxB, n + r]
   uint64_t* ztag = nullptr;    // [n + r] batch-1 router values tagged with their launch's seq (zero: none yet)
-  uint8_t* res_dev = nullptr;  // topk [maxB*K] i32 | gates [maxB*K] f32 | s [n] f32
-  size_t res_bytes = 0, off_gates = 0, off_s = 0;
-  // host records written by the router kernels (pinned, host-mapped):
-  // routing [maxB*K][2] then priorities [n], each (seq << 32) | payload
+  uint8_t* res_dev = nullptr;  // topk [maxB*K] i32 | gates [maxB*K] f32 | sel [maxB*K] i32 | s [n] f32
+  size_t res_bytes = 0, off_gates = 0, off_sel = 0, off_s = 0;
+  int32_t* slot_tabs = nullptr;  // [L, n] device expert -> slot tables
+  // host records written by the router kernels (pinned, host-mapped), in
+  // kRecSets sets that consecutive router launches take in turn: routing
+  // [maxB*K][2] then priorities [n], each (seq << 32) | payload
   uint64_t* rec_host = nullptr;
   uint64_t* rec_host_dev = nullptr;  // device-visible address of rec_host
-  size_t rec_count = 0;
+  size_t rec_count = 0;              // records of one set
+  uint32_t rec_next = 0;
   std::vector<int32_t> host_T;  // the last routing read from the records [maxB*K]
   std::vector<float> host_g;    // its gates
   std::vector<float> host_s;    // the last priorities [n]
@@ -500,6 +506,7 @@ void free_ctx(spp_ctx* c) {
     if (e) (void)hipEventDestroy(e);
   for (void* p : {static_cast<void*>(c->u_dev), static_cast<void*>(c->x_dev), static_cast<void*>(c->zbuf),
                   static_cast<void*>(c->ztag), static_cast<void*>(c->res_dev), static_cast<void*>(c->counter),
+                  static_cast<void*>(c->slot_tabs),
                   static_cast<void*>(c->partial), static_cast<void*>(c->probe_dev)})
     if (p) (void)hipFree(p);
   if (c->rec_host) (void)hipHostFree(c->rec_host);
@@ -562,15 +569,19 @@ spp_status create_impl(const spp_model_desc* desc, void* stream, spp_ctx** out) 
     return fail(SPP_ENOMEM, "scratch allocation failed");
   const size_t bk = static_cast<size_t>(d.max_batch) * d.K;
   c->off_gates = round_up(bk * sizeof(int32_t), 64);
-  c->off_s = c->off_gates + round_up(bk * sizeof(float), 64);
+  c->off_sel = c->off_gates + round_up(bk * sizeof(float), 64);
+  c->off_s = c->off_sel + round_up(bk * sizeof(int32_t), 64);
   c->res_bytes = c->off_s + round_up(static_cast<size_t>(d.n) * sizeof(float), 64);
   if (hipMalloc(&c->res_dev, c->res_bytes) != hipSuccess) return fail(SPP_ENOMEM, "result buffer allocation failed");
-  c->rec_count = 2 * bk + static_cast<size_t>(d.n);
-  if (hipHostMalloc(&c->rec_host, c->rec_count * sizeof(uint64_t), hipHostMallocMapped | hipHostMallocCoherent) !=
+  if (hipMalloc(&c->slot_tabs, static_cast<size_t>(d.L) * d.n * sizeof(int32_t)) != hipSuccess)
+    return fail(SPP_ENOMEM, "slot table allocation failed");
+  for (int32_t l = 0; l < d.L; ++l) c->layers[l].slot_tab = c->slot_tabs + static_cast<size_t>(l) * d.n;
+  c->rec_count = round_up(2 * bk + static_cast<size_t>(d.n), 8);
+  if (hipHostMalloc(&c->rec_host, kRecSets * c->rec_count * sizeof(uint64_t), hipHostMallocMapped | hipHostMallocCoherent) !=
       hipSuccess)
     return fail(SPP_ENOMEM, "pinned record buffer allocation failed");
   SPP_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->rec_host_dev), c->rec_host, 0));
-  std::memset(c->rec_host, 0, c->rec_count * sizeof(uint64_t));  // sequence 0 is never handed out
+  std::memset(c->rec_host, 0, kRecSets * c->rec_count * sizeof(uint64_t));  // sequence 0 is never handed out
   c->host_T.assign(bk, 0);
   c->host_g.assign(bk, 0.f);
   c->host_s.assign(d.n, 0.f);
@@ -601,19 +612,22 @@ uint32_t next_router_seq(spp_ctx* c) {
   return c->router_seq;
 }
 
-// Wait until the router launch tagged `seq` has written its host records:
+// The set of host records that the next router launch writes.
+uint32_t next_rec_set(spp_ctx* c) { return c->rec_next++ % kRecSets; }
+
+// Wait until the router launch tagged `seq` has written its host records (set `set`):
 // kind 0 the routing of B tokens (expert and gate of every (b, k)), kind 1 the
 // priorities s; then copy their payloads into host_T / host_g or host_s.  A
 // record is this launch's once its high half equals seq; records only ever
 // move on to a newer launch's, so the scan resumes where it stopped.  After
 // about 20 ms of spinning (queued work ahead of the router) the wait blocks on
 // the stream instead; records still missing then are an error.
-spp_status wait_router(spp_ctx* c, uint32_t seq, int kind, int32_t B) {
+spp_status wait_router(spp_ctx* c, uint32_t seq, uint32_t set, int kind, int32_t B) {
   // record arrays: expert ids [max_batch*K], gates [max_batch*K], priorities [n]
   const size_t bkmax = static_cast<size_t>(c->d.max_batch) * c->d.K;
   const size_t bk = static_cast<size_t>(B) * c->d.K;
-  const uint64_t* const part[2] = {kind == 0 ? c->rec_host : c->rec_host + 2 * bkmax,
-                                   kind == 0 ? c->rec_host + bkmax : nullptr};
+  const uint64_t* const recs = c->rec_host + set * c->rec_count;
+  const uint64_t* const part[2] = {kind == 0 ? recs : recs + 2 * bkmax, kind == 0 ? recs + bkmax : nullptr};
   const size_t count = kind == 0 ? bk : static_cast<size_t>(c->d.n);
   const auto t0 = std::chrono::steady_clock::now();
   for (int q = 0; q < 2 && part[q]; ++q) {
@@ -876,8 +890,103 @@ spp_status grouped_ffn(spp_ctx* c, LayerState& ls, const int32_t* T, int32_t B,
   return SPP_OK;
 }
 
-spp_status layer_forward_impl(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int32_t B, int32_t M_max,
-                              int32_t* topk_out, float* gate_out, spp_layer_stats* st_out) {
+// A layer call between its launches and its host side.
+struct Flight {
+  int32_t l = 0, B = 0, M_max = 0;
+  const void* h_in = nullptr;
+  void* h_out = nullptr;
+  bool naive = false, adapter_on = false, predict = false;
+  bool routed = false;  // the FFN and the combine are already enqueued, on the routing's device copy
+  int64_t tau = 0;
+  uint32_t seq = 0, set = 0;
+  TimingSet ts;
+  std::chrono::steady_clock::time_point t_router{};
+};
+
+// Whether layer `ls` needs no decision between its router and its FFN: every
+// expert holds a slot and no copy into one can still be in flight, whatever
+// the routing.  The router launch then names the slots itself
+// (RouterArgs::slot_tab) and the FFN follows it without a trip to the host.
+// With the host's decision in between, the device waits for it in every
+// layer: a resident Qwen-shaped layer at batch 1 took 31.7 us against 24.5
+// without, the 12-layer DeepSeek-shaped step 347 us against 271.  The FFN
+// split is a choice made on the host, so it keeps the host path.
+bool device_routable(spp_ctx* c, LayerState& ls, int32_t B) {
+  if (c->grouped || (c->ffn_overlap && B == 1) || !ls.policy->all_available()) return false;
+  for (int32_t j = 0; j < c->d.S; ++j) {
+    if (!ls.slot_pending[j]) continue;
+    const int32_t ev = ls.slot_event[j];
+    if (hipEventQuery(ls.slot_ready[ev]) != hipSuccess) return false;
+    if (!ls.slot_whole[ev] && hipEventQuery(ls.slot_ready2[ev]) != hipSuccess) return false;
+    ls.slot_pending[j] = 0;  // complete: later calls need not ask again
+  }
+  return true;
+}
+
+// The batch-1 FFN's work list of token b: routed experts in T order, then the
+// shared ones.  T: the routing on the host, or nullptr (the device copy).
+int build_ffn(spp_ctx* c, const LayerState& ls, int32_t b, const int32_t* T, bool split_ok, spp::FfnArgs* fa) {
+  const spp_model_desc& d = c->d;
+  *fa = spp::FfnArgs{};
+  int nW = 0;
+  if (!T) {
+    fa->sel = reinterpret_cast<const int32_t*>(c->res_dev + c->off_sel) + static_cast<size_t>(b) * d.K;
+    fa->nsel = d.K;
+    fa->slots = ls.slots;
+    fa->stride = c->stride;
+  }
+  for (int32_t k = 0; k < d.K; ++k) {
+    if (T) fa->blob[nW] = ls.slots + static_cast<size_t>(ls.policy->slot_of(T[b * d.K + k])) * c->stride;
+    fa->gate_idx[nW] = b * d.K + k;
+    ++nW;
+  }
+  for (int32_t j = 0; j < d.n_shared; ++j) {
+    fa->blob[nW] = static_cast<const uint8_t*>(ls.shared) + static_cast<size_t>(j) * c->stride;
+    fa->gate_idx[nW] = -1;
+    ++nW;
+  }
+  fa->nW = nW;
+  fa->I = d.I;
+  fa->D = d.D;
+  fa->codec = d.expert_codec;
+  fa->x = c->x_dev + static_cast<size_t>(b) * d.D;
+  fa->gates = reinterpret_cast<const float*>(c->res_dev + c->off_gates);
+  fa->partial = c->partial;
+  // sweep order, except under the FFN split, whose two launches need every
+  // workgroup on one item (the units kernel's assignment)
+  if (d.expert_codec == SPP_CODEC_Q4) {
+    if (!split_ok) {
+      const int g = spp::ffn_grid_q4_sweep(nW * d.I, &fa->rounds, &fa->upp);
+      if (g > 0) return g;
+    }
+    return spp::ffn_grid_q4(nW * d.I, d.I, &fa->upw, &fa->upp);
+  }
+  if (!split_ok) {
+    const int g = spp::ffn_grid_slices(nW * d.I, d.D, d.dtype, c->ffn_wgs, &fa->rounds);
+    if (g > 0) return g;
+  }
+  return spp::ffn_grid_for(nW * d.I, c->ffn_wgs, &fa->upw);
+}
+
+// The combine of token b's `grid` partial rows.
+spp_status combine_token(spp_ctx* c, const Flight& fl, int32_t b, int grid) {
+  const spp_model_desc& d = c->d;
+  const size_t row_bytes = static_cast<size_t>(d.D) * c->elem;
+  spp::CombineArgs ca{};
+  ca.partial = c->partial;
+  ca.nparts = grid;
+  ca.D = d.D;
+  ca.res_h = static_cast<const uint8_t*>(fl.h_in) + b * row_bytes;
+  ca.res_u = d.has_proj ? c->u_dev + static_cast<size_t>(b) * d.D : nullptr;
+  ca.out = static_cast<uint8_t*>(fl.h_out) + b * row_bytes;
+  SPP_HIP(spp::launch_combine(ca, d.dtype, c->compute));
+  c->stats.ffn_launches += 1;
+  return SPP_OK;
+}
+
+// Enqueue one layer call: projection and router, and, for a device-routable
+// layer, its FFN and combine.
+spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int32_t B, int32_t M_max, Flight* out) {
   if (spp_status s = check_layer(c, l, true)) return s;
   const spp_model_desc& d = c->d;
   if (!h_in || !h_out) return fail(SPP_EINVAL, "h_in / h_out is NULL");
@@ -885,45 +994,57 @@ spp_status layer_forward_impl(spp_ctx* c, int32_t l, const void* h_in, void* h_o
   if (B < 1 || B > d.max_batch) return fail(SPP_EINVAL, "B must be in [1, max_batch]");
   if (M_max < -1) return fail(SPP_EINVAL, "M_max must be >= -1");
   LayerState& ls = c->layers[l];
+  Flight& fl = *out;
+  fl.l = l;
+  fl.B = B;
+  fl.M_max = M_max;
+  fl.h_in = h_in;
+  fl.h_out = h_out;
   // a prediction for layer l+1: the adapter's priorities, or (Naive Prefetch)
   // the preceding step's experts of layer l+1; the adapter runs only for the first
-  const bool naive = c->prefetch_source == SPP_PREFETCH_PREV_TOKEN;
-  const bool adapter_on = l < d.L - 1 && M_max >= 0 && !naive && ls.A != nullptr && d.r > 0;
-  const bool predict = adapter_on || (naive && l < d.L - 1 && M_max >= 0);
-  if (predict && M_max > 0 && !c->layers[l + 1].bound) return fail(SPP_ESTATE, "next layer not bound");
-  const int64_t tau = ++c->clock;
+  fl.naive = c->prefetch_source == SPP_PREFETCH_PREV_TOKEN;
+  fl.adapter_on = l < d.L - 1 && M_max >= 0 && !fl.naive && ls.A != nullptr && d.r > 0;
+  fl.predict = fl.adapter_on || (fl.naive && l < d.L - 1 && M_max >= 0);
+  if (fl.predict && M_max > 0 && !c->layers[l + 1].bound) return fail(SPP_ESTATE, "next layer not bound");
+  fl.routed = device_routable(c, ls, B);
+  if (fl.routed && ls.slot_tab_version != ls.policy->version()) {
+    SPP_HIP(spp::launch_set_table(ls.slot_tab, ls.policy->expert_slots().data(), d.n, c->compute));
+    ls.slot_tab_version = ls.policy->version();
+  }
+  fl.tau = ++c->clock;
   const int dt = d.dtype;
-  const size_t row_bytes = static_cast<size_t>(d.D) * c->elem;
-
-  TimingSet ts;
+  TimingSet& ts = fl.ts;
   if (c->timing) {
     if (spp_status s = take_set(c, &ts)) return s;
     ts.l = l;
-    ts.predicted = predict;
+    ts.predicted = fl.predict;
     SPP_HIP(hipEventRecord(ts.ev[kEvStart], c->compute));
   }
   if (d.has_proj) {
     spp::ProjArgs pa{h_in, ls.proj, c->u_dev, B, d.D, d.rms_eps};
     SPP_HIP(spp::launch_proj(pa, dt, c->compute));
   }
-  int32_t* topk_dev = reinterpret_cast<int32_t*>(c->res_dev);
-  float* gates_dev = reinterpret_cast<float*>(c->res_dev + c->off_gates);
-  float* s_dev = reinterpret_cast<float*>(c->res_dev + c->off_s);
+  fl.seq = next_router_seq(c);
+  fl.set = next_rec_set(c);
+  uint64_t* rec = c->rec_host_dev + fl.set * c->rec_count;
+  const size_t bkmax = static_cast<size_t>(d.max_batch) * d.K;
   spp::RouterArgs ra{};
   ra.h = h_in;
   ra.u = d.has_proj ? c->u_dev : nullptr;
   ra.Wr = ls.router_w;
-  ra.A = adapter_on ? ls.A : nullptr;
+  ra.A = fl.adapter_on ? ls.A : nullptr;
   ra.Bm = ls.Bm;
   ra.x_out = c->x_dev;
   ra.zbuf = c->zbuf;
   ra.ztag = c->ztag;
-  ra.topk = topk_dev;
-  ra.gates = gates_dev;
-  ra.s = s_dev;
-  ra.route_rec = c->rec_host_dev;
-  ra.gate_rec = c->rec_host_dev + static_cast<size_t>(d.max_batch) * d.K;
-  ra.s_rec = adapter_on ? c->rec_host_dev + 2 * static_cast<size_t>(d.max_batch) * d.K : nullptr;
+  ra.topk = reinterpret_cast<int32_t*>(c->res_dev);
+  ra.gates = reinterpret_cast<float*>(c->res_dev + c->off_gates);
+  ra.slot_tab = fl.routed ? ls.slot_tab : nullptr;
+  ra.sel = reinterpret_cast<int32_t*>(c->res_dev + c->off_sel);
+  ra.s = reinterpret_cast<float*>(c->res_dev + c->off_s);
+  ra.route_rec = rec;
+  ra.gate_rec = rec + bkmax;
+  ra.s_rec = fl.adapter_on ? rec + 2 * bkmax : nullptr;
   ra.counter = c->counter;
   ra.B = B;
   ra.D = d.D;
@@ -933,13 +1054,45 @@ spp_status layer_forward_impl(spp_ctx* c, int32_t l, const void* h_in, void* h_o
   ra.eps = d.rms_eps;
   ra.x_given = 0;
   ra.router_on = 1;
-  ra.seq = next_router_seq(c);
+  ra.seq = fl.seq;
   SPP_HIP(spp::launch_router(ra, dt, c->compute));
-  const auto t_router = std::chrono::steady_clock::now();
+  fl.t_router = std::chrono::steady_clock::now();
   if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvRouted], c->compute));
+  if (!fl.routed) {
+    if (c->ffn_overlap && !c->grouped && B == 1) SPP_HIP(hipEventRecord(c->route_done, c->compute));
+    return SPP_OK;
+  }
+  if (c->timing)
+    for (int k : {kEvWaitA, kEvLoaded, kEvWaitB}) SPP_HIP(hipEventRecord(ts.ev[k], c->compute));
+  for (int32_t b = 0; b < B; ++b) {
+    spp::FfnArgs fa{};
+    const int grid = build_ffn(c, ls, b, nullptr, false, &fa);
+    const bool stamp = c->timing && b == B - 1;
+    SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, stamp ? ts.ev[kEvFfnBegin] : nullptr,
+                            stamp ? ts.ev[kEvFfnEnd] : nullptr));
+    if (spp_status e = combine_token(c, fl, b, grid)) return e;
+  }
+  // no last_read event: while every expert holds a slot nothing is copied
+  // into one, and a change of the table waits for the stream
+  if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvEnd], c->compute));
+  return SPP_OK;
+}
+
+// The host side of a layer call: its routing, the slot decisions (with the
+// copies, the FFN and the combine where the layer was not device-routed), the
+// prefetch for layer l+1, and the outputs.
+spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_out, spp_layer_stats* st_out) {
+  const spp_model_desc& d = c->d;
+  const int32_t l = fl.l, B = fl.B, M_max = fl.M_max;
+  const void* h_in = fl.h_in;
+  void* h_out = fl.h_out;
+  const bool naive = fl.naive, adapter_on = fl.adapter_on, predict = fl.predict;
+  const int64_t tau = fl.tau;
+  const int dt = d.dtype;
+  LayerState& ls = c->layers[l];
+  TimingSet& ts = fl.ts;
   const bool split_ok = c->ffn_overlap && !c->grouped && B == 1;
-  if (split_ok) SPP_HIP(hipEventRecord(c->route_done, c->compute));
-  if (spp_status e = wait_router(c, ra.seq, 0, B)) {
+  if (spp_status e = wait_router(c, fl.seq, fl.set, 0, B)) {
     c->clock = tau - 1;
     if (c->timing) c->free_sets.push_back(ts);
     return e;
@@ -1005,135 +1158,97 @@ spp_status layer_forward_impl(spp_ctx* c, int32_t l, const void* h_in, void* h_o
   if (!ls.policy->on_demand(T, BK, tau, &c->last_loads, &rounds, &why)) return fail(SPP_ESTATE, why);
   st.misses = static_cast<int32_t>(c->last_loads.size());
 
-  // the compute stream's wait for expert copies starts here (on-demand loads
-  // enqueued on it, or its waits for the copy streams)
-  if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvWaitA], c->compute));
-  {
-    std::vector<spp::Transfer> first;
-    for (const spp::Transfer& t : c->last_loads)
-      if (t.round == 0) first.push_back(t);
-    if (c->timing) ts.shared = !first.empty() && prefetch_in_flight(c);
-    if (spp_status e = issue_demand(c, ls, first, ls.last_read_valid ? ls.last_read : nullptr)) return e;
-  }
-  if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvLoaded], c->compute));
-
-  // the batch-1 FFN's work list (routed experts in T order, then the shared ones)
-  auto build_ffn = [&](int32_t b, spp::FfnArgs* fa) -> int {
-    *fa = spp::FfnArgs{};
-    int nW = 0;
-    for (int32_t k = 0; k < d.K; ++k) {
-      fa->blob[nW] = ls.slots + static_cast<size_t>(ls.policy->slot_of(T[b * d.K + k])) * c->stride;
-      fa->gate_idx[nW] = b * d.K + k;
-      ++nW;
-    }
-    for (int32_t j = 0; j < d.n_shared; ++j) {
-      fa->blob[nW] = static_cast<const uint8_t*>(ls.shared) + static_cast<size_t>(j) * c->stride;
-      fa->gate_idx[nW] = -1;
-      ++nW;
-    }
-    fa->nW = nW;
-    fa->I = d.I;
-    fa->D = d.D;
-    fa->codec = d.expert_codec;
-    fa->x = c->x_dev + static_cast<size_t>(b) * d.D;
-    fa->gates = gates_dev;
-    fa->partial = c->partial;
-    // sweep order, except under the FFN split, whose two launches need every
-    // workgroup on one item (the units kernel's assignment)
-    if (d.expert_codec == SPP_CODEC_Q4) {
-      if (!split_ok) {
-        const int g = spp::ffn_grid_q4_sweep(nW * d.I, &fa->rounds, &fa->upp);
-        if (g > 0) return g;
-      }
-      return spp::ffn_grid_q4(nW * d.I, d.I, &fa->upw, &fa->upp);
-    }
-    if (!split_ok) {
-      const int g = spp::ffn_grid_slices(nW * d.I, d.D, d.dtype, c->ffn_wgs, &fa->rounds);
-      if (g > 0) return g;
-    }
-    return spp::ffn_grid_for(nW * d.I, c->ffn_wgs, &fa->upw);
-  };
-  // FFN split (batch 1, on request): the experts whose data is complete now
-  // (resident, or a finished copy) run on compute2 beside the on-demand
-  // copies; the late ones (copied in this call, or still in flight) run on the
-  // compute stream after their copies.  Each workgroup works on one expert, so
-  // the two launches write the partial rows a single launch would write, and
-  // the combine gives the same bits.
-  spp::FfnArgs fa0{};
-  int grid0 = 0;
-  uint32_t late = 0, all_items = 0;
-  bool split = false;
-  if (split_ok) {
-    grid0 = build_ffn(0, &fa0);
-    all_items = fa0.nW >= 32 ? 0xFFFFFFFFu : ((1u << fa0.nW) - 1u);
-    if (d.I % fa0.upw == 0) {
-      for (int32_t k = 0; k < d.K; ++k) {
-        const int32_t slot = ls.policy->slot_of(T[k]);
-        bool pending = ls.slot_inline[slot] != 0;
-        if (!pending && ls.slot_pending[slot]) {
-          const int32_t ev = ls.slot_event[slot];
-          pending = hipEventQuery(ls.slot_ready[ev]) != hipSuccess || (!ls.slot_whole[ev] && hipEventQuery(ls.slot_ready2[ev]) != hipSuccess);
-        }
-        if (pending) late |= 1u << k;
-      }
-      split = late != 0 && late != all_items;
-    }
-    if (split) {
-      if (hipEventQuery(c->route_done) != hipSuccess) SPP_HIP(hipStreamWaitEvent(c->compute2, c->route_done, 0));
-      spp::FfnArgs hits = fa0;
-      hits.skip_mask = late;
-      SPP_HIP(spp::launch_ffn(hits, grid0, dt, c->compute2, nullptr, nullptr));
-      SPP_HIP(hipEventRecord(c->hits_done, c->compute2));
-      c->stats.ffn_split_launches += 1;
-    }
-  }
-
-  // RAW: the FFN reads each needed slot only after its copy completed
-  if (spp_status e = wait_round(c, ls, rounds[0], &st)) return e;
-  if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvWaitB], c->compute));
-  if (batched) {
-    if (spp_status e = grouped_ffn(c, ls, T, B, h_in, h_out, rounds, c->last_loads, &st, ts)) return e;
-  }
   std::chrono::steady_clock::time_point t_ffn{};
-  for (int32_t b = 0; b < B && !batched; ++b) {
-    spp::FfnArgs fa{};
-    const int grid = split_ok ? grid0 : build_ffn(b, &fa);
-    if (split_ok) fa = fa0;
-    if (split) fa.skip_mask = all_items & ~late;
-    const bool stamp = c->timing && b == B - 1;
-    SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, stamp ? ts.ev[kEvFfnBegin] : nullptr,
-                            stamp ? ts.ev[kEvFfnEnd] : nullptr));
-    if (b == 0) t_ffn = std::chrono::steady_clock::now();
-    if (split && hipEventQuery(c->hits_done) != hipSuccess) SPP_HIP(hipStreamWaitEvent(c->compute, c->hits_done, 0));
-    spp::CombineArgs ca{};
-    ca.partial = c->partial;
-    ca.nparts = grid;
-    ca.D = d.D;
-    ca.res_h = static_cast<const uint8_t*>(h_in) + b * row_bytes;
-    ca.res_u = d.has_proj ? c->u_dev + static_cast<size_t>(b) * d.D : nullptr;
-    ca.out = static_cast<uint8_t*>(h_out) + b * row_bytes;
-    SPP_HIP(spp::launch_combine(ca, dt, c->compute));
-    c->stats.ffn_launches += 1;
-  }
-  SPP_HIP(hipEventRecord(ls.last_read, c->compute));
-  ls.last_read_valid = true;
-  if (c->timing) {
-    SPP_HIP(hipEventRecord(ts.ev[kEvEnd], c->compute));
-    c->pending_sets.push_back(ts);
+  if (fl.routed) {
+    // nothing to load and nothing to wait for: one round over available experts
+    st.ready_on_time = static_cast<int32_t>(rounds[0].size());
+    if (c->timing) c->pending_sets.push_back(ts);
+  } else {
+    // the compute stream's wait for expert copies starts here (on-demand loads
+    // enqueued on it, or its waits for the copy streams)
+    if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvWaitA], c->compute));
+    {
+      std::vector<spp::Transfer> first;
+      for (const spp::Transfer& t : c->last_loads)
+        if (t.round == 0) first.push_back(t);
+      if (c->timing) ts.shared = !first.empty() && prefetch_in_flight(c);
+      if (spp_status e = issue_demand(c, ls, first, ls.last_read_valid ? ls.last_read : nullptr)) return e;
+    }
+    if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvLoaded], c->compute));
+
+    // FFN split (batch 1, on request): the experts whose data is complete now
+    // (resident, or a finished copy) run on compute2 beside the on-demand
+    // copies; the late ones (copied in this call, or still in flight) run on the
+    // compute stream after their copies.  Each workgroup works on one expert, so
+    // the two launches write the partial rows a single launch would write, and
+    // the combine gives the same bits.
+    spp::FfnArgs fa0{};
+    int grid0 = 0;
+    uint32_t late = 0, all_items = 0;
+    bool split = false;
+    if (split_ok) {
+      grid0 = build_ffn(c, ls, 0, T, true, &fa0);
+      all_items = fa0.nW >= 32 ? 0xFFFFFFFFu : ((1u << fa0.nW) - 1u);
+      if (d.I % fa0.upw == 0) {
+        for (int32_t k = 0; k < d.K; ++k) {
+          const int32_t slot = ls.policy->slot_of(T[k]);
+          bool pending = ls.slot_inline[slot] != 0;
+          if (!pending && ls.slot_pending[slot]) {
+            const int32_t ev = ls.slot_event[slot];
+            pending = hipEventQuery(ls.slot_ready[ev]) != hipSuccess || (!ls.slot_whole[ev] && hipEventQuery(ls.slot_ready2[ev]) != hipSuccess);
+          }
+          if (pending) late |= 1u << k;
+        }
+        split = late != 0 && late != all_items;
+      }
+      if (split) {
+        if (hipEventQuery(c->route_done) != hipSuccess) SPP_HIP(hipStreamWaitEvent(c->compute2, c->route_done, 0));
+        spp::FfnArgs hits = fa0;
+        hits.skip_mask = late;
+        SPP_HIP(spp::launch_ffn(hits, grid0, dt, c->compute2, nullptr, nullptr));
+        SPP_HIP(hipEventRecord(c->hits_done, c->compute2));
+        c->stats.ffn_split_launches += 1;
+      }
+    }
+
+    // RAW: the FFN reads each needed slot only after its copy completed
+    if (spp_status e = wait_round(c, ls, rounds[0], &st)) return e;
+    if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvWaitB], c->compute));
+    if (batched) {
+      if (spp_status e = grouped_ffn(c, ls, T, B, h_in, h_out, rounds, c->last_loads, &st, ts)) return e;
+    }
+    for (int32_t b = 0; b < B && !batched; ++b) {
+      spp::FfnArgs fa{};
+      const int grid = split_ok ? grid0 : build_ffn(c, ls, b, T, false, &fa);
+      if (split_ok) fa = fa0;
+      if (split) fa.skip_mask = all_items & ~late;
+      const bool stamp = c->timing && b == B - 1;
+      SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, stamp ? ts.ev[kEvFfnBegin] : nullptr,
+                              stamp ? ts.ev[kEvFfnEnd] : nullptr));
+      if (b == 0) t_ffn = std::chrono::steady_clock::now();
+      if (split && hipEventQuery(c->hits_done) != hipSuccess) SPP_HIP(hipStreamWaitEvent(c->compute, c->hits_done, 0));
+      if (spp_status e = combine_token(c, fl, b, grid)) return e;
+    }
+    SPP_HIP(hipEventRecord(ls.last_read, c->compute));
+    ls.last_read_valid = true;
+    if (c->timing) {
+      SPP_HIP(hipEventRecord(ts.ev[kEvEnd], c->compute));
+      c->pending_sets.push_back(ts);
+    }
   }
   {
     if (batched) t_ffn = c->t_grouped_launched;
     const auto us = [](std::chrono::steady_clock::duration dt) {
       return std::chrono::duration<double, std::micro>(dt).count();
     };
-    c->stats.host_route_us += us(t_routed - t_router);
-    c->stats.host_decide_us += us(t_ffn - t_routed);
+    c->stats.host_route_us += us(t_routed - fl.t_router);
+    if (!fl.routed) c->stats.host_decide_us += us(t_ffn - t_routed);
   }
   // prefetch selection for layer l+1, after the FFN launch: the adapter's
   // priorities have records of their own, which the batched selection writes
   // after every token's routing, so the FFN does not wait for them
   if (adapter_on)
-    if (spp_status e = wait_router(c, ra.seq, 1, B)) return e;
+    if (spp_status e = wait_router(c, fl.seq, fl.set, 1, B)) return e;
   LayerState* nx = predict && M_max > 0 ? &c->layers[l + 1] : nullptr;
   c->last_pref.clear();
   c->last_s_valid = predict;
@@ -1185,6 +1300,11 @@ spp_status layer_forward_impl(spp_ctx* c, int32_t l, const void* h_in, void* h_o
   c->stats.waited += st.waited;
   if (st_out) *st_out = st;
   return SPP_OK;
+}
+
+// Give up a call whose launches are enqueued but whose host side will not run.
+void layer_drop(spp_ctx* c, Flight& fl) {
+  if (c->timing) c->free_sets.push_back(fl.ts);
 }
 
 }  // namespace
@@ -1383,7 +1503,8 @@ spp_status adapter_predict(spp_ctx* c, int32_t l, const float* x_dev, int32_t B,
   if (!ls.A || d.r == 0) return fail(SPP_ESTATE, "layer has no adapter");
   spp::RouterArgs ra{};
   ra.u = x_dev;
-  ra.s_rec = c->rec_host_dev + 2 * static_cast<size_t>(d.max_batch) * d.K;
+  const uint32_t set = next_rec_set(c);
+  ra.s_rec = c->rec_host_dev + set * c->rec_count + 2 * static_cast<size_t>(d.max_batch) * d.K;
   ra.A = ls.A;
   ra.Bm = ls.Bm;
   ra.zbuf = c->zbuf;
@@ -1401,7 +1522,7 @@ spp_status adapter_predict(spp_ctx* c, int32_t l, const float* x_dev, int32_t B,
   c->logits_valid = false;
   ra.seq = next_router_seq(c);
   SPP_HIP(spp::launch_router(ra, d.dtype, c->compute));
-  if (spp_status e = wait_router(c, ra.seq, 1, B)) return e;
+  if (spp_status e = wait_router(c, ra.seq, set, 1, B)) return e;
   std::memcpy(s_out, c->host_s.data(), sizeof(float) * d.n);
   return SPP_OK;
 }
@@ -1436,7 +1557,9 @@ spp_status expert_cache_issue_prefetch(spp_ctx* c, int32_t target_layer, const f
 
 spp_status moe_layer_forward(spp_ctx* c, int32_t l, const void* h_in_dev, void* h_out_dev, int32_t B, int32_t M_max,
                              int32_t* topk_out, float* gate_out, spp_layer_stats* stats) {
-  return layer_forward_impl(c, l, h_in_dev, h_out_dev, B, M_max, topk_out, gate_out, stats);
+  Flight fl;
+  if (spp_status s = layer_begin(c, l, h_in_dev, h_out_dev, B, M_max, &fl)) return s;
+  return layer_finish(c, fl, topk_out, gate_out, stats);
 }
 
 spp_status spp_decode_step(spp_ctx* c, const void* h_in_dev, void* h_out_dev, void* h_scratch_dev, int32_t B,
@@ -1449,14 +1572,37 @@ spp_status spp_decode_step(spp_ctx* c, const void* h_in_dev, void* h_out_dev, vo
   const int32_t L = c->d.L, BK = B * c->d.K;
   for (int32_t l = 0; l < L; ++l)
     if (!c->layers[l].bound) return fail(SPP_ESTATE, "every layer must be bound");
-  // the last layer writes h_out; earlier layers alternate between the two buffers
-  const void* src = h_in_dev;
+  // the last layer writes h_out; earlier layers alternate between the two
+  // buffers.  While a layer and the one after it are device-routed, the later
+  // one's launches go out before the earlier one's routing is read, so that
+  // the stream never runs dry (the earlier one's prefetch can find nothing to
+  // load: every expert of the later layer holds a slot).  Timing level 2
+  // measures each layer by itself.
+  const auto dst_of = [&](int32_t l) { return ((L - 1 - l) % 2 == 0) ? h_out_dev : h_scratch_dev; };
+  const auto begin = [&](int32_t l, Flight* fl) {
+    return layer_begin(c, l, l == 0 ? h_in_dev : dst_of(l - 1), dst_of(l), B, M_max, fl);
+  };
+  Flight cur, next;
+  bool ahead = false;  // `cur` of this layer is already enqueued
   for (int32_t l = 0; l < L; ++l) {
-    void* dst = ((L - 1 - l) % 2 == 0) ? h_out_dev : h_scratch_dev;
-    if (spp_status s = layer_forward_impl(c, l, src, dst, B, M_max, topk_out ? topk_out + l * BK : nullptr,
-                                          gate_out ? gate_out + l * BK : nullptr, stats ? stats + l : nullptr))
+    if (!ahead) {
+      cur = Flight{};
+      if (spp_status s = begin(l, &cur)) return s;
+    }
+    ahead = cur.routed && l + 1 < L && c->timing_level < 2 && device_routable(c, c->layers[l + 1], B);
+    if (ahead) {
+      next = Flight{};
+      if (spp_status s = begin(l + 1, &next)) {
+        layer_drop(c, cur);
+        return s;
+      }
+    }
+    if (spp_status s = layer_finish(c, cur, topk_out ? topk_out + l * BK : nullptr,
+                                    gate_out ? gate_out + l * BK : nullptr, stats ? stats + l : nullptr)) {
+      if (ahead) layer_drop(c, next);
       return s;
-    src = dst;
+    }
+    if (ahead) cur = std::move(next);
   }
   return SPP_OK;
 }

@@ -1,0 +1,64 @@
+"""Layers whose experts all hold a slot follow the routing on the device; the
+host decides only where an expert may have to be loaded.  Both must give the
+same routing and the same output bits, whatever slots the experts hold and
+whenever a layer changes from one to the other."""
+import numpy as np
+import pytest
+
+import workload as w
+from workload import gen
+
+pytestmark = pytest.mark.gpu
+
+BASE = w.MoEConfig(name="routed_bf16_D640_n40_k5", L=4, D=640, n=40, K=5, I=100, r=12, S=11, windows=(2,), tokens=8,
+                   seed=41)
+
+
+@pytest.mark.parametrize("cfg", [
+    BASE,                                                  # workgroup-wide router tail (r = 12)
+    BASE.with_(r=16, n_shared=1),                          # single-wave tail, one expert per lane
+    BASE.with_(r=16, n=100, K=6, has_proj=True),           # two experts per lane, projection in front
+    BASE.with_(D=256, I=96, r=8, codec="q4"),
+    BASE.with_(D=128, I=64, r=8, dtype="f32", batch=3, S=17, n_shared=1),
+], ids=["b1_wide_tail", "b1_one_wave", "b1_n100_proj", "q4", "f32_b3"])
+def test_device_and_host_routed_layers_give_the_same_bits(cfg):
+    from paper_2607_24787_amd import spp
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    h0 = gen.hidden_states(cfg, tokens=cfg.tokens)
+    host = OffloadedMoEStack(cfg)                # S < n: every layer decided on the host
+    full = OffloadedMoEStack(cfg, S=cfg.n)       # every expert resident
+    try:
+        table = np.random.default_rng(5).permutation(cfg.n).astype(np.int32)
+        part = table.copy()
+        part[1::3] = -1
+        for l in range(cfg.L):
+            spp.spp_set_slot_table(full.ctx, l, table, np.zeros(cfg.n, np.int64))
+        for t in range(cfg.tokens):
+            if t == 3:  # two layers lose a third of their experts and load them back as they are needed
+                for l in (1, 2):
+                    spp.spp_set_slot_table(full.ctx, l, part, np.zeros(cfg.n, np.int64))
+            if t == 6:  # other slots than before
+                spp.spp_set_slot_table(full.ctx, 1, table[::-1].copy(), np.zeros(cfg.n, np.int64))
+            ref = host.decode_step_from(_in(host, h0[t]), 2)
+            got = full.decode_step_from(_in(full, h0[t]), 2)
+            for l in range(cfg.L):
+                assert np.array_equal(got[l][0], ref[l][0]), (t, l)
+                assert np.array_equal(got[l][1], ref[l][1]), (t, l)
+                distinct = len(set(got[l][0].ravel().tolist()))
+                assert got[l][2].ready_on_time + got[l][2].waited == distinct, (t, l)
+                if t < 3:
+                    assert got[l][2].hits == distinct and got[l][2].misses == 0 and got[l][2].prefetched == 0
+            assert np.array_equal(full.download(full.hbuf[0]), host.download(host.hbuf[0])), t
+        assert spp.spp_get_clock(full.ctx) == cfg.tokens * cfg.L
+        _, stamps = spp.spp_get_slot_table(full.ctx, 0, cfg.n)
+        last = set(got[0][0].ravel().tolist())
+        assert [int(s) == (cfg.tokens - 1) * cfg.L + 1 for s in stamps] == [int(e) in last for e in table]
+    finally:
+        host.close()
+        full.close()
+
+
+def _in(st, h):
+    """A device copy of stored hidden states that outlives the step."""
+    st.h_in = st.torch.from_numpy(np.ascontiguousarray(h).reshape(-1).view(np.uint8).copy()).to(st.device)
+    return st.h_in.data_ptr()
