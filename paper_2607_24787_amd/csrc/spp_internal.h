@@ -25,6 +25,8 @@ struct RouterArgs {
   const void* A;        // [r, D] or nullptr
   const void* Bm;       // [n, r]
   float* x_out;         // [B, D] router input written by block 0 (nullptr: skip)
+  uint16_t* xh;         // [B, D] the same as bf16 pairs x = xh + xl (nullptr: skip)
+  uint16_t* xl;
   float* zbuf;          // [B, n + r] logits then adapter hidden units
   uint64_t* ztag;       // [n + r] the same values tagged (seq << 32) | fp32 bits, for the batch-1
                         // single-wave tails (polled instead of a completion counter), or nullptr
@@ -73,21 +75,22 @@ struct FfnArgs {
 };
 
 // Batched decode: one group = up to kGroupTokens tokens that share one expert.
-constexpr int kGroupTokens = 16;
-struct GroupDesc {
-  const void* blob;                // expert blob (slot or shared expert)
-  int32_t m;                       // tokens in the group, 1..kGroupTokens
-  int32_t tok[kGroupTokens];       // token index b of each row
-  int32_t pair[kGroupTokens];      // output pair: b*K + k (routed) or B*K + b*n_shared + j (shared)
-  int32_t pad;
-};
+constexpr int kGroupTokens = 32;
 
 struct GroupArgs {
-  const GroupDesc* groups;  // [ngroups] (device-visible; host-mapped pinned memory)
-  int ngroups, nsplit, upw; // each group's I units are split into nsplit ranges of upw units
+  const int32_t* topk;      // [B, K] routing (device)
+  const int32_t* slot_tab;  // [n] slot of each expert, -1: not in this launch (device)
+  const uint8_t* slots;     // slot pool: slot j at slots + j * stride
+  const uint8_t* shared;    // shared experts' blobs at the same stride
+  uint64_t stride;
+  int B, K, n, n_shared;    // n_shared: shared experts of this launch (weight 1, every token)
+  int ngroups;              // workgroups are launched for this many groups; those past the last one return
+  int nsplit, upw;          // each expert's I units are split into nsplit ranges of upw units
+  int waves;                // waves per workgroup, 4 or 8; upw at most 48 per wave
   int I, D;
-  const float* x;           // [B, D] router inputs
-  float* ypart;             // [npairs * nsplit, D] partial expert outputs
+  const uint16_t* xh;       // [B, D] router inputs as bf16 pairs x = xh + xl
+  const uint16_t* xl;
+  float* ypart;             // [npairs * nsplit, D] partial outputs; pair b*K + k, then B*K + b*n_shared + j
 };
 
 struct CombineBArgs {
@@ -120,7 +123,7 @@ hipError_t launch_router(const RouterArgs& a, int dtype, hipStream_t st);
 hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop);
 hipError_t launch_combine(const CombineArgs& a, int dtype, hipStream_t st);
 hipError_t launch_proj(const ProjArgs& a, int dtype, hipStream_t st);
-// Grouped (batched) routed-expert FFN, bf16 only; D % 256 == 0.
+// Grouped (batched) routed-expert FFN, bf16 only; D % 256 == 0, I % 16 == 0.
 hipError_t launch_ffn_grouped(const GroupArgs& a, hipStream_t st, hipEvent_t start, hipEvent_t stop);
 hipError_t launch_combine_batched(const CombineBArgs& a, int dtype, hipStream_t st);
 // Host-to-device copies by a copy kernel: n copies of n16 16-byte chunks each,

@@ -99,6 +99,25 @@ __device__ __forceinline__ void store_elem<uint16_t>(void* p, size_t i, float v)
   reinterpret_cast<uint16_t*>(p)[i] = o;
 }
 
+__device__ __forceinline__ uint16_t f32_to_bf16_rne(float v) {
+  uint32_t b = __float_as_uint(v);
+  if ((b & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
+  b += 0x7fffu + ((b >> 16) & 1u);
+  return static_cast<uint16_t>(b >> 16);
+}
+
+__device__ __forceinline__ uint32_t pack2(uint16_t lo, uint16_t hi) {
+  return lo | (static_cast<uint32_t>(hi) << 16);
+}
+
+// x as a bf16 pair hi + lo (to 2^-17 of x), two values per word.
+__device__ __forceinline__ void split2(float a, float b, uint32_t* hi, uint32_t* lo) {
+  const uint16_t ha = f32_to_bf16_rne(a), hb = f32_to_bf16_rne(b);
+  *hi = pack2(ha, hb);
+  *lo = pack2(f32_to_bf16_rne(a - __uint_as_float(static_cast<uint32_t>(ha) << 16)),
+              f32_to_bf16_rne(b - __uint_as_float(static_cast<uint32_t>(hb) << 16)));
+}
+
 // DPP move of a float across lanes (row/bank masks all on).
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
@@ -550,6 +569,12 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
         float* dst = a.x_out + c * V;
 #pragma unroll
         for (int v = 0; v < V; ++v) dst[v] = xv[j][v];
+        if (a.xh) {
+#pragma unroll
+          for (int v = 0; v < V; v += 2)
+            split2(xv[j][v], xv[j][v + 1], reinterpret_cast<uint32_t*>(a.xh) + (c * V + v) / 2,
+                   reinterpret_cast<uint32_t*>(a.xl) + (c * V + v) / 2);
+        }
       }
     }
   }
@@ -1696,190 +1721,372 @@ __global__ __launch_bounds__(64 * kCombGroups) void ffn_combine_kernel(CombineAr
 //     e < 8, w = 0 gate / 1 up -- one wave load of step j is 1 KiB contiguous;
 //   down part, after the 2*I*D gate/up elements: run (s*I + i) holds
 //     W_down[256 s + c][i], c < 256 -- consecutive units of a slice are contiguous.
-// Each workgroup takes one group (up to 16 tokens routed to the same expert)
-// and one range of upw units of that expert (upw = 64, 128, 192 or 256).
-//   phase A: G = X W_gate^T and U = X W_up^T on MFMA (v_mfma_f32_16x16x32_bf16,
-//            tokens padded to the 16 rows of the tile, units as the 16
-//            columns, D as the contraction); wave w owns tiles w, w+8.  x is
-//            staged in LDS per 512-wide chunk as a bf16 pair x = hi + lo
-//            (hi = bf16(x), lo = bf16(x - hi)), and both halves are
-//            multiplied, so the contraction keeps x to ~2^-17 relative (the
-//            weights are bf16 already).  The 16 loads of one 256-column block
-//            (16 KiB contiguous per wave) are all issued before its MFMAs.
-//            H = silu(G) * U into LDS (fp32).
-//   phase B: each wave streams the down runs of the range over its 256-wide
-//            slices of D (kUB units in flight, 4 KiB contiguous) and
-//            accumulates H[t][i] * down_i for every token of the group; one
-//            partial output row per (token, range).
-// ---------------------------------------------------------------------------
-constexpr int kGrpWaves = 8;
-constexpr int kGrpThreads = 64 * kGrpWaves;
-constexpr int kGrpKC = 512;      // x columns staged per chunk (two blocks)
-constexpr int kGrpBlk = 256;     // columns per block: 8 k-steps of 32
-constexpr int kGrpMaxUpw = 256;  // units per range
+// One workgroup takes one group (up to 32 tokens that share an expert) and one
+// range of upw units of that expert.  The groups are not listed anywhere: every
+// workgroup counts the routing's experts in LDS, finds the (expert, 32-token
+// chunk) of its group index and collects that chunk's (token, k) pairs in pair
+// order, so no list crosses the host link and the host need not know the
+// routing.  Shared experts come first, over every token.
+//   phase A: G = X W_gate^T and U = X W_up^T on v_mfma_f32_16x16x32_bf16, tokens
+//     as rows (one or two tiles of 16), units as the 16 columns; wave w owns the
+//     unit tiles w, w + 4, ... of the range.  x comes as a bf16 pair x = hi + lo
+//     straight from global memory in operand order (rows past the group's end
+//     repeat its last token; a few rows sit in the cache), both halves are
+//     multiplied, so the contraction keeps x to ~2^-17 relative.  No barrier:
+//     weights and x of the next columns load while these are multiplied.
+//   H = silu(G) * U goes to LDS as three bf16 terms whose sum is the fp32 value
+//     exactly (8 + 8 + 8 bits, truncated).
+//   phase B: Y = H W_down^T on the same instruction, units as the contraction.
+//     A lane loads 16 bytes (8 columns) of each of 8 units; the B operand of
+//     column c is one byte permute per pair of units, so a wave covers 128
+//     columns x 32 units per step with 8 loads, 32 permutes and 8 MFMAs per
+//     term and token tile.  The first step's loads go out before the barrier.  One partial output row per (token, range).
+// Bound by HBM: at 64 tokens over 128 Qwen-shaped experts the launch takes
+// 183 us (6.5 TB/s of weights; its loads alone 176), from 205 us with x staged
+// through LDS behind barriers, the down product on the vector units and 4
+// ranges; at 256 tokens 215 us from 335 (16 tokens on the vector units, and
+// experts of more than 16 tokens read twice); at 4 tokens 47 us from 56.
+constexpr int kGrpBlk = 256;  // columns per block of the tiled layout: 8 k-steps of 32
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float v) {
-  uint32_t b = __float_as_uint(v);
-  if ((b & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-  b += 0x7fffu + ((b >> 16) & 1u);
-  return static_cast<uint16_t>(b >> 16);
+// H in LDS: [3 terms][kGroupTokens][row]; rows padded to whole steps of 32 units
+// and by 16 bytes (rows then start on different banks)
+__host__ __device__ constexpr int grp_h_row(int upw) { return (upw + 31) / 32 * 32 + 8; }
+// position of unit u in a row: within each step of 32 units, lane group g's
+// contraction index kk is unit 4 kk + g, so that one load of phase B reads
+// four consecutive runs
+__device__ __forceinline__ int grp_h_pos(int u) { return (u & ~31) + 8 * (u & 3) + ((u & 31) >> 2); }
+uint32_t grp_lds_bytes(int upw) { return 3u * kGroupTokens * grp_h_row(upw) * sizeof(uint16_t); }
+
+__device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                 0);
 }
 
-__device__ __forceinline__ uint32_t pack2(uint16_t lo, uint16_t hi) {
-  return lo | (static_cast<uint32_t>(hi) << 16);
+// Phase A of one wave over NT unit tiles and TT token tiles; tile0 + 4 q are
+// the tiles (of the expert), xo[tt] the lane's offset into the x planes.
+template <int W, int NT, int TT>
+__device__ __forceinline__ void grp_phase_a(const GroupArgs& a, const uint16_t* blob, int tile0, int local0, int lane,
+                                            const uint32_t (&xo)[2], uint16_t* s_h, int hrow) {
+  constexpr int KS = NT == 1 ? 4 : 2;  // k-steps of 32 columns per stage
+  const int D = a.D, nb = D / kGrpBlk;
+  struct Stage {
+    u32x4 g[NT][KS], u[NT][KS], xh[TT][KS], xl[TT][KS];
+  } s0, s1;
+  f32x4 accg[NT][TT], accu[NT][TT];
+#pragma unroll
+  for (int q = 0; q < NT; ++q)
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) accg[q][tt] = accu[q][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const u32x4* base[NT];
+#pragma unroll
+  for (int q = 0; q < NT; ++q)
+    base[q] = reinterpret_cast<const u32x4*>(blob) + static_cast<size_t>(tile0 + W * q) * nb * 1024 + lane;
+  auto load = [&](Stage& s, int i) {
+    const int k = i * KS;                            // k-step of 32 columns
+    const size_t po = static_cast<size_t>(k >> 3) * 1024 + (k & 7) * 64;
+#pragma unroll
+    for (int q = 0; q < NT; ++q)
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {
+        s.g[q][j] = __builtin_nontemporal_load(SPP_GLOBAL(u32x4, base[q] + po + j * 64));
+        s.u[q][j] = __builtin_nontemporal_load(SPP_GLOBAL(u32x4, base[q] + po + 512 + j * 64));
+      }
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {
+        s.xh[tt][j] = *SPP_GLOBAL(u32x4, a.xh + xo[tt] + 32 * (k + j));
+        s.xl[tt][j] = *SPP_GLOBAL(u32x4, a.xl + xo[tt] + 32 * (k + j));
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mul = [&](const Stage& s) {
+#pragma unroll
+    for (int j = 0; j < KS; ++j)
+#pragma unroll
+      for (int q = 0; q < NT; ++q)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) {
+          accg[q][tt] = mfma_bf16(s.xh[tt][j], s.g[q][j], accg[q][tt]);
+          accu[q][tt] = mfma_bf16(s.xh[tt][j], s.u[q][j], accu[q][tt]);
+          accg[q][tt] = mfma_bf16(s.xl[tt][j], s.g[q][j], accg[q][tt]);
+          accu[q][tt] = mfma_bf16(s.xl[tt][j], s.u[q][j], accu[q][tt]);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int n = D / (32 * KS);  // even: D is a multiple of 256
+  load(s0, 0);
+  for (int i = 0; i < n; i += 2) {
+    load(s1, i + 1);
+    mul(s0);
+    if (i + 2 < n) load(s0, i + 2);
+    mul(s1);
+  }
+  // this lane holds tokens 16 tt + 4 (lane / 16) + j of unit lane % 16 of each tile
+#pragma unroll
+  for (int q = 0; q < NT; ++q)
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float g = accg[q][tt][j];
+        const float h = g / (1.f + expf(-g)) * accu[q][tt][j];
+        const uint32_t hb = __float_as_uint(h);
+        // exact: each term takes the next 8 significant bits (a non-finite h stays in the first)
+        const float r1 = (hb & 0x7f800000u) == 0x7f800000u ? 0.f : h - __uint_as_float(hb & 0xffff0000u);
+        const uint32_t mb = __float_as_uint(r1);
+        const uint32_t lb = __float_as_uint(r1 - __uint_as_float(mb & 0xffff0000u));
+        uint16_t* o = s_h + (16 * tt + 4 * (lane >> 4) + j) * hrow + grp_h_pos((local0 + W * q) * 16 + (lane & 15));
+        o[0] = static_cast<uint16_t>(hb >> 16);
+        o[kGroupTokens * hrow] = static_cast<uint16_t>(mb >> 16);
+        o[2 * kGroupTokens * hrow] = static_cast<uint16_t>(lb >> 16);
+      }
 }
 
-__global__ __launch_bounds__(kGrpThreads) void ffn_grouped_kernel(GroupArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t s_xh[kGroupTokens * kGrpKC];  // 16 KiB, bf16(x)
-  __shared__ __attribute__((aligned(16))) uint16_t s_xl[kGroupTokens * kGrpKC];  // 16 KiB, bf16(x - hi)
-  __shared__ __attribute__((aligned(16))) float s_h[kGroupTokens * kGrpMaxUpw];  // 16 KiB
+// Phase B's loads of one step: 128 columns of slab `slab` x units u0 + 4 kk + g.
+__device__ __forceinline__ void grp_load_down(const GroupArgs& a, const uint16_t* down, int i0, int nu, int slab, int u0,
+                                              int lane, u32x4 (&r)[8]) {
+  const uint16_t* p = down + (static_cast<size_t>(slab >> 1) * a.I + i0) * kGrpBlk + (slab & 1) * 128 + 8 * (lane & 15);
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk)  // a unit past the range re-reads its last one (zeroed before use)
+    r[kk] = __builtin_nontemporal_load(
+        SPP_GLOBAL(u32x4, p + static_cast<size_t>(min(u0 + 4 * kk + (lane >> 4), nu - 1)) * kGrpBlk));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// r0 holds the loads of the wave's first step.
+template <int W, int TT>
+__device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* down, int i0, int nu, int m, int split,
+                                            int wave, int lane, const uint16_t* s_h, int hrow, const int* s_pair,
+                                            u32x4 (&r0)[8]) {
+  const int D = a.D;
+  const int nsteps = (nu + 31) >> 5;
+  const int nslab = D / 128;
+  const int mine = (nslab - wave + W - 1) / W;  // slabs wave, wave + 4, ...
+  const int total = mine * nsteps;
+  u32x4 r1[8];
+  f32x4 acc[TT][8];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[tt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // steps in order: every step of a slab, then the next slab
+  int lslab = wave, lst = 0;  // of the next load
+  auto advance = [&]() {
+    if (++lst == nsteps) {
+      lst = 0;
+      lslab += W;
+    }
+  };
+  int slab = wave, st = 0;  // of the next multiply
+  auto mul = [&](u32x4 (&r)[8]) {
+    if (32 * st + 32 > nu)  // nu is a multiple of 16: the upper half of the step is past the range
+#pragma unroll
+      for (int kk = 4; kk < 8; ++kk) r[kk] = u32x4{0, 0, 0, 0};
+    u32x4 h[TT][3];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        h[tt][p] = *reinterpret_cast<const u32x4*>(s_h + (p * kGroupTokens + 16 * tt + (lane & 15)) * hrow + 32 * st +
+                                                   8 * (lane >> 4));
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      u32x4 b;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        b[q] = __builtin_amdgcn_perm(r[2 * q + 1][c >> 1], r[2 * q][c >> 1], (c & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+        acc[tt][c] = mfma_bf16(h[tt][2], b, acc[tt][c]);
+        acc[tt][c] = mfma_bf16(h[tt][1], b, acc[tt][c]);
+        acc[tt][c] = mfma_bf16(h[tt][0], b, acc[tt][c]);
+      }
+    }
+    if (++st == nsteps) {
+      // this lane holds tokens 16 tt + 4 (lane / 16) + j of 8 consecutive columns
+      const int d0 = 128 * slab + 8 * (lane & 15);
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int t = 16 * tt + 4 * (lane >> 4) + j;
+          if (t < m) {
+            // ordinary stores: non-temporal ones took 188 us against 183 (64 tokens, 128 Qwen-shaped experts)
+            float* dst = a.ypart + (static_cast<size_t>(s_pair[t]) * a.nsplit + split) * D + d0;
+            reinterpret_cast<f32x4*>(dst)[0] = f32x4{acc[tt][0][j], acc[tt][1][j], acc[tt][2][j], acc[tt][3][j]};
+            reinterpret_cast<f32x4*>(dst)[1] = f32x4{acc[tt][4][j], acc[tt][5][j], acc[tt][6][j], acc[tt][7][j]};
+          }
+        }
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[tt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      st = 0;
+      slab += W;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  advance();
+  for (int it = 0; it < total; it += 2) {
+    if (it + 1 < total) {
+      grp_load_down(a, down, i0, nu, lslab, 32 * lst, lane, r1);
+      advance();
+    }
+    mul(r0);
+    if (it + 2 < total) {
+      grp_load_down(a, down, i0, nu, lslab, 32 * lst, lane, r0);
+      advance();
+    }
+    if (it + 1 < total) mul(r1);
+  }
+}
+
+// The group of this workgroup: its blob, its token count m and, in LDS, its
+// pairs.  Returns false if there is no such group.
+template <int W>
+__device__ __forceinline__ bool grp_find(const GroupArgs& a, int g, int tid, int* s_cnt, int* s_wave, int* s_pair,
+                                         const uint8_t** blob, int* m_out) {
+  const int lane = tid & 63, wave = tid >> 6;
+  const int BK = a.B * a.K, n = a.n;
+  const int cs = (a.B + kGroupTokens - 1) / kGroupTokens;  // chunks of a shared expert
+  const int nsg = a.n_shared * cs;
+  if (g < nsg) {
+    const int j = g / cs, b0 = (g - j * cs) * kGroupTokens;
+    const int m = min(kGroupTokens, a.B - b0);
+    if (tid < m) s_pair[tid] = BK + (b0 + tid) * a.n_shared + j;
+    *blob = a.shared + static_cast<uint64_t>(j) * a.stride;
+    *m_out = m;
+    __syncthreads();
+    return true;
+  }
+  // pairs per expert
+  for (int e = tid; e < n; e += (64 * W)) s_cnt[e] = 0;
+  __syncthreads();
+  for (int p = tid; p < BK; p += (64 * W)) {
+    const int e = a.topk[p];
+    if (static_cast<unsigned>(e) < static_cast<unsigned>(n)) atomicAdd(&s_cnt[e], 1);
+  }
+  __syncthreads();
+  // the (expert, chunk) of group g - nsg, in expert order: every wave scans the
+  // whole table, a contiguous run of experts per lane
+  const int per = (n + 63) / 64;
+  int mine = 0;
+  for (int q = 0; q < per; ++q) {
+    const int e = lane * per + q;
+    if (e < n && a.slot_tab[e] >= 0) mine += (s_cnt[e] + kGroupTokens - 1) / kGroupTokens;
+  }
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o);
+    if (lane >= o) incl += t;
+  }
+  const int want = g - nsg;
+  const uint64_t hit = __ballot(want < incl);
+  if (!hit) return false;
+  const int src = __builtin_ctzll(hit);
+  int e_found = 0, chunk = 0, slot = 0;
+  if (lane == src) {
+    int rest = want - (incl - mine);
+    for (int q = 0; q < per; ++q) {
+      const int e = lane * per + q;
+      if (e >= n || a.slot_tab[e] < 0) continue;
+      const int c = (s_cnt[e] + kGroupTokens - 1) / kGroupTokens;
+      if (rest < c) {
+        e_found = e;
+        chunk = rest;
+        slot = a.slot_tab[e];
+        break;
+      }
+      rest -= c;
+    }
+  }
+  const int e = __builtin_amdgcn_readlane(e_found, src);
+  const int r0 = __builtin_amdgcn_readlane(chunk, src) * kGroupTokens;
+  slot = __builtin_amdgcn_readlane(slot, src);
+  const int cnt = s_cnt[e];
+  // its pairs r0 .. r0 + 31 in pair order: wave w looks through a quarter of the routing
+  const int seg = (BK + (64 * W) - 1) / (64 * W) * 64;
+  int before = 0;
+  for (int p0 = wave * seg; p0 < min(BK, (wave + 1) * seg); p0 += 64)
+    before += __builtin_popcountll(__ballot(p0 + lane < BK && a.topk[min(p0 + lane, BK - 1)] == e));
+  if (lane == 0) s_wave[wave] = before;
+  __syncthreads();
+  int rank0 = -r0;
+  for (int w = 0; w < wave; ++w) rank0 += s_wave[w];
+  for (int p0 = wave * seg; p0 < min(BK, (wave + 1) * seg); p0 += 64) {
+    const bool is = p0 + lane < BK && a.topk[min(p0 + lane, BK - 1)] == e;
+    const uint64_t mask = __ballot(is);
+    const int rank = rank0 + __builtin_popcountll(mask & ((uint64_t{1} << lane) - 1));
+    if (is && rank >= 0 && rank < kGroupTokens) s_pair[rank] = p0 + lane;
+    rank0 += __builtin_popcountll(mask);
+  }
+  __syncthreads();
+  *blob = a.slots + static_cast<uint64_t>(static_cast<uint32_t>(slot)) * a.stride;
+  *m_out = min(kGroupTokens, cnt - r0);
+  return true;
+}
+
+template <int W, int NT>
+__global__ __launch_bounds__(64 * W, 2) void ffn_grouped_kernel(GroupArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t s_h[];
+  __shared__ int s_cnt[kMaxExpertsTopK];
+  __shared__ int s_wave[W];
   __shared__ int s_pair[kGroupTokens];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int D = a.D, I = a.I, nb = D / kGrpBlk;
   const int g = blockIdx.x / a.nsplit, split = blockIdx.x - g * a.nsplit;
-  const GroupDesc* G = a.groups + g;
-  const int m = G->m;
+  const uint8_t* blob8 = nullptr;
+  int m = 0;
+  if (!grp_find<W>(a, g, tid, s_cnt, s_wave, s_pair, &blob8, &m)) return;
+  m = __builtin_amdgcn_readfirstlane(m);
+  const uint16_t* blob = reinterpret_cast<const uint16_t*>(blob8);
   const int i0 = split * a.upw;
-  const int nu = min(a.upw, I - i0);  // a multiple of 16
-  const uint16_t* blob = reinterpret_cast<const uint16_t*>(G->blob);
-  if (tid < kGroupTokens) s_pair[tid] = tid < m ? G->pair[tid] : 0;  // read after the first barrier
-
-  // ---- phase A: gate / up tiles of 16 units on MFMA
+  const int nu = min(a.upw, a.I - i0);  // a multiple of 16
   const int ntiles = nu >> 4;
-  constexpr int kMaxTilesPerWave = kGrpMaxUpw / 16 / kGrpWaves;  // 2
-  f32x4 accg[kMaxTilesPerWave], accu[kMaxTilesPerWave];
-#pragma unroll
-  for (int q = 0; q < kMaxTilesPerWave; ++q) accg[q] = accu[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int krow = lane & 15;        // A row (token) of this lane
-  const int koff = 8 * (lane >> 4);  // this lane's 8-wide k slice inside a 32-wide step
-  // x staging: thread tid covers float4 column c4 = tid % 128 of tokens tid / 128 + 4 q
-  const int sc4 = tid & 127, st0 = tid >> 7;
-  const float* xrow[kGroupTokens / 4];
-#pragma unroll
-  for (int q = 0; q < kGroupTokens / 4; ++q) {
-    const int t = st0 + 4 * q;
-    xrow[q] = a.x + static_cast<size_t>(G->tok[t < m ? t : 0]) * D;
-  }
-  for (int kc = 0; kc < D; kc += kGrpKC) {
-    const int kw = min(kGrpKC, D - kc);  // 512 or 256
-    __syncthreads();                     // previous chunk consumed
-    if (4 * sc4 < kw) {
-      float4 v[kGroupTokens / 4];
-#pragma unroll
-      for (int q = 0; q < kGroupTokens / 4; ++q) v[q] = *SPP_GLOBAL(float4, xrow[q] + kc + 4 * sc4);
-#pragma unroll
-      for (int q = 0; q < kGroupTokens / 4; ++q) {
-        const int t = st0 + 4 * q;
-        const float vv[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-        uint16_t hi[4], lo[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          hi[c] = t < m ? f32_to_bf16_rne(vv[c]) : 0;
-          lo[c] = t < m ? f32_to_bf16_rne(vv[c] - __uint_as_float(static_cast<uint32_t>(hi[c]) << 16)) : 0;
-        }
-        const int o = t * kGrpKC + 4 * sc4;
-        *reinterpret_cast<uint2*>(s_xh + o) = make_uint2(pack2(hi[0], hi[1]), pack2(hi[2], hi[3]));
-        *reinterpret_cast<uint2*>(s_xl + o) = make_uint2(pack2(lo[0], lo[1]), pack2(lo[2], lo[3]));
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kMaxTilesPerWave; ++q) {
-      const int tile = wave + q * kGrpWaves;
-      if (tile >= ntiles) continue;  // wave-uniform
-      const int gt = (i0 >> 4) + tile;
-      for (int bo = 0; bo < kw; bo += kGrpBlk) {
-        const int blk = (kc + bo) / kGrpBlk;
-        const u32x4* pg = reinterpret_cast<const u32x4*>(blob) + static_cast<size_t>(gt * nb + blk) * 2 * 8 * 64 + lane;
-        u32x4 bg[kGrpBlk / 32], bu[kGrpBlk / 32];
-#pragma unroll
-        for (int j = 0; j < kGrpBlk / 32; ++j) {
-          bg[j] = __builtin_nontemporal_load(SPP_GLOBAL(u32x4, pg + j * 64));
-          bu[j] = __builtin_nontemporal_load(SPP_GLOBAL(u32x4, pg + (8 + j) * 64));
-        }
-        __builtin_amdgcn_sched_barrier(0);  // keep the whole block of loads ahead of the MFMAs
-#pragma unroll
-        for (int j = 0; j < kGrpBlk / 32; ++j) {
-          const int ko = krow * kGrpKC + bo + 32 * j + koff;
-          const bf16x8 ah = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(s_xh + ko));
-          const bf16x8 al = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(s_xl + ko));
-          const bf16x8 wg = __builtin_bit_cast(bf16x8, bg[j]), wu = __builtin_bit_cast(bf16x8, bu[j]);
-          accg[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, wg, accg[q], 0, 0, 0);
-          accg[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, wg, accg[q], 0, 0, 0);
-          accu[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, wu, accu[q], 0, 0, 0);
-          accu[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, wu, accu[q], 0, 0, 0);
-        }
-      }
-    }
-  }
-  // this lane holds rows (tokens) 4*(lane/16)+j of column (unit) lane%16
-#pragma unroll
-  for (int q = 0; q < kMaxTilesPerWave; ++q) {
-    const int tile = wave + q * kGrpWaves;
-    if (tile >= ntiles) continue;
-    const int ul = tile * 16 + krow;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int t = 4 * (lane >> 4) + j;
-      const float gv = accg[q][j];
-      s_h[t * kGrpMaxUpw + ul] = gv / (1.f + expf(-gv)) * accu[q][j];
-    }
-  }
-  __syncthreads();
+  const int hrow = grp_h_row(a.upw);
 
-  // ---- phase B: down runs over 256-wide slices of D, all tokens of the group
-  constexpr int kUB = 8;  // down-run loads in flight per lane (nu is a multiple of 16)
-  const uint16_t* down = blob + static_cast<size_t>(2) * I * D;
-  for (int dc = wave; dc < nb; dc += kGrpWaves) {
-    const int d0 = dc * kGrpBlk + lane * 4;
-    float acc[kGroupTokens][4];
+  uint32_t xo[2];
 #pragma unroll
-    for (int t = 0; t < kGroupTokens; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[t][v] = 0.f;
-    const uint16_t* drun = down + (static_cast<size_t>(dc) * I + i0) * kGrpBlk + lane * 4;
-    for (int u = 0; u < nu; u += kUB) {
-      // non-temporal, as the phase-A loads: the down runs are read once per launch
-      uint2 raw[kUB];
-#pragma unroll
-      for (int uu = 0; uu < kUB; ++uu) {
-        const u32x2 t = __builtin_nontemporal_load(SPP_GLOBAL(u32x2, drun + static_cast<size_t>(u + uu) * kGrpBlk));
-        raw[uu] = make_uint2(t.x, t.y);
-      }
-#pragma unroll
-      for (int t = 0; t < kGroupTokens; ++t) {
-        if (t < m) {  // wave-uniform
-          const float4* hp = reinterpret_cast<const float4*>(s_h + t * kGrpMaxUpw + u);
-#pragma unroll
-          for (int p = 0; p < kUB / 4; ++p) {
-            const float4 h4 = hp[p];
-            const float hv[4] = {h4.x, h4.y, h4.z, h4.w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const uint2 r = raw[4 * p + c];
-              acc[t][0] += hv[c] * __uint_as_float(r.x << 16);
-              acc[t][1] += hv[c] * __uint_as_float(r.x & 0xffff0000u);
-              acc[t][2] += hv[c] * __uint_as_float(r.y << 16);
-              acc[t][3] += hv[c] * __uint_as_float(r.y & 0xffff0000u);
-            }
-          }
-        }
-      }
+  for (int tt = 0; tt < 2; ++tt) {
+    const int pair = s_pair[min(16 * tt + (lane & 15), m - 1)];
+    const int tok = pair < a.B * a.K ? pair / a.K : (pair - a.B * a.K) / a.n_shared;
+    xo[tt] = static_cast<uint32_t>(tok) * a.D + 8 * (lane >> 4);
+  }
+  if (nu & 16) {  // the second half of the last step of 32 units
+    for (int k = tid; k < 3 * kGroupTokens * 16; k += (64 * W))
+      s_h[(k >> 4) * hrow + grp_h_pos(nu + (k & 15))] = 0;
+  }
+  const int tile0 = (i0 >> 4) + wave;
+  const int nt = (ntiles - wave + W - 1) / W;  // this wave's tiles (0: none)
+  auto phase_a = [&](auto tt_c) {
+    constexpr int TT = decltype(tt_c)::value;
+    if (nt >= NT) {
+      grp_phase_a<W, NT, TT>(a, blob, tile0, wave, lane, xo, s_h, hrow);
+    } else if (NT > 1 && nt == NT - 1) {
+      grp_phase_a<W, (NT > 1 ? NT - 1 : 1), TT>(a, blob, tile0, wave, lane, xo, s_h, hrow);
+    } else {
+      for (int q = 0; q < nt; ++q)
+        grp_phase_a<W, 1, TT>(a, blob, tile0 + W * q, wave + W * q, lane, xo, s_h, hrow);
     }
-    // non-temporal: the partial rows are read once, by the combine.  Over 128
-    // Qwen-shaped experts at B = 64 (24 MiB of partials) the launch takes
-    // 183 us with no stores, 198 us with these and 204 us with plain stores.
-#pragma unroll
-    for (int t = 0; t < kGroupTokens; ++t) {
-      if (t < m) {
-        float* dst = a.ypart + (static_cast<size_t>(s_pair[t]) * a.nsplit + split) * D + d0;
-        __builtin_nontemporal_store(f32x4{acc[t][0], acc[t][1], acc[t][2], acc[t][3]}, reinterpret_cast<f32x4*>(dst));
-      }
-    }
+  };
+  const uint16_t* down = blob + static_cast<size_t>(2) * a.I * a.D;
+  u32x4 r0[8];  // phase B's first loads cross the barrier in flight
+  const int slab0 = min(wave, a.D / 128 - 1);
+  if (m <= 16) {
+    phase_a(std::integral_constant<int, 1>{});
+    grp_load_down(a, down, i0, nu, slab0, 0, lane, r0);
+    __syncthreads();
+    grp_phase_b<W, 1>(a, down, i0, nu, m, split, wave, lane, s_h, hrow, s_pair, r0);
+  } else {
+    phase_a(std::integral_constant<int, 2>{});
+    grp_load_down(a, down, i0, nu, slab0, 0, lane, r0);
+    __syncthreads();
+    grp_phase_b<W, 2>(a, down, i0, nu, m, split, wave, lane, s_h, hrow, s_pair, r0);
   }
 }
 
@@ -2129,6 +2336,14 @@ __global__ __launch_bounds__(64 * kRowWaves) void router_rows_mfma_kernel(Router
           ur[q].get(f);
           *reinterpret_cast<float4*>(xo + 16 * (c0 + q) + 4 * g) =
               make_float4(f[0] * inv, f[1] * inv, f[2] * inv, f[3] * inv);
+          if (a.xh) {
+            uint2 hi, lo;
+            split2(f[0] * inv, f[1] * inv, &hi.x, &lo.x);
+            split2(f[2] * inv, f[3] * inv, &hi.y, &lo.y);
+            const size_t o = static_cast<size_t>(b0 + i) * D + 16 * (c0 + q) + 4 * g;
+            *reinterpret_cast<uint2*>(a.xh + o) = hi;
+            *reinterpret_cast<uint2*>(a.xl + o) = lo;
+          }
         }
       }
     }
@@ -2470,14 +2685,34 @@ hipError_t launch_proj(const ProjArgs& a, int dtype, hipStream_t st) {
 }
 
 hipError_t launch_ffn_grouped(const GroupArgs& a, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
-  if (a.ngroups <= 0 || a.nsplit <= 0 || (a.upw != 64 && a.upw != 128 && a.upw != 192 && a.upw != 256) ||
-      a.D % kGrpBlk != 0 || a.I % 16 != 0 || a.nsplit * a.upw < a.I || !a.groups || !a.x || !a.ypart)
+  if (a.ngroups <= 0 || a.nsplit <= 0 || a.upw < 16 || a.upw % 16 != 0 || (a.waves != 4 && a.waves != 8) ||
+      a.D % kGrpBlk != 0 || a.I % 16 != 0 || a.nsplit * a.upw < a.I || (a.nsplit - 1) * a.upw >= a.I || !a.topk ||
+      !a.slot_tab || !a.xh || !a.xl || !a.ypart || a.n > kMaxExpertsTopK)
     return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(a.ngroups * a.nsplit));
-  if (start || stop)
-    hipExtLaunchKernelGGL(ffn_grouped_kernel, grid, dim3(kGrpThreads), 0, st, start, stop, 0u, a);
-  else
-    hipLaunchKernelGGL(ffn_grouped_kernel, grid, dim3(kGrpThreads), 0, st, a);
+  const uint32_t lds = grp_lds_bytes(a.upw);
+  const int nt = (a.upw / 16 + a.waves - 1) / a.waves;  // tiles of a wave
+#define SPP_GROUPED(W, NT)                                                                                  \
+  if (start || stop)                                                                                        \
+    hipExtLaunchKernelGGL((ffn_grouped_kernel<W, NT>), grid, dim3(64 * W), lds, st, start, stop, 0u, a);    \
+  else                                                                                                      \
+    hipLaunchKernelGGL((ffn_grouped_kernel<W, NT>), grid, dim3(64 * W), lds, st, a)
+  if (a.waves == 4) {
+    switch (nt) {
+      case 1: SPP_GROUPED(4, 1); break;
+      case 2: SPP_GROUPED(4, 2); break;
+      case 3: SPP_GROUPED(4, 3); break;
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (nt) {
+      case 1: SPP_GROUPED(8, 1); break;
+      case 2: SPP_GROUPED(8, 2); break;
+      case 3: SPP_GROUPED(8, 3); break;
+      default: return hipErrorInvalidValue;
+    }
+  }
+#undef SPP_GROUPED
   return hipGetLastError();
 }
 

@@ -135,15 +135,11 @@ struct spp_ctx {
   uint8_t* probe_dev = nullptr;  // one blob, for copy profiling
   // batched decode (B > 1, bf16): expert groups and partial outputs
   bool grouped = false;
-  int max_groups = 0, max_nsplit = 0;
-  spp::GroupDesc* groups_dev = nullptr;   // device address of groups_host (host-mapped)
-  spp::GroupDesc* groups_host = nullptr;  // per-layer group list, pinned and device-mapped: the grouped
-                                          // kernel reads it in place (rewritten only after the next
-                                          // router, i.e. after the previous FFN, has finished)
+  uint16_t* xh_dev = nullptr;  // [maxB, D] router inputs as bf16 pairs, xh then xl
+  uint16_t* xl_dev = nullptr;
+  int32_t* round_tab = nullptr;  // [n] slots of one round's experts (host-decided layers)
   float* ypart = nullptr;
   std::vector<hipEvent_t> round_done;  // per on-demand round: its FFN launch finished
-  std::vector<int32_t> grp_start, grp_fill, grp_order;  // group building scratch (per call)
-  std::vector<int> grp_rstart, grp_rcount;
   int64_t clock = 0;
   int ffn_wgs = 512;  // about this many workgroups share one batch-1 FFN launch (bf16/fp32 experts)
   // test hooks
@@ -180,6 +176,39 @@ namespace {
 bool tiled_layout(const spp_model_desc& d) {
   return d.expert_codec == SPP_CODEC_PLAIN && d.max_batch > 1 && d.dtype == SPP_DTYPE_BF16 && d.D % 256 == 0 &&
          d.I % 16 == 0;
+}
+
+// Unit ranges of the grouped FFN: nsplit ranges of upw units (a multiple of
+// 16), by workgroups of 8 waves above 192 units and of 4 below (at most three
+// tiles of 16 per wave).  Two things cost time: compute units left without a
+// workgroup (or with one less than others), and every further range, which
+// writes its partial rows and reads x again.  nsplit minimises
+//   1 / fill + nsplit (0.025 + 0.0016 m),
+// fill = the share of busy compute units over the rounds of workgroups that
+// the expected number of groups gives, m = tokens per group.  Measured (FFN
+// launch, us): 64 tokens over 128 Qwen-shaped experts (126 groups) 2 ranges
+// 183, 4 ranges 195, 6 ranges 216; 256 tokens 215 / 237 / 279 (8); 4 tokens
+// (29 groups) 8 ranges 47, 12 ranges 53, 4 ranges 63; 13 tokens of the
+// DeepSeek shape (48 groups) 5 ranges 59, 10 ranges 62, 3 ranges 73.  A
+// function of the shape and the batch alone, so that a layer gives the same
+// bits whichever of its experts are resident.
+constexpr int kGroupMinUnits = 32, kGroupMaxUnits = 384;
+void grouped_split(const spp_model_desc& d, int32_t B, int num_cu, int* nsplit, int* upw) {
+  const double pairs = static_cast<double>(B) * d.K;
+  const double active = d.n * (1.0 - std::pow(1.0 - static_cast<double>(d.K) / d.n, B));
+  const double m = pairs / active;
+  const double groups = std::max(1.0, active * std::max(1.0, m / spp::kGroupTokens + 0.5) +
+                                          d.n_shared * ((B + spp::kGroupTokens - 1) / spp::kGroupTokens));
+  double best = 0.0;
+  *nsplit = 0;
+  for (int ns = (d.I + kGroupMaxUnits - 1) / kGroupMaxUnits; ns <= (d.I + kGroupMinUnits - 1) / kGroupMinUnits; ++ns) {
+    const double rounds = groups * ns / num_cu;
+    const double cost = std::ceil(rounds) / rounds + ns * (0.025 + 0.0016 * std::min(m, 1.0 * spp::kGroupTokens));
+    if (*nsplit && cost >= best) continue;
+    best = cost;
+    *upw = ((d.I + ns - 1) / ns + 15) / 16 * 16;
+    *nsplit = (d.I + *upw - 1) / *upw;
+  }
 }
 
 // Bytes of one expert blob (before the 4 KiB stride rounding).
@@ -510,7 +539,8 @@ void free_ctx(spp_ctx* c) {
                   static_cast<void*>(c->partial), static_cast<void*>(c->probe_dev)})
     if (p) (void)hipFree(p);
   if (c->rec_host) (void)hipHostFree(c->rec_host);
-  if (c->groups_host) (void)hipHostFree(c->groups_host);
+  if (c->xh_dev) (void)hipFree(c->xh_dev);
+  if (c->round_tab) (void)hipFree(c->round_tab);
   if (c->ypart) (void)hipFree(c->ypart);
   if (c->copy) (void)hipStreamDestroy(c->copy);
   if (c->copy2) (void)hipStreamDestroy(c->copy2);
@@ -588,14 +618,17 @@ spp_status create_impl(const spp_model_desc* desc, void* stream, spp_ctx** out) 
   // batched decode runs the routed experts as grouped MFMA contractions
   c->grouped = tiled_layout(d);
   if (c->grouped) {
-    c->max_groups = d.max_batch * d.K + d.n_shared * ((d.max_batch + spp::kGroupTokens - 1) / spp::kGroupTokens);
-    c->max_nsplit = (d.I + 63) / 64;
-    const size_t npairs = static_cast<size_t>(d.max_batch) * (d.K + d.n_shared);
-    if (hipHostMalloc(&c->groups_host, sizeof(spp::GroupDesc) * c->max_groups,
-                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-        hipMalloc(&c->ypart, npairs * c->max_nsplit * d.D * sizeof(float)) != hipSuccess)
+    size_t rows = 0;  // partial rows of the batch that needs the most
+    for (int32_t B = 1, ns = 0, upw = 0; B <= d.max_batch; ++B) {
+      grouped_split(d, B, c->num_cu, &ns, &upw);
+      rows = std::max(rows, static_cast<size_t>(B) * (d.K + d.n_shared) * ns);
+    }
+    const size_t xn = static_cast<size_t>(d.max_batch) * d.D;
+    if (hipMalloc(&c->xh_dev, 2 * xn * sizeof(uint16_t)) != hipSuccess ||
+        hipMalloc(&c->round_tab, d.n * sizeof(int32_t)) != hipSuccess ||
+        hipMalloc(&c->ypart, rows * d.D * sizeof(float)) != hipSuccess)
       return fail(SPP_ENOMEM, "batched-decode buffers allocation failed");
-    SPP_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&c->groups_dev), c->groups_host, 0));
+    c->xl_dev = c->xh_dev + xn;
   }
   SPP_HIP(hipMemset(c->counter, 0, 256));
   SPP_HIP(hipMemset(c->ztag, 0, static_cast<size_t>(d.n + d.r) * sizeof(uint64_t)));  // seq 0 is never handed out
@@ -768,81 +801,64 @@ spp_status round_event(spp_ctx* c, size_t r, hipEvent_t* out) {
   return SPP_OK;
 }
 
-// Batched decode: group the (token, k) pairs by expert (ascending expert,
-// ascending token, at most kGroupTokens per group) round by round, with the
-// shared experts in round 0; upload the list once; per round: the round's
-// copies (waiting for the previous round's FFN, whose slots they reuse), the
-// compute stream's waits for them, one grouped FFN launch; then one combine.
-spp_status grouped_ffn(spp_ctx* c, LayerState& ls, const int32_t* T, int32_t B,
-                       const void* h_in, void* h_out, const std::vector<spp::Round>& rounds,
-                       const std::vector<spp::Transfer>& loads, spp_layer_stats* st, TimingSet& ts) {
+// One grouped FFN launch over the experts that `slot_tab` (device) gives a
+// slot, `nexp` at most, with the shared experts if wanted.
+spp_status launch_groups(spp_ctx* c, const LayerState& ls, int32_t B, const int32_t* slot_tab, int32_t nexp,
+                         bool shared, hipEvent_t start, hipEvent_t stop) {
   const spp_model_desc& d = c->d;
   const int32_t BK = B * d.K;
-  bool launched = false;  // the first grouped launch stamps c->t_grouped_launched
-  c->t_grouped_launched = std::chrono::steady_clock::now();
-  // the (token, k) pairs of each expert in pair order: a stable counting sort
-  // into context scratch (pair p belongs to token p / K)
-  std::vector<int32_t>& start = c->grp_start;
-  std::vector<int32_t>& order = c->grp_order;
-  start.assign(d.n + 1, 0);
-  for (int32_t p = 0; p < BK; ++p) start[T[p] + 1] += 1;
-  for (int32_t e = 0; e < d.n; ++e) start[e + 1] += start[e];
-  c->grp_fill.assign(start.begin(), start.end() - 1);
-  order.resize(BK);
-  for (int32_t p = 0; p < BK; ++p) order[c->grp_fill[T[p]]++] = p;
-  int ng = 0;
-  // groups of up to kGroupTokens rows; row i of `count` is (tok(i), pair(i))
-  auto add = [&](const void* blob, int32_t count, auto row) -> bool {
-    for (int32_t r0 = 0; r0 < count; r0 += spp::kGroupTokens) {
-      if (ng >= c->max_groups) return false;
-      spp::GroupDesc& g = c->groups_host[ng++];
-      g.blob = blob;
-      g.m = std::min(spp::kGroupTokens, count - r0);
-      for (int32_t t = 0; t < spp::kGroupTokens; ++t) {
-        const bool used = t < g.m;
-        const std::pair<int32_t, int32_t> tp = used ? row(r0 + t) : std::pair<int32_t, int32_t>{0, 0};
-        g.tok[t] = tp.first;
-        g.pair[t] = tp.second;
-      }
-      g.pad = 0;
-    }
-    return true;
-  };
-  std::vector<int>& rstart = c->grp_rstart;
-  std::vector<int>& rcount = c->grp_rcount;
-  rstart.assign(rounds.size(), 0);
-  rcount.assign(rounds.size(), 0);
-  int maxg = 0;
-  for (size_t r = 0; r < rounds.size(); ++r) {
-    rstart[r] = ng;
-    for (const auto& es : rounds[r]) {
-      const int32_t* rows = order.data() + start[es.first];
-      const auto routed = [&](int32_t i) { return std::pair<int32_t, int32_t>{rows[i] / d.K, rows[i]}; };
-      if (!add(ls.slots + static_cast<size_t>(es.second) * c->stride, start[es.first + 1] - start[es.first], routed))
-        return fail(SPP_ESTATE, "group list overflow");
-    }
-    if (r == 0)
-      for (int32_t j = 0; j < d.n_shared; ++j) {
-        const auto shared = [&](int32_t b) { return std::pair<int32_t, int32_t>{b, BK + b * d.n_shared + j}; };
-        if (!add(static_cast<const uint8_t*>(ls.shared) + static_cast<size_t>(j) * c->stride, B, shared))
-          return fail(SPP_ESTATE, "group list overflow");
-      }
-    rcount[r] = ng - rstart[r];
-    maxg = std::max(maxg, rcount[r]);
-  }
-  // unit ranges: the widest of 192 and 128 units that divides I and still
-  // gives the largest round about two workgroups per compute unit, else 64.
-  // Fewer ranges write fewer partial rows and stage x less often: over 128
-  // Qwen-shaped experts at B = 64, 192 units (512 workgroups) took 193.7 us
-  // against 198.4 for 128 (768) and 207.8 for 256 (384)
-  int upw = 64;
-  for (int cand : {192, 128})
-    if (d.I % cand == 0 && 10L * maxg * (d.I / cand) >= 19L * c->num_cu) {
-      upw = cand;
-      break;
-    }
-  const int nsplit = (d.I + upw - 1) / upw;
-  if (nsplit > c->max_nsplit) return fail(SPP_ESTATE, "unit split exceeds the partial buffer");
+  spp::GroupArgs ga{};
+  ga.topk = reinterpret_cast<const int32_t*>(c->res_dev);
+  ga.slot_tab = slot_tab;
+  ga.slots = ls.slots;
+  ga.shared = static_cast<const uint8_t*>(ls.shared);
+  ga.stride = c->stride;
+  ga.B = B;
+  ga.K = d.K;
+  ga.n = d.n;
+  ga.n_shared = shared ? d.n_shared : 0;
+  // at most one group per pair, and at most one partly filled group per expert
+  ga.ngroups = std::min(BK, nexp + BK / spp::kGroupTokens) +
+               ga.n_shared * ((B + spp::kGroupTokens - 1) / spp::kGroupTokens);
+  grouped_split(d, B, c->num_cu, &ga.nsplit, &ga.upw);
+  ga.waves = ga.upw > 192 ? 8 : 4;
+  ga.I = d.I;
+  ga.D = d.D;
+  ga.xh = c->xh_dev;
+  ga.xl = c->xl_dev;
+  ga.ypart = c->ypart;
+  if (ga.ngroups == 0) return SPP_OK;
+  SPP_HIP(spp::launch_ffn_grouped(ga, c->compute, start, stop));
+  return SPP_OK;
+}
+
+spp_status combine_batch(spp_ctx* c, int32_t B, const void* h_in, void* h_out) {
+  const spp_model_desc& d = c->d;
+  spp::CombineBArgs cb{};
+  int upw = 0;
+  grouped_split(d, B, c->num_cu, &cb.nsplit, &upw);
+  cb.ypart = c->ypart;
+  cb.gates = reinterpret_cast<const float*>(c->res_dev + c->off_gates);
+  cb.B = B;
+  cb.K = d.K;
+  cb.n_shared = d.n_shared;
+  cb.D = d.D;
+  cb.res_h = h_in;
+  cb.res_u = d.has_proj ? c->u_dev : nullptr;
+  cb.out = h_out;
+  SPP_HIP(spp::launch_combine_batched(cb, d.dtype, c->compute));
+  c->stats.ffn_launches += 1;
+  return SPP_OK;
+}
+
+// Batched decode of a host-decided layer.  Per round: the round's copies
+// (waiting for the previous round's FFN, whose slots they reuse), the compute
+// stream's waits for them, the round's slot table, and one grouped FFN launch
+// (the shared experts in the first); then one combine.
+spp_status grouped_ffn(spp_ctx* c, LayerState& ls, int32_t B, const void* h_in, void* h_out,
+                       const std::vector<spp::Round>& rounds, const std::vector<spp::Transfer>& loads,
+                       spp_layer_stats* st, TimingSet& ts) {
+  std::vector<int32_t> table(c->d.n);
   for (size_t r = 0; r < rounds.size(); ++r) {
     if (r > 0) {
       hipEvent_t done;
@@ -858,36 +874,17 @@ spp_status grouped_ffn(spp_ctx* c, LayerState& ls, const int32_t* T, int32_t B,
       if (c->timing)
         if (spp_status e = record_extra(c, ts)) return e;
     }
-    if (rcount[r] == 0) continue;
-    spp::GroupArgs ga{};
-    ga.groups = c->groups_dev + rstart[r];
-    ga.ngroups = rcount[r];
-    ga.nsplit = nsplit;
-    ga.upw = upw;
-    ga.I = d.I;
-    ga.D = d.D;
-    ga.x = c->x_dev;
-    ga.ypart = c->ypart;
     const bool first = r == 0, last = r + 1 == rounds.size();
-    SPP_HIP(spp::launch_ffn_grouped(ga, c->compute, c->timing && first ? ts.ev[kEvFfnBegin] : nullptr,
-                                    c->timing && last ? ts.ev[kEvFfnEnd] : nullptr));
-    if (!launched) c->t_grouped_launched = std::chrono::steady_clock::now();
-    launched = true;
+    std::fill(table.begin(), table.end(), -1);
+    for (const auto& es : rounds[r]) table[es.first] = es.second;
+    SPP_HIP(spp::launch_set_table(c->round_tab, table.data(), c->d.n, c->compute));
+    if (spp_status e = launch_groups(c, ls, B, c->round_tab, static_cast<int32_t>(rounds[r].size()), first,
+                                     c->timing && first ? ts.ev[kEvFfnBegin] : nullptr,
+                                     c->timing && last ? ts.ev[kEvFfnEnd] : nullptr))
+      return e;
+    if (first) c->t_grouped_launched = std::chrono::steady_clock::now();
   }
-  spp::CombineBArgs cb{};
-  cb.ypart = c->ypart;
-  cb.gates = reinterpret_cast<const float*>(c->res_dev + c->off_gates);
-  cb.B = B;
-  cb.K = d.K;
-  cb.n_shared = d.n_shared;
-  cb.nsplit = nsplit;
-  cb.D = d.D;
-  cb.res_h = h_in;
-  cb.res_u = d.has_proj ? c->u_dev : nullptr;
-  cb.out = h_out;
-  SPP_HIP(spp::launch_combine_batched(cb, d.dtype, c->compute));
-  c->stats.ffn_launches += 1;
-  return SPP_OK;
+  return combine_batch(c, B, h_in, h_out);
 }
 
 // A layer call between its launches and its host side.
@@ -912,7 +909,7 @@ struct Flight {
 // without, the 12-layer DeepSeek-shaped step 347 us against 271.  The FFN
 // split is a choice made on the host, so it keeps the host path.
 bool device_routable(spp_ctx* c, LayerState& ls, int32_t B) {
-  if (c->grouped || (c->ffn_overlap && B == 1) || !ls.policy->all_available()) return false;
+  if ((c->ffn_overlap && !c->grouped && B == 1) || !ls.policy->all_available()) return false;
   for (int32_t j = 0; j < c->d.S; ++j) {
     if (!ls.slot_pending[j]) continue;
     const int32_t ev = ls.slot_event[j];
@@ -1035,6 +1032,8 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   ra.A = fl.adapter_on ? ls.A : nullptr;
   ra.Bm = ls.Bm;
   ra.x_out = c->x_dev;
+  ra.xh = c->xh_dev;
+  ra.xl = c->xl_dev;
   ra.zbuf = c->zbuf;
   ra.ztag = c->ztag;
   ra.topk = reinterpret_cast<int32_t*>(c->res_dev);
@@ -1064,7 +1063,13 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   }
   if (c->timing)
     for (int k : {kEvWaitA, kEvLoaded, kEvWaitB}) SPP_HIP(hipEventRecord(ts.ev[k], c->compute));
-  for (int32_t b = 0; b < B; ++b) {
+  if (c->grouped) {
+    if (spp_status e = launch_groups(c, ls, B, ls.slot_tab, d.n, true, c->timing ? ts.ev[kEvFfnBegin] : nullptr,
+                                     c->timing ? ts.ev[kEvFfnEnd] : nullptr))
+      return e;
+    if (spp_status e = combine_batch(c, B, h_in, h_out)) return e;
+  }
+  for (int32_t b = 0; b < B && !c->grouped; ++b) {
     spp::FfnArgs fa{};
     const int grid = build_ffn(c, ls, b, nullptr, false, &fa);
     const bool stamp = c->timing && b == B - 1;
@@ -1215,7 +1220,7 @@ spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_o
     if (spp_status e = wait_round(c, ls, rounds[0], &st)) return e;
     if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvWaitB], c->compute));
     if (batched) {
-      if (spp_status e = grouped_ffn(c, ls, T, B, h_in, h_out, rounds, c->last_loads, &st, ts)) return e;
+      if (spp_status e = grouped_ffn(c, ls, B, h_in, h_out, rounds, c->last_loads, &st, ts)) return e;
     }
     for (int32_t b = 0; b < B && !batched; ++b) {
       spp::FfnArgs fa{};

@@ -62,3 +62,46 @@ def _in(st, h):
     """A device copy of stored hidden states that outlives the step."""
     st.h_in = st.torch.from_numpy(np.ascontiguousarray(h).reshape(-1).view(np.uint8).copy()).to(st.device)
     return st.h_in.data_ptr()
+
+
+# batched: groups of more than 16 and of more than 32 tokens, shared experts over several chunks of tokens, unit
+# ranges that end in half a step of 32 units, ranges wide enough for workgroups of 8 waves, more experts than lanes
+GROUPED = w.MoEConfig(name="grouped_bf16_D512_n6_k2_I400", L=2, D=512, n=6, K=2, I=400, r=8, S=6, windows=(1,),
+                      tokens=2, batch=40, n_shared=1, seed=43)
+
+
+@pytest.mark.parametrize("cfg", [
+    GROUPED,
+    GROUPED.with_(n=4, K=1, I=1104, n_shared=2, batch=75),
+    GROUPED.with_(n=140, K=3, I=784, D=256, n_shared=0, batch=90, r=16),
+    GROUPED.with_(n=24, K=5, I=16, D=768, batch=3, has_proj=True),
+    GROUPED.with_(n=9, K=9, I=336, D=1280, batch=2),
+], ids=["chunks", "wide_ranges", "n140", "one_tile", "k_eq_n"])
+@pytest.mark.parametrize("resident", [True, False], ids=["resident", "rounds"])
+def test_grouped_layers_against_the_oracle(cfg, resident):
+    from lockstep import run_lockstep
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    st = OffloadedMoEStack(cfg, S=cfg.n if resident else max(cfg.n // 2, 1))
+    try:
+        rep = run_lockstep(st, cfg, cfg.tokens, 1)
+    finally:
+        st.close()
+    assert rep.max_ulp_h <= 1.0 + 1e-9 and rep.max_err_g <= 1e-5
+    assert len(rep.exempt) <= 1
+
+
+def test_grouped_layers_give_the_same_bits_whatever_is_resident():
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    cfg = GROUPED.with_(n=24, K=4, I=208, batch=21, n_shared=0)
+    h0 = gen.hidden_states(cfg, tokens=2)
+    outs = []
+    for S in (24, 13, 5):
+        st = OffloadedMoEStack(cfg, S=S)
+        try:
+            outs.append([])
+            for t in range(2):
+                st.decode_step_from(_in(st, h0[t]), 1)
+                outs[-1].append(st.download(st.hbuf[0]))
+        finally:
+            st.close()
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
