@@ -757,11 +757,10 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
 }
 
 // ---------------------------------------------------------------------------
-// Router for B > 1 tokens, in two launches.
-//   rows:   router_rows_mfma_kernel (below, with the MFMA kernels);
-//   select: one workgroup per token -- Top-K, gates and the adapter
-//           distribution; the last workgroup to finish sums the distributions
-//           over the tokens, in token order, into s.
+// Selection for B > 1 tokens (their rows: router_rows_kernel, below with the
+// MFMA kernels): one workgroup per token -- Top-K, gates and
+// the adapter distribution; the last workgroup to finish sums the
+// distributions over the tokens, in token order, into s.
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kThreads) void router_select_kernel(RouterArgs a) {
@@ -840,8 +839,8 @@ __global__ __launch_bounds__(kThreads) void router_select_kernel(RouterArgs a) {
   if (tid == 0) __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Selection for B > 1 tokens with one wave per token (bf16, n <= 64 EPL,
-// K <= 64, r <= 64 and a multiple of 8): lane l holds experts l + 64 q.  Top-K
+// Selection for B > 1 tokens with one wave per token (n <= 64 EPL, K <= 64;
+// with an adapter: bf16, r <= 64 and a multiple of 8): lane l holds experts l + 64 q.  Top-K
 // by K rounds of a wave maximum over the 32-bit logit order (the lowest index
 // taking a tie), the gates, and the adapter distribution from B's rows of the
 // lane's experts in registers -- the products, maxima and sums of
@@ -2198,53 +2197,59 @@ __global__ __launch_bounds__(kThreads) void proj_kernel(ProjArgs a) {
   }
 }
 
-// Router and adapter-A rows for B > 1 tokens on fp32 MFMA:
+// Router and adapter-A rows for B > 1 tokens:
 //   z[b][row] = inv_b * sum_k u[b][k] W[row][k],  inv_b = 1 / rms(u_b)
 // (inv_b = 1 when u already is the router input x); the router rows, then the
 // adapter rows, form the row axis, written to zbuf at their columns.  One
-// workgroup per 16 tokens x 16 rows; its waves split D into runs of 16
-// columns.  A lane loads 4 consecutive columns of its token row and of its
-// weight row, and 4 MFMA steps consume them: step q multiplies columns
-// 16c + 4(lane/16) + q (the step's k index is lane/16), so the four steps
-// cover the run exactly once.  Products are exact in fp32 (bf16 weights widen
-// exactly); the waves' partial tiles and partial sums of squares add in wave
-// order through LDS.  The workgroups also write x = inv_b * u_b (x_out), each
-// a slice of D for its tokens.
+// workgroup per 16 tokens x 16 rows; its waves split D into runs of KSW steps
+// of 32 columns, every load of a run in flight at once: a lane loads 8
+// consecutive columns of its token row and of its weight row.  bf16 states and
+// weights multiply on the bf16 MFMA; an fp32 operand on the fp32 MFMA, step q
+// of 8 taking column 8 (lane/16) + q of every lane (bf16 weights widen
+// exactly).  Products are exact either way where one operand is bf16.  The
+// waves' partial tiles and sums of squares add in wave order through LDS.  x =
+// inv_b u_b (and its bf16 pair) goes out from the registers that hold u, each
+// row tile writing its share of the steps.
+// Bound by latency (cold weights, one round of loads): 64 tokens of the Qwen
+// shape 10.2 us with fp32 states in front (12.0 with 8-byte loads in two
+// rounds and a second read of u for x), 4 tokens 6.4 us from 9.2.  Measured
+// and not kept: selecting in the last workgroup of a token tile instead of a
+// launch of one wave per token (4 tokens 10.1 us against 6.4 + 3.2, 64 tokens
+// with an adapter 27 against 10.2 + 7.5: two tokens per wave in series), and
+// 16 waves (9.6 us, but fp32 9.1 against 6.7).
 constexpr int kRowWaves = 8;
-constexpr int kRowRuns = 16;  // runs of 16 columns per wave and pass, loads in flight together
 
+// 8 consecutive elements of a row as raw bits
 template <typename T>
-__device__ __forceinline__ void widen4(const uint2 r, float* f) {
-  f[0] = __uint_as_float(r.x << 16);
-  f[1] = __uint_as_float(r.x & 0xffff0000u);
-  f[2] = __uint_as_float(r.y << 16);
-  f[3] = __uint_as_float(r.y & 0xffff0000u);
-}
-
-// 4 consecutive elements of a row as raw bits: 8 bytes (bf16) or 16 bytes (fp32)
-template <typename T>
-struct Raw4;
+struct Raw8;
 template <>
-struct Raw4<uint16_t> {
-  uint2 v;
-  __device__ __forceinline__ void load(const uint16_t* p) { v = *SPP_GLOBAL(uint2, p); }
-  __device__ __forceinline__ void get(float* f) const { widen4<uint16_t>(v, f); }
+struct Raw8<uint16_t> {
+  u32x4 v;
+  __device__ __forceinline__ void load(const uint16_t* p) { v = *SPP_GLOBAL(u32x4, p); }
+  __device__ __forceinline__ void zero() { v = u32x4{0, 0, 0, 0}; }
+  __device__ __forceinline__ void get(float* f) const { unpack<uint16_t>(make_uint4(v.x, v.y, v.z, v.w), f); }
 };
 template <>
-struct Raw4<float> {
-  uint4 v;
-  __device__ __forceinline__ void load(const float* p) { v = *SPP_GLOBAL(uint4, p); }
-  __device__ __forceinline__ void get(float* f) const { unpack<float>(v, f); }
+struct Raw8<float> {
+  u32x4 v[2];
+  __device__ __forceinline__ void load(const float* p) {
+    v[0] = *SPP_GLOBAL(u32x4, p);
+    v[1] = *SPP_GLOBAL(u32x4, p + 4);
+  }
+  __device__ __forceinline__ void zero() { v[0] = v[1] = u32x4{0, 0, 0, 0}; }
+  __device__ __forceinline__ void get(float* f) const {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) unpack<float>(make_uint4(v[q].x, v[q].y, v[q].z, v[q].w), f + 4 * q);
+  }
 };
 
-// UF: the token rows come as fp32 u (else as h in the storage type T)
-template <typename T, bool UF>
-__global__ __launch_bounds__(64 * kRowWaves) void router_rows_mfma_kernel(RouterArgs a) {
-  using TU = typename std::conditional<UF, float, T>::type;
+// TU: element type of u (float, or T when the layer input itself is read)
+template <typename T, typename TU, int KSW>
+__global__ __launch_bounds__(64 * kRowWaves) void router_rows_kernel(RouterArgs a) {
   __shared__ f32x4 s_acc[kRowWaves][64];
   __shared__ float s_ss[kRowWaves][16];
-  __shared__ float s_inv[16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = a.D, n = a.n, ldz = a.n + a.r;
   const int nr = a.router_on ? n : 0, na = a.A ? a.r : 0, rows = nr + na;
   const int b0 = blockIdx.y * 16, r0 = blockIdx.x * 16;
@@ -2253,34 +2258,41 @@ __global__ __launch_bounds__(64 * kRowWaves) void router_rows_mfma_kernel(Router
   const int row = min(r0 + i, rows - 1);
   const T* wrow = row < nr ? reinterpret_cast<const T*>(a.Wr) + static_cast<size_t>(row) * D
                            : reinterpret_cast<const T*>(a.A) + static_cast<size_t>(row - nr) * D;
-  const TU* urow = (UF ? reinterpret_cast<const TU*>(a.u) : reinterpret_cast<const TU*>(a.h)) +
+  const TU* urow = (a.u ? reinterpret_cast<const TU*>(a.u) : reinterpret_cast<const TU*>(a.h)) +
                    static_cast<size_t>(tok) * D;
-  const int nruns = D / 16;  // D % 16 == 0 (checked at launch)
-  const int per = (nruns + kRowWaves - 1) / kRowWaves;
-  const int c_begin = min(nruns, wave * per), c_end = min(nruns, c_begin + per);
+  const int nks = (D + 31) / 32;  // D is a multiple of 16: a lane's 8 columns are all in or all out
+  const int per = (nks + kRowWaves - 1) / kRowWaves;  // <= KSW
+  const int c0 = wave * per, cnt = max(0, min(nks - c0, per));
+  Raw8<TU> ur[KSW];
+  Raw8<T> wr[KSW];
+#pragma unroll
+  for (int q = 0; q < KSW; ++q) {
+    const int k = 32 * (c0 + q) + 8 * g;
+    const bool ok = q < cnt && k < D;
+    ur[q].load(urow + (ok ? k : 0));
+    wr[q].load(wrow + (ok ? k : 0));
+  }
+  __builtin_amdgcn_sched_barrier(0);
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
   float ss = 0.f;
-  for (int c0 = c_begin; c0 < c_end; c0 += kRowRuns) {
-    Raw4<TU> ur[kRowRuns];
-    Raw4<T> wr[kRowRuns];
 #pragma unroll
-    for (int q = 0; q < kRowRuns; ++q) {
-      const int k = 16 * min(c0 + q, c_end - 1) + 4 * g;  // past the range: a valid run, dropped below
-      ur[q].load(urow + k);
-      wr[q].load(wrow + k);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int q = 0; q < kRowRuns; ++q) {
-      if (c0 + q < c_end) {  // wave-uniform
-        float uf[4], wf[4];
-        ur[q].get(uf);
+  for (int q = 0; q < KSW; ++q) {
+    if (q < cnt) {  // wave-uniform
+      if (32 * (c0 + q) + 8 * g >= D) {
+        ur[q].zero();
+        wr[q].zero();
+      }
+      float uf[8];
+      ur[q].get(uf);
+  #pragma unroll
+      for (int e = 0; e < 8; ++e) ss += uf[e] * uf[e];
+      if constexpr (sizeof(T) == 2 && sizeof(TU) == 2) {
+        acc = mfma_bf16(ur[q].v, wr[q].v, acc);
+      } else {
+        float wf[8];
         wr[q].get(wf);
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(uf[st], wf[st], acc, 0, 0, 0);
-          ss += uf[st] * uf[st];
-        }
+  #pragma unroll
+        for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(uf[e], wf[e], acc, 0, 0, 0);
       }
     }
   }
@@ -2290,13 +2302,13 @@ __global__ __launch_bounds__(64 * kRowWaves) void router_rows_mfma_kernel(Router
   s_acc[wave][lane] = acc;
   if (lane < 16) s_ss[wave][lane] = ss;
   __syncthreads();
-  if (wave == 0) {
-    if (lane < 16) {
-      float sst = s_ss[0][lane];
+  auto inv_of = [&](int t) {
+    float sst = s_ss[0][t];
 #pragma unroll
-      for (int w = 1; w < kRowWaves; ++w) sst += s_ss[w][lane];
-      s_inv[lane] = a.x_given ? 1.f : 1.0f / sqrtf(sst / static_cast<float>(D) + a.eps);
-    }
+    for (int w = 1; w < kRowWaves; ++w) sst += s_ss[w][t];
+    return a.x_given ? 1.f : 1.0f / sqrtf(sst / static_cast<float>(D) + a.eps);
+  };
+  if (wave == 0) {
     f32x4 z = s_acc[0][lane];
 #pragma unroll
     for (int w = 1; w < kRowWaves; ++w) {
@@ -2310,41 +2322,32 @@ __global__ __launch_bounds__(64 * kRowWaves) void router_rows_mfma_kernel(Router
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int t = 4 * g + j;
-        const int b = b0 + t;
-        if (b < a.B) a.zbuf[static_cast<size_t>(b) * ldz + zcol] = z[j] * s_inv[t];
+        if (b0 + t < a.B) a.zbuf[static_cast<size_t>(b0 + t) * ldz + zcol] = z[j] * inv_of(t);
       }
     }
   }
-  if (!a.x_out) return;
-  __syncthreads();
-  // x = inv * u for the workgroup's tokens: the row tiles of a token tile
-  // share its runs of 16 columns, the waves share a row tile's runs
-  if (b0 + i < a.B) {
-    const float inv = s_inv[i];
-    float* xo = a.x_out + static_cast<size_t>(b0 + i) * D;
-    const int nrt = gridDim.x, rt = blockIdx.x;
-    const int x0 = nruns * rt / nrt, x1 = nruns * (rt + 1) / nrt;
-    constexpr int kX = 4;  // runs per wave and pass, loads in flight together
-    for (int c0 = x0 + wave * kX; c0 < x1; c0 += kRowWaves * kX) {
-      Raw4<TU> ur[kX];
+  if (a.x_out && b0 + i < a.B) {
+    const float inv = inv_of(i);
+    const size_t xb = static_cast<size_t>(b0 + i) * D;
 #pragma unroll
-      for (int q = 0; q < kX; ++q) ur[q].load(urow + 16 * min(c0 + q, x1 - 1) + 4 * g);
+    for (int q = 0; q < KSW; ++q) {
+      const int k = 32 * (c0 + q) + 8 * g;
+      if (q >= cnt || (c0 + q) % static_cast<int>(gridDim.x) != static_cast<int>(blockIdx.x) || k >= D) continue;
+      float f[8];
+      ur[q].get(f);
 #pragma unroll
-      for (int q = 0; q < kX; ++q) {
-        if (c0 + q < x1) {
-          float f[4];
-          ur[q].get(f);
-          *reinterpret_cast<float4*>(xo + 16 * (c0 + q) + 4 * g) =
-              make_float4(f[0] * inv, f[1] * inv, f[2] * inv, f[3] * inv);
-          if (a.xh) {
-            uint2 hi, lo;
-            split2(f[0] * inv, f[1] * inv, &hi.x, &lo.x);
-            split2(f[2] * inv, f[3] * inv, &hi.y, &lo.y);
-            const size_t o = static_cast<size_t>(b0 + i) * D + 16 * (c0 + q) + 4 * g;
-            *reinterpret_cast<uint2*>(a.xh + o) = hi;
-            *reinterpret_cast<uint2*>(a.xl + o) = lo;
-          }
-        }
+      for (int e = 0; e < 8; ++e) f[e] *= inv;
+      float4* xo = reinterpret_cast<float4*>(a.x_out + xb + k);
+      xo[0] = make_float4(f[0], f[1], f[2], f[3]);
+      xo[1] = make_float4(f[4], f[5], f[6], f[7]);
+      if (a.xh) {
+        uint4 hi, lo;
+        split2(f[0], f[1], &hi.x, &lo.x);
+        split2(f[2], f[3], &hi.y, &lo.y);
+        split2(f[4], f[5], &hi.z, &lo.z);
+        split2(f[6], f[7], &hi.w, &lo.w);
+        *reinterpret_cast<uint4*>(a.xh + xb + k) = hi;
+        *reinterpret_cast<uint4*>(a.xl + xb + k) = lo;
       }
     }
   }
@@ -2502,6 +2505,18 @@ bool full_rows(int D) {
   return (D / Vec<T>::N) % 64 == 0;
 }
 
+template <typename T, typename TU>
+void router_rows_t(const RouterArgs& a, int rows, hipStream_t st) {
+  const dim3 grid((rows + 15) / 16, (a.B + 15) / 16), block(64 * kRowWaves);
+  const int per = ((a.D + 31) / 32 + kRowWaves - 1) / kRowWaves;  // steps of a wave: up to 16 at D 4096
+  if (per <= 4)
+    hipLaunchKernelGGL((router_rows_kernel<T, TU, 4>), grid, block, 0, st, a);
+  else if (per <= 8)
+    hipLaunchKernelGGL((router_rows_kernel<T, TU, 8>), grid, block, 0, st, a);
+  else if constexpr (sizeof(T) == 2)  // fp32 rows have at most 2048 columns
+    hipLaunchKernelGGL((router_rows_kernel<T, TU, 16>), grid, block, 0, st, a);
+}
+
 template <typename T, bool FULL>
 hipError_t router_tf(const RouterArgs& a, hipStream_t st) {
   const int rows = (a.router_on ? a.n : 0) + (a.A ? a.r : 0);
@@ -2526,15 +2541,15 @@ hipError_t router_tf(const RouterArgs& a, hipStream_t st) {
     return hipGetLastError();
   }
   if (a.D % 16 != 0) return hipErrorInvalidValue;
-  const dim3 g2((rows + 15) / 16, (a.B + 15) / 16);
-  if (a.u)
-    hipLaunchKernelGGL((router_rows_mfma_kernel<T, true>), g2, dim3(64 * kRowWaves), 0, st, a);
+  if (a.u || sizeof(T) == 4)
+    router_rows_t<T, float>(a, rows, st);
   else
-    hipLaunchKernelGGL((router_rows_mfma_kernel<T, false>), g2, dim3(64 * kRowWaves), 0, st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // one wave per token where the shapes allow it (as the batch-1 one-wave tails)
-  const bool wave1 = sizeof(T) == 2 && a.n <= 128 && a.K <= 64 && (!a.A || (a.r <= 64 && a.r % 8 == 0));
+    router_rows_t<T, T>(a, rows, st);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  // one wave per token: n <= 128, K <= 64, an adapter in bf16 with r <= 64 and
+  // a multiple of 8 (as the batch-1 one-wave tails); 3.3 us against 3.9 for a
+  // workgroup per token (6 fp32 tokens over 32 experts)
+  const bool wave1 = a.n <= 128 && a.K <= 64 && (!a.A || (sizeof(T) == 2 && a.r <= 64 && a.r % 8 == 0));
   if (wave1 && a.n <= 64)
     hipLaunchKernelGGL((router_select_wave_kernel<1>), dim3(a.B), dim3(64), 0, st, a);
   else if (wave1)
