@@ -90,6 +90,7 @@ struct GroupArgs {
   int I, D;
   const uint16_t* xh;       // [B, D] router inputs as bf16 pairs x = xh + xl
   const uint16_t* xl;
+  const float* x;           // [B, D] router inputs (unit-layout experts)
   float* ypart;             // [npairs * nsplit, D] partial outputs; pair b*K + k, then B*K + b*n_shared + j
 };
 
@@ -97,6 +98,7 @@ struct CombineBArgs {
   const float* ypart;       // [npairs * nsplit, D]
   const float* gates;       // [B, K]
   int B, K, n_shared, nsplit, D;
+  int parts;                // set by the launch
   const void* res_h;        // [B, D] residual in storage dtype (used when res_u == nullptr)
   const float* res_u;       // [B, D] fp32 residual (prologue output)
   void* out;                // [B, D] storage dtype
@@ -125,6 +127,10 @@ hipError_t launch_combine(const CombineArgs& a, int dtype, hipStream_t st);
 hipError_t launch_proj(const ProjArgs& a, int dtype, hipStream_t st);
 // Grouped (batched) routed-expert FFN, bf16 only; D % 256 == 0, I % 16 == 0.
 hipError_t launch_ffn_grouped(const GroupArgs& a, hipStream_t st, hipEvent_t start, hipEvent_t stop);
+// The same over experts in the unit layout (dtype 0 or 1); nsplit and upw as
+// batch_units_split gives them, waves unused.
+hipError_t launch_ffn_units_batch(const GroupArgs& a, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop);
+void batch_units_split(int I, int D, int dtype, int* nsplit, int* upw);
 hipError_t launch_combine_batched(const CombineBArgs& a, int dtype, hipStream_t st);
 // Host-to-device copies by a copy kernel: n copies of n16 16-byte chunks each,
 // from pinned host memory (its device-visible, 16-byte aligned address) to

@@ -2089,13 +2089,133 @@ __global__ __launch_bounds__(64 * W, 2) void ffn_grouped_kernel(GroupArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Batched decode over experts in the unit layout (fp32, and bf16 shapes that
+// the tiled layout does not take).  One workgroup takes one group (grp_find)
+// and R x 4 units of its expert; every weight of the range is loaded into
+// registers once and serves every token of the group.  As in
+// ffn_slices_kernel a wave holds the gate and up rows of its own R units and
+// its D-slice of all the down columns:
+//   1. per token, h of the wave's units into LDS (the next token's x loads
+//      beside it); one barrier;
+//   2. per token, the wave's slice of sum_u h_u down_u to the partial row.
+// A launch per token read every expert once per token and paid two launches
+// each: 6 fp32 tokens over 32 experts (D 1024, I 704) took 6 x (8.0 + 4.1) us.
+// ---------------------------------------------------------------------------
+template <typename T, int NCH, bool FULL, int R, int DS>
+__global__ __launch_bounds__(64 * kSlWaves) void ffn_units_batch_kernel(GroupArgs a) {
+  constexpr int V = Vec<T>::N;
+  constexpr int W = kSlWaves;
+  __shared__ int s_cnt[kMaxExpertsTopK];
+  __shared__ int s_wave[W];
+  __shared__ int s_pair[kGroupTokens];
+  __shared__ float s_h[kGroupTokens][R * W];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int D = a.D, nch = D / V, I = a.I;
+  const int g = blockIdx.x / a.nsplit, split = blockIdx.x - g * a.nsplit;
+  const uint8_t* blob = nullptr;
+  int m = 0;
+  if (!grp_find<W>(a, g, tid, s_cnt, s_wave, s_pair, &blob, &m)) return;
+  m = __builtin_amdgcn_readfirstlane(m);
+  const int i0 = split * R * W;
+  const int cpw = (nch + W - 1) / W, c0 = wave * cpw;
+  auto xrow = [&](int t) {
+    const int pair = __builtin_amdgcn_readfirstlane(s_pair[t]);
+    const int tok = pair < a.B * a.K ? pair / a.K : (pair - a.B * a.K) / a.n_shared;
+    return a.x + static_cast<size_t>(tok) * D;
+  };
+  float xv[NCH][V];
+  load_row_f32<T, NCH, FULL>(xrow(0), lane, nch, xv);
+  __builtin_amdgcn_sched_barrier(0);
+  // a unit past the end re-reads the last one, a lane past its slice chunk 0; neither is used
+  uint4 rg[R][NCH], ru[R][NCH], rd[R][W][DS];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const T* base = reinterpret_cast<const T*>(blob) + static_cast<size_t>(min(i0 + r * W + wave, I - 1)) * 3 * D;
+    load_chunks<NCH, FULL, true>(base, lane, nch, rg[r]);
+    load_chunks<NCH, FULL, true>(base + D, lane, nch, ru[r]);
+#pragma unroll
+    for (int w2 = 0; w2 < W; ++w2) {
+      const T* dbase = reinterpret_cast<const T*>(blob) + (static_cast<size_t>(min(i0 + r * W + w2, I - 1)) * 3 + 2) * D;
+#pragma unroll
+      for (int s = 0; s < DS; ++s) {
+        const int c = c0 + lane + 64 * s;
+        rd[r][w2][s] = ld_chunk<true>(dbase, lane + 64 * s < cpw && c < nch ? c : 0);
+      }
+    }
+  }
+  for (int t = 0; t < m; ++t) {
+    float xn[NCH][V];
+    load_row_f32<T, NCH, FULL>(xrow(min(t + 1, m - 1)), lane, nch, xn);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float gs = 0.f, us = 0.f;
+#pragma unroll
+      for (int j = 0; j < NCH; ++j) {
+        float fg[V], fu[V];
+        unpack<T>(rg[r][j], fg);
+        unpack<T>(ru[r][j], fu);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          gs += fg[v] * xv[j][v];
+          us += fu[v] * xv[j][v];
+        }
+      }
+      const float gv = wave_sum(gs);
+      const float uv = wave_sum(us);
+      if (lane == 0) s_h[t][r * W + wave] = gv / (1.f + expf(-gv)) * uv;
+    }
+#pragma unroll
+    for (int j = 0; j < NCH; ++j)
+#pragma unroll
+      for (int v = 0; v < V; ++v) xv[j][v] = xn[j][v];
+  }
+  __syncthreads();
+  for (int t = 0; t < m; ++t) {
+    float acc[DS][V];
+#pragma unroll
+    for (int s = 0; s < DS; ++s)
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[s][v] = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int w2 = 0; w2 < W; ++w2) {
+        if (i0 + r * W + w2 >= I) continue;  // workgroup-uniform
+        const float h = s_h[t][r * W + w2];
+#pragma unroll
+        for (int s = 0; s < DS; ++s) {
+          float fd[V];
+          unpack<T>(rd[r][w2][s], fd);
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[s][v] += h * fd[v];
+        }
+      }
+    float* out = a.ypart + (static_cast<size_t>(s_pair[t]) * a.nsplit + split) * D;
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+      const int c = c0 + lane + 64 * s;
+      if (lane + 64 * s < cpw && c < nch) {
+#pragma unroll
+        for (int v = 0; v < V; v += 4)
+          *reinterpret_cast<float4*>(out + c * V + v) = make_float4(acc[s][v], acc[s][v + 1], acc[s][v + 2], acc[s][v + 3]);
+      }
+    }
+  }
+}
+
 // Batched combine: h_out[b] = round(residual[b] + sum_k g_bk sum_r ypart[(b,k), r]
 //                                   + sum_j sum_r ypart[(b, shared j), r]), fixed order.
 // Batched combine: y_b = sum_k g_bk * (sum over unit ranges of pair (b,k)'s
 // partial rows) + the same sums of the shared experts (weight 1), plus the
-// residual.  One workgroup per (256 columns, token); wave w sums the ranges of
-// pairs w, w + kCombWaves, ... with every range load of a pair in flight at
-// once (4 columns per lane); wave 0 then folds the pairs in order from LDS.
+// residual.  One workgroup per (256 columns, token), 4 columns per lane.  The
+// ranges of a pair are cut into `parts` runs; wave w sums runs w, w + waves,
+// ..., kCombRanges loads in flight; wave 0 then folds runs and pairs in order
+// from LDS.  parts is 1 up to kCombRanges ranges; beyond, as many as give
+// every wave of a full workgroup a run (59 ranges of 4 pairs in one run each
+// would wait for four rounds of loads).
 constexpr int kCombWaves = 16;
 constexpr int kCombRanges = 16;  // range loads of one pair in flight per pass
 template <typename T>
@@ -2104,20 +2224,22 @@ __global__ __launch_bounds__(64 * kCombWaves) void ffn_combine_batched_kernel(Co
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
   const int b = blockIdx.y;
   const int npairs = a.K + a.n_shared;
+  const int parts = a.parts, per = (a.nsplit + parts - 1) / parts;
   const int col = 4 * (blockIdx.x * 64 + lane);
   const int c = min(col, a.D - 4);  // lanes past D re-read the last columns, unused
-  for (int p = wave; p < npairs; p += nwaves) {
+  for (int q0 = wave; q0 < npairs * parts; q0 += nwaves) {
+    const int p = q0 / parts, rb = (q0 - p * parts) * per, re = min(a.nsplit, rb + per);
     const int pair = p < a.K ? b * a.K + p : a.B * a.K + b * a.n_shared + (p - a.K);
     const float* base = a.ypart + static_cast<size_t>(pair) * a.nsplit * a.D + c;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int r0 = 0; r0 < a.nsplit; r0 += kCombRanges) {
+    for (int r0 = rb; r0 < re; r0 += kCombRanges) {
       float4 w[kCombRanges];
 #pragma unroll
       for (int q = 0; q < kCombRanges; ++q)
-        w[q] = *SPP_GLOBAL(float4, base + static_cast<size_t>(min(r0 + q, a.nsplit - 1)) * a.D);
+        w[q] = *SPP_GLOBAL(float4, base + static_cast<size_t>(min(r0 + q, re - 1)) * a.D);
 #pragma unroll
       for (int q = 0; q < kCombRanges; ++q) {
-        if (r0 + q < a.nsplit) {  // ranges in order
+        if (r0 + q < re) {  // ranges in order
           v.x += w[q].x;
           v.y += w[q].y;
           v.z += w[q].z;
@@ -2125,7 +2247,7 @@ __global__ __launch_bounds__(64 * kCombWaves) void ffn_combine_batched_kernel(Co
         }
       }
     }
-    s_v[p][lane] = v;
+    s_v[q0][lane] = v;
   }
   // the gates and the residual go out while the other waves finish
   float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -2144,7 +2266,11 @@ __global__ __launch_bounds__(64 * kCombWaves) void ffn_combine_batched_kernel(Co
   if (wave != 0 || col >= a.D) return;
   float y[4] = {0.f, 0.f, 0.f, 0.f};
   for (int p = 0; p < npairs; ++p) {
-    const float4 v = s_v[p][lane];
+    float4 v = s_v[p * parts][lane];
+    for (int q = 1; q < parts; ++q) {
+      const float4 w = s_v[p * parts + q][lane];
+      v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+    }
     const float g = p < a.K ? a.gates[b * a.K + p] : 1.f;
     y[0] = p < a.K ? fmaf(g, v.x, y[0]) : y[0] + v.x;
     y[1] = p < a.K ? fmaf(g, v.y, y[1]) : y[1] + v.y;
@@ -2584,6 +2710,13 @@ constexpr int slices_ds() {
   return NCH <= 4 ? 1 : 2;
 }
 
+// Units per wave of ffn_units_batch_kernel: as many as stay in 256 registers
+// beside two rows of x (bf16 rows hold twice the columns per chunk).
+template <typename T>
+constexpr int batch_rounds(int nch) {
+  return sizeof(T) == 2 ? (nch <= 3 ? 3 : nch == 4 ? 2 : 1) : (nch <= 4 ? 3 : 2);
+}
+
 template <typename T, bool FULL, int R>
 hipError_t ffn_slices_tr(const FfnArgs& a, int grid, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
   const int nchl = nch_for<T>(a.D);
@@ -2731,11 +2864,47 @@ hipError_t launch_ffn_grouped(const GroupArgs& a, hipStream_t st, hipEvent_t sta
   return hipGetLastError();
 }
 
-hipError_t launch_combine_batched(const CombineBArgs& a, int dtype, hipStream_t st) {
+void batch_units_split(int I, int D, int dtype, int* nsplit, int* upw) {
+  const int nchl = dtype == 1 ? nch_for<uint16_t>(D) : nch_for<float>(D);
+  *upw = (dtype == 1 ? batch_rounds<uint16_t>(nchl) : batch_rounds<float>(nchl)) * kSlWaves;
+  *nsplit = (I + *upw - 1) / *upw;
+}
+
+template <typename T, bool FULL>
+hipError_t ffn_units_batch_tf(const GroupArgs& a, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
+  const dim3 grid(static_cast<unsigned>(a.ngroups * a.nsplit)), block(64 * kSlWaves);
+  if (start || stop) {
+    SPP_DISPATCH_NCH(nch_for<T>(a.D),
+                     hipExtLaunchKernelGGL((ffn_units_batch_kernel<T, NCH, FULL, batch_rounds<T>(NCH), slices_ds<NCH>()>),
+                                           grid, block, 0, st, start, stop, 0u, a));
+  } else {
+    SPP_DISPATCH_NCH(nch_for<T>(a.D),
+                     hipLaunchKernelGGL((ffn_units_batch_kernel<T, NCH, FULL, batch_rounds<T>(NCH), slices_ds<NCH>()>),
+                                        grid, block, 0, st, a));
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_ffn_units_batch(const GroupArgs& a, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
+  int nsplit = 0, upw = 0;
+  batch_units_split(a.I, a.D, dtype, &nsplit, &upw);
+  if (a.ngroups <= 0 || a.nsplit != nsplit || a.upw != upw || !a.topk || !a.slot_tab || !a.x || !a.ypart ||
+      a.n > kMaxExpertsTopK)
+    return hipErrorInvalidValue;
+  if (dtype == 1)
+    return full_rows<uint16_t>(a.D) ? ffn_units_batch_tf<uint16_t, true>(a, st, start, stop)
+                                    : ffn_units_batch_tf<uint16_t, false>(a, st, start, stop);
+  return full_rows<float>(a.D) ? ffn_units_batch_tf<float, true>(a, st, start, stop)
+                               : ffn_units_batch_tf<float, false>(a, st, start, stop);
+}
+
+hipError_t launch_combine_batched(const CombineBArgs& args, int dtype, hipStream_t st) {
+  CombineBArgs a = args;
   const int npairs = a.K + a.n_shared;
   if (a.D % 4 != 0 || npairs < 1 || npairs > kMaxWork || a.nsplit < 1) return hipErrorInvalidValue;
+  a.parts = std::max(1, std::min(kCombWaves / npairs, (a.nsplit + kCombRanges - 1) / kCombRanges));
   const dim3 grid((a.D / 4 + 63) / 64, a.B);
-  const dim3 block(64 * min(npairs, kCombWaves));
+  const dim3 block(64 * min(npairs * a.parts, kCombWaves));
   if (dtype == 1)
     hipLaunchKernelGGL((ffn_combine_batched_kernel<uint16_t>), grid, block, 0, st, a);
   else

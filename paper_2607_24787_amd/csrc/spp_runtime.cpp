@@ -137,7 +137,9 @@ struct spp_ctx {
   bool grouped = false;
   uint16_t* xh_dev = nullptr;  // [maxB, D] router inputs as bf16 pairs, xh then xl
   uint16_t* xl_dev = nullptr;
-  int32_t* round_tab = nullptr;  // [n] slots of one round's experts (host-decided layers)
+  int32_t* round_tab = nullptr;  // [n] slots of one round's experts (host-decided batched layers)
+  int32_t batch_tokens = 1;      // tokens of one batched FFN launch: max_batch, unless its partial rows
+                                 // would exceed kMaxPartialBytes
   float* ypart = nullptr;
   std::vector<hipEvent_t> round_done;  // per on-demand round: its FFN launch finished
   int64_t clock = 0;
@@ -209,6 +211,15 @@ void grouped_split(const spp_model_desc& d, int32_t B, int num_cu, int* nsplit, 
     *upw = ((d.I + ns - 1) / ns + 15) / 16 * 16;
     *nsplit = (d.I + *upw - 1) / *upw;
   }
+}
+
+// Unit ranges of a batched FFN over either layout.
+constexpr size_t kMaxPartialBytes = size_t{256} << 20;  // unit layout: partial rows of one launch
+void batch_split(const spp_model_desc& d, int32_t B, int num_cu, int* nsplit, int* upw) {
+  if (tiled_layout(d))
+    grouped_split(d, B, num_cu, nsplit, upw);
+  else
+    spp::batch_units_split(d.I, d.D, d.dtype, nsplit, upw);
 }
 
 // Bytes of one expert blob (before the 4 KiB stride rounding).
@@ -618,17 +629,28 @@ spp_status create_impl(const spp_model_desc* desc, void* stream, spp_ctx** out) 
   // batched decode runs the routed experts as grouped MFMA contractions
   c->grouped = tiled_layout(d);
   if (c->grouped) {
-    size_t rows = 0;  // partial rows of the batch that needs the most
-    for (int32_t B = 1, ns = 0, upw = 0; B <= d.max_batch; ++B) {
-      grouped_split(d, B, c->num_cu, &ns, &upw);
-      rows = std::max(rows, static_cast<size_t>(B) * (d.K + d.n_shared) * ns);
-    }
     const size_t xn = static_cast<size_t>(d.max_batch) * d.D;
-    if (hipMalloc(&c->xh_dev, 2 * xn * sizeof(uint16_t)) != hipSuccess ||
-        hipMalloc(&c->round_tab, d.n * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc(&c->ypart, rows * d.D * sizeof(float)) != hipSuccess)
+    if (hipMalloc(&c->xh_dev, 2 * xn * sizeof(uint16_t)) != hipSuccess)
       return fail(SPP_ENOMEM, "batched-decode buffers allocation failed");
     c->xl_dev = c->xh_dev + xn;
+  }
+  if (d.max_batch > 1) {
+    size_t rows = 0;  // partial rows of the batch that needs the most
+    c->batch_tokens = d.max_batch;
+    if (!c->grouped) {
+      int ns = 0, upw = 0;
+      batch_split(d, 1, c->num_cu, &ns, &upw);
+      const size_t per_token = static_cast<size_t>(d.K + d.n_shared) * ns;
+      c->batch_tokens = static_cast<int32_t>(std::max<size_t>(
+          1, std::min<size_t>(d.max_batch, kMaxPartialBytes / (per_token * d.D * sizeof(float)))));
+    }
+    for (int32_t B = 1, ns = 0, upw = 0; B <= c->batch_tokens; ++B) {
+      batch_split(d, B, c->num_cu, &ns, &upw);
+      rows = std::max(rows, static_cast<size_t>(B) * (d.K + d.n_shared) * ns);
+    }
+    if (hipMalloc(&c->round_tab, d.n * sizeof(int32_t)) != hipSuccess ||
+        hipMalloc(&c->ypart, rows * d.D * sizeof(float)) != hipSuccess)
+      return fail(SPP_ENOMEM, "batched-decode buffers allocation failed");
   }
   SPP_HIP(hipMemset(c->counter, 0, 256));
   SPP_HIP(hipMemset(c->ztag, 0, static_cast<size_t>(d.n + d.r) * sizeof(uint64_t)));  // seq 0 is never handed out
@@ -801,14 +823,15 @@ spp_status round_event(spp_ctx* c, size_t r, hipEvent_t* out) {
   return SPP_OK;
 }
 
-// One grouped FFN launch over the experts that `slot_tab` (device) gives a
-// slot, `nexp` at most, with the shared experts if wanted.
-spp_status launch_groups(spp_ctx* c, const LayerState& ls, int32_t B, const int32_t* slot_tab, int32_t nexp,
-                         bool shared, hipEvent_t start, hipEvent_t stop) {
+// One batched FFN launch over tokens [b0, b0 + B) and the experts that
+// `slot_tab` (device) gives a slot, `nexp` at most, with the shared experts if
+// wanted.
+spp_status launch_groups(spp_ctx* c, const LayerState& ls, int32_t b0, int32_t B, const int32_t* slot_tab,
+                         int32_t nexp, bool shared, hipEvent_t start, hipEvent_t stop) {
   const spp_model_desc& d = c->d;
   const int32_t BK = B * d.K;
   spp::GroupArgs ga{};
-  ga.topk = reinterpret_cast<const int32_t*>(c->res_dev);
+  ga.topk = reinterpret_cast<const int32_t*>(c->res_dev) + static_cast<size_t>(b0) * d.K;
   ga.slot_tab = slot_tab;
   ga.slots = ls.slots;
   ga.shared = static_cast<const uint8_t*>(ls.shared);
@@ -820,34 +843,55 @@ spp_status launch_groups(spp_ctx* c, const LayerState& ls, int32_t B, const int3
   // at most one group per pair, and at most one partly filled group per expert
   ga.ngroups = std::min(BK, nexp + BK / spp::kGroupTokens) +
                ga.n_shared * ((B + spp::kGroupTokens - 1) / spp::kGroupTokens);
-  grouped_split(d, B, c->num_cu, &ga.nsplit, &ga.upw);
+  batch_split(d, B, c->num_cu, &ga.nsplit, &ga.upw);
   ga.waves = ga.upw > 192 ? 8 : 4;
   ga.I = d.I;
   ga.D = d.D;
   ga.xh = c->xh_dev;
   ga.xl = c->xl_dev;
+  ga.x = c->x_dev + static_cast<size_t>(b0) * d.D;
   ga.ypart = c->ypart;
   if (ga.ngroups == 0) return SPP_OK;
-  SPP_HIP(spp::launch_ffn_grouped(ga, c->compute, start, stop));
+  if (c->grouped)
+    SPP_HIP(spp::launch_ffn_grouped(ga, c->compute, start, stop));
+  else
+    SPP_HIP(spp::launch_ffn_units_batch(ga, d.dtype, c->compute, start, stop));
   return SPP_OK;
 }
 
-spp_status combine_batch(spp_ctx* c, int32_t B, const void* h_in, void* h_out) {
+spp_status combine_batch(spp_ctx* c, int32_t b0, int32_t B, const void* h_in, void* h_out) {
   const spp_model_desc& d = c->d;
+  const size_t row_bytes = static_cast<size_t>(d.D) * c->elem;
   spp::CombineBArgs cb{};
   int upw = 0;
-  grouped_split(d, B, c->num_cu, &cb.nsplit, &upw);
+  batch_split(d, B, c->num_cu, &cb.nsplit, &upw);
   cb.ypart = c->ypart;
-  cb.gates = reinterpret_cast<const float*>(c->res_dev + c->off_gates);
+  cb.gates = reinterpret_cast<const float*>(c->res_dev + c->off_gates) + static_cast<size_t>(b0) * d.K;
   cb.B = B;
   cb.K = d.K;
   cb.n_shared = d.n_shared;
   cb.D = d.D;
-  cb.res_h = h_in;
-  cb.res_u = d.has_proj ? c->u_dev : nullptr;
-  cb.out = h_out;
+  cb.res_h = static_cast<const uint8_t*>(h_in) + b0 * row_bytes;
+  cb.res_u = d.has_proj ? c->u_dev + static_cast<size_t>(b0) * d.D : nullptr;
+  cb.out = static_cast<uint8_t*>(h_out) + b0 * row_bytes;
   SPP_HIP(spp::launch_combine_batched(cb, d.dtype, c->compute));
   c->stats.ffn_launches += 1;
+  return SPP_OK;
+}
+
+// The batched FFN and combine of a layer whose experts are all in place
+// (`slot_tab`): one launch each, or, in the unit layout, one per batch_tokens.
+spp_status launch_batch(spp_ctx* c, const LayerState& ls, int32_t B, const int32_t* slot_tab, int32_t nexp,
+                        const void* h_in, void* h_out, const TimingSet& ts) {
+  for (int32_t b0 = 0; b0 < B; b0 += c->batch_tokens) {
+    const int32_t Bc = std::min(c->batch_tokens, B - b0);
+    if (spp_status e = launch_groups(c, ls, b0, Bc, slot_tab, nexp, true,
+                                     c->timing && b0 == 0 ? ts.ev[kEvFfnBegin] : nullptr,
+                                     c->timing && b0 + Bc == B ? ts.ev[kEvFfnEnd] : nullptr))
+      return e;
+    if (b0 == 0) c->t_grouped_launched = std::chrono::steady_clock::now();
+    if (spp_status e = combine_batch(c, b0, Bc, h_in, h_out)) return e;
+  }
   return SPP_OK;
 }
 
@@ -859,6 +903,15 @@ spp_status grouped_ffn(spp_ctx* c, LayerState& ls, int32_t B, const void* h_in, 
                        const std::vector<spp::Round>& rounds, const std::vector<spp::Transfer>& loads,
                        spp_layer_stats* st, TimingSet& ts) {
   std::vector<int32_t> table(c->d.n);
+  const auto set_table = [&](const spp::Round& round) {
+    std::fill(table.begin(), table.end(), -1);
+    for (const auto& es : round) table[es.first] = es.second;
+    return spp::launch_set_table(c->round_tab, table.data(), c->d.n, c->compute);
+  };
+  if (!c->grouped) {  // one round: every distinct expert fits in the slots
+    SPP_HIP(set_table(rounds[0]));
+    return launch_batch(c, ls, B, c->round_tab, static_cast<int32_t>(rounds[0].size()), h_in, h_out, ts);
+  }
   for (size_t r = 0; r < rounds.size(); ++r) {
     if (r > 0) {
       hipEvent_t done;
@@ -875,17 +928,19 @@ spp_status grouped_ffn(spp_ctx* c, LayerState& ls, int32_t B, const void* h_in, 
         if (spp_status e = record_extra(c, ts)) return e;
     }
     const bool first = r == 0, last = r + 1 == rounds.size();
-    std::fill(table.begin(), table.end(), -1);
-    for (const auto& es : rounds[r]) table[es.first] = es.second;
-    SPP_HIP(spp::launch_set_table(c->round_tab, table.data(), c->d.n, c->compute));
-    if (spp_status e = launch_groups(c, ls, B, c->round_tab, static_cast<int32_t>(rounds[r].size()), first,
+    SPP_HIP(set_table(rounds[r]));
+    if (spp_status e = launch_groups(c, ls, 0, B, c->round_tab, static_cast<int32_t>(rounds[r].size()), first,
                                      c->timing && first ? ts.ev[kEvFfnBegin] : nullptr,
                                      c->timing && last ? ts.ev[kEvFfnEnd] : nullptr))
       return e;
     if (first) c->t_grouped_launched = std::chrono::steady_clock::now();
   }
-  return combine_batch(c, B, h_in, h_out);
+  return combine_batch(c, 0, B, h_in, h_out);
 }
+
+// The batched kernels read the tiled layout at any batch, the unit layout
+// above one token.
+bool batched_ffn(const spp_ctx* c, int32_t B) { return c->grouped || B > 1; }
 
 // A layer call between its launches and its host side.
 struct Flight {
@@ -920,21 +975,21 @@ bool device_routable(spp_ctx* c, LayerState& ls, int32_t B) {
   return true;
 }
 
-// The batch-1 FFN's work list of token b: routed experts in T order, then the
-// shared ones.  T: the routing on the host, or nullptr (the device copy).
-int build_ffn(spp_ctx* c, const LayerState& ls, int32_t b, const int32_t* T, bool split_ok, spp::FfnArgs* fa) {
+// The batch-1 FFN's work list: routed experts in T order, then the shared
+// ones.  T: the routing on the host, or nullptr (the device copy).
+int build_ffn(spp_ctx* c, const LayerState& ls, const int32_t* T, bool split_ok, spp::FfnArgs* fa) {
   const spp_model_desc& d = c->d;
   *fa = spp::FfnArgs{};
   int nW = 0;
   if (!T) {
-    fa->sel = reinterpret_cast<const int32_t*>(c->res_dev + c->off_sel) + static_cast<size_t>(b) * d.K;
+    fa->sel = reinterpret_cast<const int32_t*>(c->res_dev + c->off_sel);
     fa->nsel = d.K;
     fa->slots = ls.slots;
     fa->stride = c->stride;
   }
   for (int32_t k = 0; k < d.K; ++k) {
-    if (T) fa->blob[nW] = ls.slots + static_cast<size_t>(ls.policy->slot_of(T[b * d.K + k])) * c->stride;
-    fa->gate_idx[nW] = b * d.K + k;
+    if (T) fa->blob[nW] = ls.slots + static_cast<size_t>(ls.policy->slot_of(T[k])) * c->stride;
+    fa->gate_idx[nW] = k;
     ++nW;
   }
   for (int32_t j = 0; j < d.n_shared; ++j) {
@@ -946,7 +1001,7 @@ int build_ffn(spp_ctx* c, const LayerState& ls, int32_t b, const int32_t* T, boo
   fa->I = d.I;
   fa->D = d.D;
   fa->codec = d.expert_codec;
-  fa->x = c->x_dev + static_cast<size_t>(b) * d.D;
+  fa->x = c->x_dev;
   fa->gates = reinterpret_cast<const float*>(c->res_dev + c->off_gates);
   fa->partial = c->partial;
   // sweep order, except under the FFN split, whose two launches need every
@@ -965,18 +1020,16 @@ int build_ffn(spp_ctx* c, const LayerState& ls, int32_t b, const int32_t* T, boo
   return spp::ffn_grid_for(nW * d.I, c->ffn_wgs, &fa->upw);
 }
 
-// The combine of token b's `grid` partial rows.
-spp_status combine_token(spp_ctx* c, const Flight& fl, int32_t b, int grid) {
-  const spp_model_desc& d = c->d;
-  const size_t row_bytes = static_cast<size_t>(d.D) * c->elem;
+// The batch-1 combine of `grid` partial rows.
+spp_status combine_token(spp_ctx* c, const Flight& fl, int grid) {
   spp::CombineArgs ca{};
   ca.partial = c->partial;
   ca.nparts = grid;
-  ca.D = d.D;
-  ca.res_h = static_cast<const uint8_t*>(fl.h_in) + b * row_bytes;
-  ca.res_u = d.has_proj ? c->u_dev + static_cast<size_t>(b) * d.D : nullptr;
-  ca.out = static_cast<uint8_t*>(fl.h_out) + b * row_bytes;
-  SPP_HIP(spp::launch_combine(ca, d.dtype, c->compute));
+  ca.D = c->d.D;
+  ca.res_h = fl.h_in;
+  ca.res_u = c->d.has_proj ? c->u_dev : nullptr;
+  ca.out = fl.h_out;
+  SPP_HIP(spp::launch_combine(ca, c->d.dtype, c->compute));
   c->stats.ffn_launches += 1;
   return SPP_OK;
 }
@@ -1063,19 +1116,14 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   }
   if (c->timing)
     for (int k : {kEvWaitA, kEvLoaded, kEvWaitB}) SPP_HIP(hipEventRecord(ts.ev[k], c->compute));
-  if (c->grouped) {
-    if (spp_status e = launch_groups(c, ls, B, ls.slot_tab, d.n, true, c->timing ? ts.ev[kEvFfnBegin] : nullptr,
-                                     c->timing ? ts.ev[kEvFfnEnd] : nullptr))
-      return e;
-    if (spp_status e = combine_batch(c, B, h_in, h_out)) return e;
-  }
-  for (int32_t b = 0; b < B && !c->grouped; ++b) {
+  if (batched_ffn(c, B)) {
+    if (spp_status e = launch_batch(c, ls, B, ls.slot_tab, d.n, h_in, h_out, ts)) return e;
+  } else {
     spp::FfnArgs fa{};
-    const int grid = build_ffn(c, ls, b, nullptr, false, &fa);
-    const bool stamp = c->timing && b == B - 1;
-    SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, stamp ? ts.ev[kEvFfnBegin] : nullptr,
-                            stamp ? ts.ev[kEvFfnEnd] : nullptr));
-    if (spp_status e = combine_token(c, fl, b, grid)) return e;
+    const int grid = build_ffn(c, ls, nullptr, false, &fa);
+    SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, c->timing ? ts.ev[kEvFfnBegin] : nullptr,
+                            c->timing ? ts.ev[kEvFfnEnd] : nullptr));
+    if (spp_status e = combine_token(c, fl, grid)) return e;
   }
   // no last_read event: while every expert holds a slot nothing is copied
   // into one, and a change of the table waits for the stream
@@ -1108,7 +1156,7 @@ spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_o
   const float* g = c->host_g.data();
   const float* s = c->host_s.data();  // valid after the wait for kind 1
   const int32_t BK = B * d.K;
-  const bool batched = c->grouped;  // the tiled layout is read by the grouped kernel only
+  const bool batched = batched_ffn(c, B);
   {
     // refusals after the routing leave the context as it was before the call
     // (the step clock included); nothing below this point has changed it yet
@@ -1116,7 +1164,7 @@ spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_o
     std::string msg;
     for (int32_t i = 0; i < BK && bad == SPP_OK; ++i)
       if (T[i] < 0 || T[i] >= d.n) bad = SPP_EHIP, msg = "router produced an out-of-range expert id";
-    if (bad == SPP_OK && !batched && ls.policy->distinct(T, BK) > d.S)
+    if (bad == SPP_OK && !c->grouped && ls.policy->distinct(T, BK) > d.S)
       bad = SPP_ESTATE, msg = "batch demand exceeds the slot count; more than S distinct experts per step "
                               "needs the batched bf16 path";
     if (bad != SPP_OK) {
@@ -1192,7 +1240,7 @@ spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_o
     uint32_t late = 0, all_items = 0;
     bool split = false;
     if (split_ok) {
-      grid0 = build_ffn(c, ls, 0, T, true, &fa0);
+      grid0 = build_ffn(c, ls, T, true, &fa0);
       all_items = fa0.nW >= 32 ? 0xFFFFFFFFu : ((1u << fa0.nW) - 1u);
       if (d.I % fa0.upw == 0) {
         for (int32_t k = 0; k < d.K; ++k) {
@@ -1222,17 +1270,16 @@ spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_o
     if (batched) {
       if (spp_status e = grouped_ffn(c, ls, B, h_in, h_out, rounds, c->last_loads, &st, ts)) return e;
     }
-    for (int32_t b = 0; b < B && !batched; ++b) {
+    if (!batched) {
       spp::FfnArgs fa{};
-      const int grid = split_ok ? grid0 : build_ffn(c, ls, b, T, false, &fa);
+      const int grid = split_ok ? grid0 : build_ffn(c, ls, T, false, &fa);
       if (split_ok) fa = fa0;
       if (split) fa.skip_mask = all_items & ~late;
-      const bool stamp = c->timing && b == B - 1;
-      SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, stamp ? ts.ev[kEvFfnBegin] : nullptr,
-                              stamp ? ts.ev[kEvFfnEnd] : nullptr));
-      if (b == 0) t_ffn = std::chrono::steady_clock::now();
+      SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, c->timing ? ts.ev[kEvFfnBegin] : nullptr,
+                              c->timing ? ts.ev[kEvFfnEnd] : nullptr));
+      t_ffn = std::chrono::steady_clock::now();
       if (split && hipEventQuery(c->hits_done) != hipSuccess) SPP_HIP(hipStreamWaitEvent(c->compute, c->hits_done, 0));
-      if (spp_status e = combine_token(c, fl, b, grid)) return e;
+      if (spp_status e = combine_token(c, fl, grid)) return e;
     }
     SPP_HIP(hipEventRecord(ls.last_read, c->compute));
     ls.last_read_valid = true;
