@@ -66,7 +66,7 @@ struct FfnArgs {
                                // nonzero mask needs upw to divide I (each workgroup on one item)
   int codec;                   // 0: experts in dtype; 1: 4-bit blocks (dtype bf16)
   int rounds;                  // 0: workgroup b takes units [b*upw, (b+1)*upw) (ffn_units_kernel, and
-                               // ffn_q4_kernel by range); 1..3: sweep rounds of ffn_slices_kernel (see
+                               // ffn_q4_kernel by range); 1..6: sweep rounds of ffn_slices_kernel (see
                                // ffn_grid_slices); 4-bit experts: 1..2 sweep passes of ffn_q4_kernel
                                // (see ffn_grid_q4_sweep); upw unused in sweep order
   const float* x;              // [D] router input of the token
@@ -151,8 +151,9 @@ hipError_t launch_spin(uint64_t ticks, uint32_t max_iter, hipStream_t st);
 // (*upw) so that about `target_wgs` workgroups share the work; returns the grid.
 int ffn_grid_for(int nunits, int target_wgs, int* upw);
 // The same work list in sweep rounds (bf16/fp32 experts, no skip mask): the
-// number of rounds (*rounds, 1..3) that puts the grid nearest `target_wgs`
-// workgroups; returns the grid, or 0 when it would exceed ffn_max_grid().
+// fewest rounds (*rounds, 1..6, as many as registers allow) with at most
+// `target_wgs` workgroups; returns the grid, or 0 when it would exceed
+// ffn_max_grid().
 int ffn_grid_slices(int nunits, int D, int dtype, int target_wgs, int* rounds);
 // 4-bit experts in sweep order (no skip mask): passes (*rounds, 1 or 2) of 3
 // units per wave (*upp); returns the grid, or 0 when it would exceed

@@ -1679,36 +1679,63 @@ __global__ __launch_bounds__(kFfnThreads) void read_probe_q4_kernel(FfnArgs a, u
 }
 
 // y = sum of the workgroup partials (fixed order), h_out = round(residual + y).
-// 1024 threads cover 64 outputs: 16 groups split the partials (8 loads in
-// flight per thread), then the groups are added in order.
+// A workgroup of 16 waves covers kCombCols columns, 4 per lane: a wave's load
+// takes kCombRowsPerWave partial rows, and all loads of up to kCombPass rows
+// are in flight together.  Each lane adds its rows in order, the lanes of a
+// column add across the wave, then the waves in order through LDS.  Latency
+// bound: 3.85 us for 512 rows of 2048 columns (4.05 with 4-byte loads and 64
+// columns per workgroup; 16 and 64 columns per workgroup 3.8 and 3.85).
 constexpr int kCombGroups = 16;
-constexpr int kCombRows = 32;
+constexpr int kCombCols = 32;
+constexpr int kCombLanes = kCombCols / 4;
+constexpr int kCombRowsPerWave = 64 / kCombLanes;
+constexpr int kCombPass = 512;
+constexpr int kCombLoads = kCombPass / (kCombGroups * kCombRowsPerWave);
 
 template <typename T>
 __global__ __launch_bounds__(64 * kCombGroups) void ffn_combine_kernel(CombineArgs a) {
-  __shared__ float s_part[kCombGroups][64];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int col0 = static_cast<int>(blockIdx.x) * 64 + lane;
-  const int col = min(col0, a.D - 1);  // lanes past D re-read the last column, unused
-  // group g sums partial rows g*kCombRows.. of every pass; a pass's loads all
-  // go out before the first add (one round trip for up to 512 partial rows),
-  // the residual behind the first pass's (group 0 always has a first pass)
-  float s = 0.f, res = 0.f;
-  for (int w0 = grp * kCombRows; w0 < a.nparts; w0 += kCombGroups * kCombRows) {
-    float v[kCombRows];
+  __shared__ float4 s_part[kCombGroups][kCombLanes];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cl = lane % kCombLanes;
+  const int col = min(static_cast<int>(blockIdx.x) * kCombCols + 4 * cl, a.D - 4);  // lanes past D re-read the last columns
+  const int row0 = wave * kCombRowsPerWave + lane / kCombLanes;
+  // the residual of thread t < kCombCols: its column
+  const int oc = static_cast<int>(blockIdx.x) * kCombCols + tid;
+  const bool out = tid < kCombCols && oc < a.D;
+  float res = 0.f;
+  if (out) res = a.res_u ? a.res_u[oc] : load_elem<T>(a.res_h, oc);
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int p0 = 0; p0 < a.nparts; p0 += kCombPass) {
+    float4 v[kCombLoads];
 #pragma unroll
-    for (int k = 0; k < kCombRows; ++k) v[k] = a.partial[static_cast<size_t>(min(w0 + k, a.nparts - 1)) * a.D + col];
-    if (w0 == grp * kCombRows) res = a.res_u ? a.res_u[col] : load_elem<T>(a.res_h, col);
+    for (int k = 0; k < kCombLoads; ++k)
+      v[k] = *SPP_GLOBAL(float4, a.partial + static_cast<size_t>(min(p0 + row0 + k * kCombGroups * kCombRowsPerWave,
+                                                                      a.nparts - 1)) * a.D + col);
 #pragma unroll
-    for (int k = 0; k < kCombRows; ++k) s += w0 + k < a.nparts ? v[k] : 0.f;
+    for (int k = 0; k < kCombLoads; ++k) {
+      if (p0 + row0 + k * kCombGroups * kCombRowsPerWave < a.nparts) {
+        s.x += v[k].x;
+        s.y += v[k].y;
+        s.z += v[k].z;
+        s.w += v[k].w;
+      }
+    }
   }
-  s_part[grp][lane] = s;
-  __syncthreads();
-  if (grp == 0 && col0 < a.D) {
-    float y = s_part[0][lane];
 #pragma unroll
-    for (int g = 1; g < kCombGroups; ++g) y += s_part[g][lane];
-    store_elem<T>(a.out, col, res + y);
+  for (int o = kCombLanes; o < 64; o <<= 1) {
+    s.x += __shfl_xor(s.x, o);
+    s.y += __shfl_xor(s.y, o);
+    s.z += __shfl_xor(s.z, o);
+    s.w += __shfl_xor(s.w, o);
+  }
+  if (lane < kCombLanes) s_part[wave][lane] = s;
+  __syncthreads();
+  if (out) {
+    const float* p = reinterpret_cast<const float*>(s_part) + tid;
+    float y = p[0];
+#pragma unroll
+    for (int g = 1; g < kCombGroups; ++g) y += p[g * kCombCols];
+    store_elem<T>(a.out, oc, res + y);
   }
 }
 
@@ -2703,11 +2730,18 @@ hipError_t ffn_tf(const FfnArgs& a, int grid, hipStream_t st, hipEvent_t start, 
   return hipGetLastError();
 }
 
-// The sweep-round kernel: R rounds (1..3 with up to 4 chunks per lane, 1
-// above), DS = chunks of a wave's D-slice per lane.
+// DS: chunks of a wave's D-slice per lane in the sweep-round kernel.
 template <int NCH>
 constexpr int slices_ds() {
   return NCH <= 4 ? 1 : 2;
+}
+
+// Most sweep rounds whose loads stay in registers (2 NCH + 4 DS chunks of 4
+// registers each per round, beside x).
+constexpr int kSlMaxRounds = 6;
+template <typename T>
+constexpr int slices_rounds(int nch) {
+  return nch <= 2 ? 6 : nch <= 4 ? 4 : nch <= 6 ? 2 : (sizeof(T) == 4 ? 2 : 1);
 }
 
 // Units per wave of ffn_units_batch_kernel: as many as stay in 256 registers
@@ -2720,14 +2754,15 @@ constexpr int batch_rounds(int nch) {
 template <typename T, bool FULL, int R>
 hipError_t ffn_slices_tr(const FfnArgs& a, int grid, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
   const int nchl = nch_for<T>(a.D);
-  if (R > 1 && nchl > 4) return hipErrorInvalidValue;
+  if (R > slices_rounds<T>(nchl)) return hipErrorInvalidValue;
+#define SPP_SLICES(NCHX) ffn_slices_kernel<T, NCHX, FULL, (R <= slices_rounds<T>(NCHX) ? R : 1), slices_ds<NCHX>()>
   if (start || stop) {
-    SPP_DISPATCH_NCH(nchl, hipExtLaunchKernelGGL((ffn_slices_kernel<T, NCH, FULL, (NCH <= 4 ? R : 1), slices_ds<NCH>()>),
-                                                  dim3(grid), dim3(64 * kSlWaves), 0, st, start, stop, 0u, a));
+    SPP_DISPATCH_NCH(nchl, hipExtLaunchKernelGGL((SPP_SLICES(NCH)), dim3(grid), dim3(64 * kSlWaves), 0, st, start,
+                                                  stop, 0u, a));
   } else {
-    SPP_DISPATCH_NCH(nchl, hipLaunchKernelGGL((ffn_slices_kernel<T, NCH, FULL, (NCH <= 4 ? R : 1), slices_ds<NCH>()>),
-                                               dim3(grid), dim3(64 * kSlWaves), 0, st, a));
+    SPP_DISPATCH_NCH(nchl, hipLaunchKernelGGL((SPP_SLICES(NCH)), dim3(grid), dim3(64 * kSlWaves), 0, st, a));
   }
+#undef SPP_SLICES
   return hipGetLastError();
 }
 
@@ -2737,6 +2772,9 @@ hipError_t ffn_slices_tf(const FfnArgs& a, int grid, hipStream_t st, hipEvent_t 
     case 1: return ffn_slices_tr<T, FULL, 1>(a, grid, st, start, stop);
     case 2: return ffn_slices_tr<T, FULL, 2>(a, grid, st, start, stop);
     case 3: return ffn_slices_tr<T, FULL, 3>(a, grid, st, start, stop);
+    case 4: return ffn_slices_tr<T, FULL, 4>(a, grid, st, start, stop);
+    case 5: return ffn_slices_tr<T, FULL, 5>(a, grid, st, start, stop);
+    case 6: return ffn_slices_tr<T, FULL, 6>(a, grid, st, start, stop);
     default: return hipErrorInvalidValue;
   }
 }
@@ -2800,7 +2838,7 @@ hipError_t ffn_q4_t(const FfnArgs& a, int grid, hipStream_t st, hipEvent_t start
 
 hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
   if (a.nW <= 0 || a.nW > kMaxWork || grid <= 0 || a.D > 4096) return hipErrorInvalidValue;
-  if (a.rounds > 0 && (a.skip_mask != 0 || a.rounds > (a.codec ? 2 : 3))) return hipErrorInvalidValue;
+  if (a.rounds > 0 && (a.skip_mask != 0 || a.rounds > (a.codec ? 2 : kSlMaxRounds))) return hipErrorInvalidValue;
   if (a.rounds == 0 && a.upw <= 0) return hipErrorInvalidValue;
   if (a.skip_mask != 0 && a.I % a.upw != 0) return hipErrorInvalidValue;  // a workgroup would span two items
   if (a.codec == 1) {
@@ -2816,7 +2854,7 @@ hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hip
 }
 
 hipError_t launch_combine(const CombineArgs& a, int dtype, hipStream_t st) {
-  const int grid = (a.D + 63) / 64;
+  const int grid = (a.D + kCombCols - 1) / kCombCols;
   if (dtype == 1)
     hipLaunchKernelGGL((ffn_combine_kernel<uint16_t>), dim3(grid), dim3(64 * kCombGroups), 0, st, a);
   else
@@ -2991,7 +3029,7 @@ hipError_t read_probe_q4_t(const FfnArgs& a, int grid, uint32_t* sink, hipStream
 
 hipError_t launch_read_probe(const FfnArgs& a, int grid, uint32_t* sink, hipStream_t st, hipEvent_t start,
                              hipEvent_t stop) {
-  if (a.nW <= 0 || a.nW > kMaxWork || grid <= 0 || a.rounds < 1 || a.rounds > 3 || !sink) return hipErrorInvalidValue;
+  if (a.nW <= 0 || a.nW > kMaxWork || grid <= 0 || a.rounds < 1 || a.rounds > kSlMaxRounds || !sink) return hipErrorInvalidValue;
   if (a.codec == 1) {
     // the sweep-order 4-bit FFN's loads: 3 units per wave and pass, 1 or 2 passes
     if (a.rounds > 2 || a.upp != 3 || a.D % 256 != 0 || a.D > 4096 ||
@@ -3005,14 +3043,17 @@ hipError_t launch_read_probe(const FfnArgs& a, int grid, uint32_t* sink, hipStre
   }
   if (static_cast<long>(grid) * kSlWaves * a.rounds < static_cast<long>(a.nW) * a.I) return hipErrorInvalidValue;
   const int nchl = nch_for<uint16_t>(a.D);
-  if (a.rounds > 1 && nchl > 4) return hipErrorInvalidValue;
+  if (a.rounds > slices_rounds<uint16_t>(nchl)) return hipErrorInvalidValue;
 #define SPP_PROBE(RR)                                                                                       \
-  SPP_DISPATCH_NCH(nchl, hipExtLaunchKernelGGL((read_probe_kernel<NCH, (NCH <= 4 ? RR : 1), slices_ds<NCH>()>), \
+  SPP_DISPATCH_NCH(nchl, hipExtLaunchKernelGGL((read_probe_kernel<NCH, (RR <= slices_rounds<uint16_t>(NCH) ? RR : 1), slices_ds<NCH>()>), \
                                                 dim3(grid), dim3(64 * kSlWaves), 0, st, start, stop, 0u, a, sink))
   switch (a.rounds) {
     case 1: SPP_PROBE(1); break;
     case 2: SPP_PROBE(2); break;
-    default: SPP_PROBE(3); break;
+    case 3: SPP_PROBE(3); break;
+    case 4: SPP_PROBE(4); break;
+    case 5: SPP_PROBE(5); break;
+    default: SPP_PROBE(6); break;
   }
 #undef SPP_PROBE
   return hipGetLastError();
@@ -3028,10 +3069,17 @@ hipError_t launch_stream_probe(const void* base, size_t bytes, uint32_t* sink, h
 }
 
 int ffn_grid_slices(int nunits, int D, int dtype, int target_wgs, int* rounds) {
-  const int nchl = dtype == 1 ? nch_for<uint16_t>(D) : nch_for<float>(D);
-  const int rmax = nchl <= 4 ? 3 : 1;
-  int r = static_cast<int>((static_cast<long>(nunits) + static_cast<long>(kSlWaves) * target_wgs / 2) /
+  const int rmax = dtype == 1 ? slices_rounds<uint16_t>(nch_for<uint16_t>(D)) : slices_rounds<float>(nch_for<float>(D));
+  int r = static_cast<int>((static_cast<long>(nunits) + static_cast<long>(kSlWaves) * target_wgs - 1) /
                            (static_cast<long>(kSlWaves) * std::max(target_wgs, 1)));
+  // The fewest rounds whose workgroups all fit on the device at once (two per
+  // compute unit; a third one waits for a whole launch's latency): the
+  // DeepSeek shape (7,168 units) took 22.4 us per layer with 598 workgroups of
+  // 3 rounds and 20.7 with 448 of 4, the Qwen shape 23.4 with 512 of 3 and
+  // 24.4 with 384 of 4.  Small lists take two rounds rather than more than
+  // one workgroup per compute unit (2,000 units of 2,048 columns: 16.7 us
+  // with 500 workgroups, 15.6 with 250).
+  if (r == 1 && nunits > kSlWaves * target_wgs / 2) r = 2;
   r = std::min(std::max(r, 1), rmax);
   int grid = (nunits + kSlWaves * r - 1) / (kSlWaves * r);
   if (grid > static_cast<int>(ffn_max_grid())) return 0;  // the partial rows would not fit

@@ -143,7 +143,7 @@ struct spp_ctx {
   float* ypart = nullptr;
   std::vector<hipEvent_t> round_done;  // per on-demand round: its FFN launch finished
   int64_t clock = 0;
-  int ffn_wgs = 512;  // about this many workgroups share one batch-1 FFN launch (bf16/fp32 experts)
+  int ffn_wgs = 512;  // at most about this many workgroups share one batch-1 FFN launch (bf16/fp32 experts)
   // test hooks
   bool poison = false;
   int32_t copy_delay_us = 0;

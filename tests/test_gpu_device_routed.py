@@ -116,3 +116,20 @@ def test_grouped_layers_give_the_same_bits_whatever_is_resident():
         finally:
             st.close()
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("D,I,dtype", [(512, 2600, "bf16"), (640, 2300, "bf16"), (1536, 1801, "bf16"),
+                                       (2048, 1900, "bf16"), (2304, 600, "bf16"), (2048, 351, "f32"), (520, 61, "bf16")],
+                         ids=["r6", "r5", "r4_ragged", "r4", "r2_long", "r2_f32_long", "r1"])
+def test_sweep_rounds_of_the_batch_1_ffn(D, I, dtype):
+    """Every number of sweep rounds the unit counts lead to, with rows that end inside a wave's chunks."""
+    from lockstep import run_lockstep
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    cfg = w.MoEConfig(name=f"rounds_D{D}_I{I}", L=1, D=D, n=6, K=4, I=I, r=0, S=6, windows=(1,), tokens=2, dtype=dtype,
+                      seed=47)
+    st = OffloadedMoEStack(cfg)
+    try:
+        rep = run_lockstep(st, cfg, cfg.tokens, -1)
+    finally:
+        st.close()
+    assert rep.max_ulp_h <= 1.0 + 1e-9 and not rep.exempt
