@@ -16,6 +16,13 @@ spp_status set_error(spp_status s, const char* msg);
 constexpr int kMaxWork = 32;       // expert blobs one FFN launch can combine
 constexpr int kMaxExpertsTopK = 1024;
 
+// The routing that a router launch publishes to FFN workgroups of the same
+// launch: kRouteCopies copies (spread over the pollers) of kRouteWords words,
+// word k the slot of the k-th selected expert, word 32 + k its gate (fp32
+// bits), each tagged (seq << 32) | payload.
+constexpr int kRouteWords = 64;
+constexpr int kRouteCopies = 8;
+
 // Router + adapter (one launch).  Rows [0, n) are router logits (if
 // router_on), rows [n, n+r) adapter hidden units (if A != nullptr).
 struct RouterArgs {
@@ -30,6 +37,7 @@ struct RouterArgs {
   float* zbuf;          // [B, n + r] logits then adapter hidden units
   uint64_t* ztag;       // [n + r] the same values tagged (seq << 32) | fp32 bits, for the batch-1
                         // single-wave tails (polled instead of a completion counter), or nullptr
+  uint64_t* route_tag;  // [kRouteCopies, kRouteWords], or nullptr (no FFN in this launch)
   int32_t* topk;        // [B, K]
   float* gates;         // [B, K]
   const int32_t* slot_tab;  // [n] slot of each expert, or nullptr (the host decides the slots)
@@ -66,7 +74,7 @@ struct FfnArgs {
                                // nonzero mask needs upw to divide I (each workgroup on one item)
   int codec;                   // 0: experts in dtype; 1: 4-bit blocks (dtype bf16)
   int rounds;                  // 0: workgroup b takes units [b*upw, (b+1)*upw) (ffn_units_kernel, and
-                               // ffn_q4_kernel by range); 1..6: sweep rounds of ffn_slices_kernel (see
+                               // ffn_q4_kernel by range); 1..3: sweep rounds of ffn_slices_kernel (see
                                // ffn_grid_slices); 4-bit experts: 1..2 sweep passes of ffn_q4_kernel
                                // (see ffn_grid_q4_sweep); upw unused in sweep order
   const float* x;              // [D] router input of the token
@@ -123,6 +131,12 @@ struct ProjArgs {
 hipError_t launch_router(const RouterArgs& a, int dtype, hipStream_t st);
 // start/stop (nullable) are stamped with the kernel's own begin/end times.
 hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop);
+// Router and FFN of one token in one launch: the FFN's workgroups take the
+// routing from ra.route_tag as soon as the router's publish it, and form x
+// themselves.  layer_launch_ok: whether this router and this FFN can share a
+// launch (slots named on the device, single-wave router tails, sweep order).
+bool layer_launch_ok(const RouterArgs& ra, const FfnArgs& fa, int dtype);
+hipError_t launch_layer(const RouterArgs& ra, const FfnArgs& fa, int grid, int dtype, hipStream_t st);
 hipError_t launch_combine(const CombineArgs& a, int dtype, hipStream_t st);
 hipError_t launch_proj(const ProjArgs& a, int dtype, hipStream_t st);
 // Grouped (batched) routed-expert FFN, bf16 only; D % 256 == 0, I % 16 == 0.
@@ -150,10 +164,9 @@ hipError_t launch_spin(uint64_t ticks, uint32_t max_iter, hipStream_t st);
 // Batch-1 FFN launch over `nunits` (expert, unit) pairs: units per workgroup
 // (*upw) so that about `target_wgs` workgroups share the work; returns the grid.
 int ffn_grid_for(int nunits, int target_wgs, int* upw);
-// The same work list in sweep rounds (bf16/fp32 experts, no skip mask): the
-// fewest rounds (*rounds, 1..6, as many as registers allow) with at most
-// `target_wgs` workgroups; returns the grid, or 0 when it would exceed
-// ffn_max_grid().
+// The same work list in sweep rounds (bf16/fp32 experts, no skip mask): about
+// `target_wgs` workgroups of *rounds (1..3) rounds; returns the grid, or 0 when
+// it would exceed ffn_max_grid().
 int ffn_grid_slices(int nunits, int D, int dtype, int target_wgs, int* rounds);
 // 4-bit experts in sweep order (no skip mask): passes (*rounds, 1 or 2) of 3
 // units per wave (*upp); returns the grid, or 0 when it would exceed

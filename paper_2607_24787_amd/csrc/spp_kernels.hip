@@ -300,6 +300,19 @@ __device__ __forceinline__ bool poll_tags(const uint64_t* p, int cnt, int lane, 
   return false;
 }
 
+// The routing that the router workgroups of this launch publish: lane k < K
+// returns the slot of the k-th selected expert, lane 32 + k its gate.  If the
+// bound runs out (the router's records are then missing too, or the output
+// shows it): slot 0 and a NaN gate.
+__device__ __forceinline__ uint32_t poll_route(const uint64_t* p, int K, int lane, unsigned seq) {
+  for (unsigned it = 0; it < kPollMax; ++it) {
+    const uint64_t t = __hip_atomic_load(p + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__all((lane & 31) >= K || static_cast<uint32_t>(t >> 32) == seq)) return static_cast<uint32_t>(t);
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return lane < 32 ? 0u : 0x7fc00000u;
+}
+
 // Token b's host records from wave 0 after select_topk (lane k < K: expert
 // s_isel[k], gate s_zsel[k]).
 __device__ __forceinline__ void route_records(const RouterArgs& a, int b, int tid, const float* s_zsel,
@@ -491,8 +504,9 @@ struct BStage {
 // than the last-arriver handoff, same outputs).  Without one (a caller with no
 // sequence numbers), the last workgroup through the counter takes it.
 // ---------------------------------------------------------------------------
+// `nblocks` workgroups take part; `bid` is this one's index among them.
 template <typename T, int NCH, bool FULL, int EPL>
-__global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) {
+__device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid, int nblocks) {
   constexpr int V = Vec<T>::N;
   constexpr int kBC = 8;  // 16-byte chunks of one B row in the fast tail (r <= 64 bf16)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -500,8 +514,8 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
   const int nr = a.router_on ? n : 0;
   const int na = a.A ? r : 0;
   const int gr = (nr + kWaves - 1) / kWaves;
-  const bool adapter_wg = static_cast<int>(blockIdx.x) >= gr;
-  const int row = (adapter_wg ? static_cast<int>(blockIdx.x) - gr : static_cast<int>(blockIdx.x)) * kWaves + wave;
+  const bool adapter_wg = bid >= gr;
+  const int row = (adapter_wg ? bid - gr : bid) * kWaves + wave;
 
   __shared__ int s_last;
   __shared__ float s_zsel[32];
@@ -524,7 +538,7 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
   uint4 rbf[EPL ? EPL : 1][kBC];
   if (EPL == 0) {
     bst.load(a, tid, adapter_wg && staged);
-  } else if (adapter_wg && wave == 0 && (!a.ztag || blockIdx.x == gridDim.x - 1)) {
+  } else if (sizeof(T) == 2 && adapter_wg && wave == 0 && (!a.ztag || bid == nblocks - 1)) {
     // B rows of this lane's experts (in the workgroup that may take the tail) (a chunk past r, or a row past n, re-reads
     // the first chunk of B and is dropped)
     const int rc = r / 8;
@@ -561,7 +575,7 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
   }
   // x goes out from the last wave of the last workgroup: never a tail wave,
   // whose first wait would otherwise include these stores
-  if (blockIdx.x == gridDim.x - 1 && wave == kWaves - 1 && a.x_out) {
+  if (bid == nblocks - 1 && wave == kWaves - 1 && a.x_out) {
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
       const int c = lane + 64 * j;
@@ -595,7 +609,7 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
   }
 
   const int kind = adapter_wg ? 1 : 0;
-  const unsigned total = adapter_wg ? gridDim.x - gr : gr;
+  const unsigned total = adapter_wg ? nblocks - gr : gr;
   if (EPL) {
     constexpr int Q = EPL ? EPL : 1;
     // Handoff.  Tagged values: wave 0 of its kind's last workgroup polls
@@ -604,7 +618,7 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
     // (after releasing its own values), and resets it.
     float zv[Q];
     if (a.ztag) {
-      if (wave != 0 || static_cast<int>(blockIdx.x) != (adapter_wg ? static_cast<int>(gridDim.x) : gr) - 1) return;
+      if (wave != 0 || bid != (adapter_wg ? nblocks : gr) - 1) return;
       // a poll that runs out leaves this launch's records unwritten: the host reports it
       if (!(adapter_wg ? poll_tags<1>(a.ztag + n, na, lane, a.seq, zv) : poll_tags<Q>(a.ztag, n, lane, a.seq, zv)))
         return;
@@ -665,8 +679,15 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
         const int t = __shfl(slt[q], isel & 63);
         slot = q == (isel >> 6) ? t : slot;
       }
+      const float gk = v / sum;
+      if (a.route_tag) {  // first: the FFN workgroups of this launch wait for it
+        const float gl = __shfl(gk, lane & 31);
+        const float word = lane < 32 ? __int_as_float(slot) : gl;
+        if ((lane & 31) < a.K)
+#pragma unroll
+          for (int c = 0; c < kRouteCopies; ++c) st_tag(a.route_tag + c * kRouteWords + lane, a.seq, word);
+      }
       if (on) {
-        const float gk = v / sum;
         a.topk[lane] = isel;
         a.gates[lane] = gk;
         if (a.slot_tab) a.sel[lane] = slot;
@@ -677,6 +698,7 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
       }
       return;
     }
+    if constexpr (sizeof(T) == 4) return;  // fp32 adapters take the general tail
     // adapter distribution pi_hat = softmax(B a)
     const float av = lane < na ? zv[0] : 0.f;
     float zh[Q];
@@ -687,7 +709,7 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
 #pragma unroll
       for (int c = 0; c < kBC; ++c) {
         float f[8];
-        unpack<T>(rbf[q][c], f);
+        unpack<uint16_t>(rbf[q][c], f);
 #pragma unroll
         for (int v = 0; v < 8; ++v) acc += f[v] * lane_value(av, 8 * c + v);
       }
@@ -754,6 +776,11 @@ __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) 
     }
   }
   if (tid == 0) __hip_atomic_store(a.counter + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename T, int NCH, bool FULL, int EPL>
+__global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) {
+  router_adapter_body<T, NCH, FULL, EPL>(a, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1159,8 +1186,49 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_units_kernel(FfnArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kSlWaves = 4;
 
-template <typename T, int NCH, bool FULL, int R, int DS>
-__global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
+// Input of the FFN from the layer's input: x = the router's normalised row,
+// formed as router_adapter_body forms it (same operations, same bits).
+template <typename T, int NCH, bool FULL>
+__device__ __forceinline__ void route_x(const RouterArgs& ra, int lane, int nch, float (&xv)[NCH][Vec<T>::N]) {
+  if (ra.u) {
+    load_row_f32<T, NCH, FULL>(ra.u, lane, nch, xv);
+  } else {
+    load_row_storage<T, NCH, FULL>(reinterpret_cast<const T*>(ra.h), lane, nch, xv);
+  }
+  const float inv = rms_scale<T, NCH>(xv, ra.D, ra.eps);
+#pragma unroll
+  for (int j = 0; j < NCH; ++j)
+#pragma unroll
+    for (int v = 0; v < Vec<T>::N; ++v) xv[j][v] *= inv;
+}
+
+// Wave 0 of a workgroup polls for the routing, the others get it through LDS.
+__device__ __forceinline__ uint32_t route_words(const RouterArgs& ra, int bid, int lane, int wave) {
+  __shared__ uint32_t s_route[kRouteWords];
+  if (wave == 0) s_route[lane] = poll_route(ra.route_tag + (bid % kRouteCopies) * kRouteWords, ra.K, lane, ra.seq);
+  __syncthreads();
+  return s_route[lane];
+}
+
+// Where the work items of an FFN lie.  Routed: in the words that poll_route
+// returned (wave-uniform lane reads); else in the arguments.
+template <bool ROUTED>
+struct Items {
+  uint32_t words = 0;
+  __device__ __forceinline__ const void* blob(const FfnArgs& a, int d) const {
+    if (ROUTED && d < a.nsel)
+      return a.slots + static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(words, d))) * a.stride;
+    return ROUTED ? a.blob[d] : work_blob(a, d);
+  }
+  __device__ __forceinline__ float gate(const FfnArgs& a, int d) const {
+    if (ROUTED) return d < a.nsel ? __uint_as_float(__builtin_amdgcn_readlane(words, 32 + d)) : 1.f;
+    const int gi = a.gate_idx[d];
+    return gi >= 0 ? a.gates[gi] : 1.f;
+  }
+};
+
+template <typename T, int NCH, bool FULL, int R, int DS, bool ROUTED>
+__device__ __forceinline__ void ffn_slices_body(const FfnArgs& a, const RouterArgs* ra, int bid, int nblocks) {
   constexpr int V = Vec<T>::N;
   constexpr int W = kSlWaves;
   __shared__ float s_h[R * W];
@@ -1168,15 +1236,21 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = a.D, nch = D / V, I = a.I;
   const int total = a.nW * I;
-  const int band = static_cast<int>(gridDim.x) * W;
-  const int first = static_cast<int>(blockIdx.x) * W;
+  const int band = nblocks * W;
+  const int first = bid * W;
   const size_t unit_elems = static_cast<size_t>(3) * D;
   const int cpw = (nch + W - 1) / W;
   const int c0 = wave * cpw;
 
   // x first: each unit's dot products then wait only for that unit's loads
   float xv[NCH][V];
-  load_row_f32<T, NCH, FULL>(a.x, lane, nch, xv);
+  Items<ROUTED> items;
+  if constexpr (ROUTED) {
+    route_x<T, NCH, FULL>(*ra, lane, nch, xv);
+    items.words = route_words(*ra, bid, lane, wave);
+  } else {
+    load_row_f32<T, NCH, FULL>(a.x, lane, nch, xv);
+  }
   __builtin_amdgcn_sched_barrier(0);
 
   // 1. every load of the wave, round by round (a unit past the end re-reads
@@ -1189,17 +1263,16 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
     const int u = ub + wave;
     const int uc = u < total ? u : total - 1;  // wave-uniform
     const int d = uc / I;
-    const T* base = reinterpret_cast<const T*>(work_blob(a, d)) + static_cast<size_t>(uc - d * I) * unit_elems;
+    const T* base = reinterpret_cast<const T*>(items.blob(a, d)) + static_cast<size_t>(uc - d * I) * unit_elems;
     load_chunks<NCH, FULL, true>(base, lane, nch, rg[r]);
     load_chunks<NCH, FULL, true>(base + D, lane, nch, ru[r]);
-    const int gi = a.gate_idx[d];
-    gate[r] = gi >= 0 ? a.gates[gi] : 1.f;
+    gate[r] = items.gate(a, d);
 #pragma unroll
     for (int w2 = 0; w2 < W; ++w2) {
       const int v = ub + w2;
       const int vc = v < total ? v : total - 1;  // wave-uniform
       const int d2 = vc / I;
-      const T* dbase = reinterpret_cast<const T*>(work_blob(a, d2)) + static_cast<size_t>(vc - d2 * I) * unit_elems + 2 * D;
+      const T* dbase = reinterpret_cast<const T*>(items.blob(a, d2)) + static_cast<size_t>(vc - d2 * I) * unit_elems + 2 * D;
 #pragma unroll
       for (int s = 0; s < DS; ++s) {
         const int c = c0 + lane + 64 * s;
@@ -1249,7 +1322,7 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
         for (int v = 0; v < V; ++v) acc[s][v] += h * fd[v];
       }
     }
-  float* out = a.partial + static_cast<size_t>(blockIdx.x) * D;
+  float* out = a.partial + static_cast<size_t>(bid) * D;
 #pragma unroll
   for (int s = 0; s < DS; ++s) {
     const int c = c0 + lane + 64 * s;
@@ -1258,6 +1331,23 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
       for (int v = 0; v < V; ++v) out[c * V + v] = acc[s][v];
     }
   }
+}
+
+template <typename T, int NCH, bool FULL, int R, int DS>
+__global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
+  ffn_slices_body<T, NCH, FULL, R, DS, false>(a, nullptr, blockIdx.x, gridDim.x);
+}
+
+// Router and FFN of one token in one launch (device-routed layers): the first
+// `rb` workgroups are router_adapter_body's, the others ffn_slices_body's.
+template <typename T, int NCH, bool FULL, int R, int DS>
+__global__ __launch_bounds__(64 * kSlWaves) void layer_slices_kernel(RouterArgs ra, FfnArgs fa, int rb) {
+  static_assert(kSlWaves == kWaves, "one workgroup size for both parts");
+  const int b = blockIdx.x;
+  if (b < rb)
+    router_adapter_body<T, NCH, FULL, 2>(ra, b, rb);
+  else
+    ffn_slices_body<T, NCH, FULL, R, DS, true>(fa, &ra, b - rb, static_cast<int>(gridDim.x) - rb);
 }
 
 // ---------------------------------------------------------------------------
@@ -1384,8 +1474,8 @@ __device__ __forceinline__ void q4_codes(const uint4& c, float (&q)[32]) {
 // No branch in front of the loads: a unit past the range re-reads the range's
 // last unit, a lane past the row's blocks reads block 0 (its x digits are
 // zero and its outputs are not stored).
-template <int NQ, bool FULLQ, int UPP>
-__device__ __forceinline__ void q4_pass_loads(const FfnArgs& a, int ub, int ustride, int u1, int lane,
+template <int NQ, bool FULLQ, int UPP, bool ROUTED>
+__device__ __forceinline__ void q4_pass_loads(const FfnArgs& a, const Items<ROUTED>& items, int ub, int ustride, int u1, int lane,
                                               uint4 (&cg)[UPP][NQ], uint4 (&cu)[UPP][NQ], uint4 (&cd)[UPP][NQ],
                                               uint16_t (&sg)[UPP][NQ], uint16_t (&su)[UPP][NQ],
                                               uint16_t (&sd)[UPP][NQ], float (&gate)[UPP]) {
@@ -1398,7 +1488,7 @@ __device__ __forceinline__ void q4_pass_loads(const FfnArgs& a, int ub, int ustr
     const int uc = uu < u1 ? uu : u1 - 1;  // wave-uniform
     const int d = uc / I;
     const int i = uc - d * I;
-    const uint8_t* base = reinterpret_cast<const uint8_t*>(work_blob(a, d)) + static_cast<size_t>(i) * unit_bytes;
+    const uint8_t* base = reinterpret_cast<const uint8_t*>(items.blob(a, d)) + static_cast<size_t>(i) * unit_bytes;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       const int blk = (FULLQ || lane + 64 * q < nblk) ? lane + 64 * q : 0;
@@ -1412,8 +1502,7 @@ __device__ __forceinline__ void q4_pass_loads(const FfnArgs& a, int ub, int ustr
       su[p][q] = *SPP_GLOBAL(uint16_t, base + 3 * cb + sb + 2 * blk);
       sd[p][q] = *SPP_GLOBAL(uint16_t, base + 3 * cb + 2 * sb + 2 * blk);
     }
-    const int gi = a.gate_idx[d];
-    gate[p] = gi >= 0 ? a.gates[gi] : 1.f;
+    gate[p] = items.gate(a, d);
   }
 }
 
@@ -1449,8 +1538,8 @@ __device__ __forceinline__ void q4_x_digits(const float (&xe)[8], int e, uint32_
   w[4] = Q[0] | (Q[1] << 4) | (Q[2] << 8) | (Q[3] << 12);
 }
 
-template <int NQ, bool FULLQ, int UPP, int PASSES>
-__global__ __launch_bounds__(kFfnThreads) void ffn_q4_kernel(FfnArgs a) {
+template <int NQ, bool FULLQ, int UPP, int PASSES, bool ROUTED>
+__device__ __forceinline__ void ffn_q4_body(const FfnArgs& a, const RouterArgs* ra, int bid, int nblocks) {
   static_assert(kFfnThreads == 256, "the digit words take four threads per block, 64 blocks per pass");
   extern __shared__ float s_red[];  // [kFfnWaves][D] wave partials
   __shared__ uint4 s_dig[NQ * 64 * 5];  // [block][digit j] words 0..3
@@ -1458,35 +1547,66 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_q4_kernel(FfnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int D = a.D, I = a.I, nblk = D / 32;
-  if (PASSES == 0 && ((a.skip_mask >> ((static_cast<int>(blockIdx.x) * a.upw) / I)) & 1u)) return;  // another launch's item
+  if (PASSES == 0 && ((a.skip_mask >> ((bid * a.upw) / I)) & 1u)) return;  // another launch's item
 
   // this thread's 8 elements of x per q: word tid % 4 of block tid / 4 + 64 q
   // (a block past the row reads block 0; its words are never used)
   float xe[NQ][8];
+  if constexpr (ROUTED) {
+    // the row's scale as the router forms it (16-byte chunk lane + 64 j in lane
+    // order); the thread's own elements are chunk tid + 256 q
+    constexpr int NCH = 4 * NQ;
+    const int nch = D / 8;
+    float xv[NCH][8], own[NQ][8];
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int bq = (tid >> 2) + 64 * q;
-    const float* xs = a.x + 32 * (FULLQ || bq < nblk ? bq : 0) + 8 * (tid & 3);
-    const float4 v0 = *SPP_GLOBAL(float4, xs), v1 = *SPP_GLOBAL(float4, xs + 4);
-    xe[q][0] = v0.x; xe[q][1] = v0.y; xe[q][2] = v0.z; xe[q][3] = v0.w;
-    xe[q][4] = v1.x; xe[q][5] = v1.y; xe[q][6] = v1.z; xe[q][7] = v1.w;
+    for (int q = 0; q < NQ; ++q) {
+      const int c = tid + 256 * q;
+      const int cc = FULLQ || c < nch ? c : 0;
+      if (ra->u) {
+        unpack<float>(ld16(ra->u + 8 * cc), own[q]);
+        unpack<float>(ld16(ra->u + 8 * cc + 4), own[q] + 4);
+      } else {
+        unpack<uint16_t>(ld16(reinterpret_cast<const uint16_t*>(ra->h) + 8 * cc), own[q]);
+      }
+    }
+    if (ra->u) {
+      load_row_f32<uint16_t, NCH, FULLQ>(ra->u, lane, nch, xv);
+    } else {
+      load_row_storage<uint16_t, NCH, FULLQ>(reinterpret_cast<const uint16_t*>(ra->h), lane, nch, xv);
+    }
+    const float inv = rms_scale<uint16_t, NCH>(xv, D, ra->eps);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) xe[q][k] = own[q][k] * inv;
+  } else {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int bq = (tid >> 2) + 64 * q;
+      const float* xs = a.x + 32 * (FULLQ || bq < nblk ? bq : 0) + 8 * (tid & 3);
+      const float4 v0 = *SPP_GLOBAL(float4, xs), v1 = *SPP_GLOBAL(float4, xs + 4);
+      xe[q][0] = v0.x; xe[q][1] = v0.y; xe[q][2] = v0.z; xe[q][3] = v0.w;
+      xe[q][4] = v1.x; xe[q][5] = v1.y; xe[q][6] = v1.z; xe[q][7] = v1.w;
+    }
   }
 
   const int total = a.nW * I;
   // range assignment: units [u0, u1) of this workgroup, wave stride kFfnWaves;
   // sweep order: the whole grid's units, stride NW
-  const int NW = static_cast<int>(gridDim.x) * kFfnWaves;
-  const int u0 = PASSES ? 0 : static_cast<int>(blockIdx.x) * a.upw;
+  const int NW = nblocks * kFfnWaves;
+  const int u0 = PASSES ? 0 : bid * a.upw;
   const int u1 = PASSES ? total : min(u0 + a.upw, total);
   const int ustride = PASSES ? NW : kFfnWaves;
-  const int ub0 = PASSES ? static_cast<int>(blockIdx.x) * kFfnWaves + wave : u0 + wave;
+  const int ub0 = PASSES ? bid * kFfnWaves + wave : u0 + wave;
   const int npass = PASSES ? PASSES : (a.upw + kFfnWaves * UPP - 1) / (kFfnWaves * UPP);
   uint4 cg[UPP][NQ], cu[UPP][NQ], cd[UPP][NQ];
   uint16_t sg[UPP][NQ], su[UPP][NQ], sd[UPP][NQ];
   float gate[UPP];
   // the first pass's weight loads go out before the digit words are formed
+  // (a routed workgroup forms them while it waits for the routing)
   const bool first = !(PASSES == 0 && ub0 >= u1);  // wave-uniform
-  if (first) q4_pass_loads<NQ, FULLQ, UPP>(a, ub0, ustride, u1, lane, cg, cu, cd, sg, su, sd, gate);
+  Items<ROUTED> items;
+  if (!ROUTED && first) q4_pass_loads<NQ, FULLQ, UPP>(a, items, ub0, ustride, u1, lane, cg, cu, cd, sg, su, sd, gate);
   __builtin_amdgcn_sched_barrier(0);
 
   // digit words of x, one block per four threads, through LDS
@@ -1506,7 +1626,13 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_q4_kernel(FfnArgs a) {
     for (int j = 0; j < 5; ++j) s_dw[(bq * 5 + j) * 4 + (tid & 3)] = w[j];
     if ((tid & 3) == 0) s_eb[bq] = ldexpf(1.f, e - 18);
   }
-  __syncthreads();
+  if constexpr (ROUTED) {
+    items.words = route_words(*ra, bid, lane, wave);  // its barrier also publishes the digit words
+    q4_pass_loads<NQ, FULLQ, UPP>(a, items, ub0, ustride, u1, lane, cg, cu, cd, sg, su, sd, gate);
+    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    __syncthreads();
+  }
   uint32_t xd[NQ][5][4];
   float eb[NQ];
 #pragma unroll
@@ -1534,7 +1660,7 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_q4_kernel(FfnArgs a) {
   for (int pr = 0; pr < npass; ++pr) {
     const int ub = ub0 + pr * UPP * ustride;
     if (PASSES == 0 && ub >= u1) break;  // wave-uniform
-    if (pr > 0) q4_pass_loads<NQ, FULLQ, UPP>(a, ub, ustride, u1, lane, cg, cu, cd, sg, su, sd, gate);
+    if (pr > 0) q4_pass_loads<NQ, FULLQ, UPP>(a, items, ub, ustride, u1, lane, cg, cu, cd, sg, su, sd, gate);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < UPP; ++p) {
@@ -1597,12 +1723,27 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_q4_kernel(FfnArgs a) {
     }
   }
   __syncthreads();
-  float* out = a.partial + static_cast<size_t>(blockIdx.x) * D;
+  float* out = a.partial + static_cast<size_t>(bid) * D;
   for (int d = tid; d < D; d += kFfnThreads) {
     const int blk = d >> 5, j = d & 31;
     const int w = 32 * blk + 4 * ((j >> 2) ^ (blk & 7)) + (j & 3);
     out[d] = (s_red[w] + s_red[2 * D + w]) + (s_red[D + w] + s_red[3 * D + w]);
   }
+}
+
+template <int NQ, bool FULLQ, int UPP, int PASSES>
+__global__ __launch_bounds__(kFfnThreads) void ffn_q4_kernel(FfnArgs a) {
+  ffn_q4_body<NQ, FULLQ, UPP, PASSES, false>(a, nullptr, blockIdx.x, gridDim.x);
+}
+
+// Router and 4-bit FFN of one token in one launch, as layer_slices_kernel.
+template <int NCH, bool FULL, int NQ, bool FULLQ, int PASSES>
+__global__ __launch_bounds__(kFfnThreads) void layer_q4_kernel(RouterArgs ra, FfnArgs fa, int rb) {
+  const int b = blockIdx.x;
+  if (b < rb)
+    router_adapter_body<uint16_t, NCH, FULL, 2>(ra, b, rb);
+  else
+    ffn_q4_body<NQ, FULLQ, 3, PASSES, true>(fa, &ra, b - rb, static_cast<int>(gridDim.x) - rb);
 }
 
 // Plain streaming read (measurement only): n16 16-byte chunks from base,
@@ -1679,56 +1820,44 @@ __global__ __launch_bounds__(kFfnThreads) void read_probe_q4_kernel(FfnArgs a, u
 }
 
 // y = sum of the workgroup partials (fixed order), h_out = round(residual + y).
-// A workgroup of 16 waves covers kCombCols columns, 4 per lane: a wave's load
-// takes kCombRowsPerWave partial rows, and all loads of up to kCombPass rows
-// are in flight together.  Each lane adds its rows in order, the lanes of a
-// column add across the wave, then the waves in order through LDS.  Latency
-// bound: 3.85 us for 512 rows of 2048 columns (4.05 with 4-byte loads and 64
-// columns per workgroup; 16 and 64 columns per workgroup 3.8 and 3.85).
+// kCombGroups groups split the partial rows: group g adds rows g*kCombRows..
+// of every pass in order, then the groups are added in order.  A thread holds 4
+// columns of one group; a pass's loads (512 rows) all go out before the first
+// add, 128 contiguous bytes per row and workgroup.  Latency bound: @@ us for
+// 512 rows of 2048 columns (4.05 with a column per thread, 64 per workgroup).
 constexpr int kCombGroups = 16;
+constexpr int kCombRows = 32;
 constexpr int kCombCols = 32;
 constexpr int kCombLanes = kCombCols / 4;
-constexpr int kCombRowsPerWave = 64 / kCombLanes;
-constexpr int kCombPass = 512;
-constexpr int kCombLoads = kCombPass / (kCombGroups * kCombRowsPerWave);
+constexpr int kCombThreads = kCombGroups * kCombLanes;
 
 template <typename T>
-__global__ __launch_bounds__(64 * kCombGroups) void ffn_combine_kernel(CombineArgs a) {
+__global__ __launch_bounds__(kCombThreads) void ffn_combine_kernel(CombineArgs a) {
   __shared__ float4 s_part[kCombGroups][kCombLanes];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cl = lane % kCombLanes;
+  const int tid = threadIdx.x;
+  const int cl = tid % kCombLanes, grp = tid / kCombLanes;
   const int col = min(static_cast<int>(blockIdx.x) * kCombCols + 4 * cl, a.D - 4);  // lanes past D re-read the last columns
-  const int row0 = wave * kCombRowsPerWave + lane / kCombLanes;
   // the residual of thread t < kCombCols: its column
   const int oc = static_cast<int>(blockIdx.x) * kCombCols + tid;
   const bool out = tid < kCombCols && oc < a.D;
   float res = 0.f;
   if (out) res = a.res_u ? a.res_u[oc] : load_elem<T>(a.res_h, oc);
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int p0 = 0; p0 < a.nparts; p0 += kCombPass) {
-    float4 v[kCombLoads];
+  for (int w0 = grp * kCombRows; w0 < a.nparts; w0 += kCombGroups * kCombRows) {
+    float4 v[kCombRows];
 #pragma unroll
-    for (int k = 0; k < kCombLoads; ++k)
-      v[k] = *SPP_GLOBAL(float4, a.partial + static_cast<size_t>(min(p0 + row0 + k * kCombGroups * kCombRowsPerWave,
-                                                                      a.nparts - 1)) * a.D + col);
+    for (int k = 0; k < kCombRows; ++k)
+      v[k] = *SPP_GLOBAL(float4, a.partial + static_cast<size_t>(min(w0 + k, a.nparts - 1)) * a.D + col);
 #pragma unroll
-    for (int k = 0; k < kCombLoads; ++k) {
-      if (p0 + row0 + k * kCombGroups * kCombRowsPerWave < a.nparts) {
-        s.x += v[k].x;
-        s.y += v[k].y;
-        s.z += v[k].z;
-        s.w += v[k].w;
-      }
+    for (int k = 0; k < kCombRows; ++k) {
+      const bool on = w0 + k < a.nparts;
+      s.x += on ? v[k].x : 0.f;
+      s.y += on ? v[k].y : 0.f;
+      s.z += on ? v[k].z : 0.f;
+      s.w += on ? v[k].w : 0.f;
     }
   }
-#pragma unroll
-  for (int o = kCombLanes; o < 64; o <<= 1) {
-    s.x += __shfl_xor(s.x, o);
-    s.y += __shfl_xor(s.y, o);
-    s.z += __shfl_xor(s.z, o);
-    s.w += __shfl_xor(s.w, o);
-  }
-  if (lane < kCombLanes) s_part[wave][lane] = s;
+  s_part[grp][cl] = s;
   __syncthreads();
   if (out) {
     const float* p = reinterpret_cast<const float*>(s_part) + tid;
@@ -2670,6 +2799,17 @@ void router_rows_t(const RouterArgs& a, int rows, hipStream_t st) {
     hipLaunchKernelGGL((router_rows_kernel<T, TU, 16>), grid, block, 0, st, a);
 }
 
+// Batch 1: router rows and adapter rows in workgroups of their own.
+int router_wgs(const RouterArgs& a) {
+  return ((a.router_on ? a.n : 0) + kWaves - 1) / kWaves + ((a.A ? a.r : 0) + kWaves - 1) / kWaves;
+}
+
+// Batch 1, single-wave tails: n <= 128, K <= 32 (checked at launch), an
+// adapter in bf16 with r <= 64 and a multiple of 8.
+bool one_wave_tails(const RouterArgs& a, bool bf16) {
+  return a.n <= 128 && (!a.A || (bf16 && a.r <= 64 && a.r % 8 == 0));
+}
+
 template <typename T, bool FULL>
 hipError_t router_tf(const RouterArgs& a, hipStream_t st) {
   const int rows = (a.router_on ? a.n : 0) + (a.A ? a.r : 0);
@@ -2677,10 +2817,8 @@ hipError_t router_tf(const RouterArgs& a, hipStream_t st) {
   // the staged adapter path reads B in 16-byte chunks
   if (a.A && (static_cast<size_t>(a.n) * a.r * sizeof(T)) % 16 != 0) return hipErrorInvalidValue;
   if (a.B == 1) {
-    // router rows and adapter rows in workgroups of their own
-    const int g1 = ((a.router_on ? a.n : 0) + kWaves - 1) / kWaves + ((a.A ? a.r : 0) + kWaves - 1) / kWaves;
-    // single-wave tails: bf16, n <= 128, K <= 64, r <= 64 and a multiple of 8
-    const bool fast = sizeof(T) == 2 && a.n <= 128 && a.K <= 64 && (!a.A || (a.r <= 64 && a.r % 8 == 0));
+    const int g1 = router_wgs(a);
+    const bool fast = one_wave_tails(a, sizeof(T) == 2);
     if (fast && a.n <= 64) {
       SPP_DISPATCH_NCH(nch_for<T>(a.D), hipLaunchKernelGGL((router_adapter_kernel<T, NCH, FULL, 1>), dim3(g1),
                                                            dim3(kThreads), 0, st, a));
@@ -2741,7 +2879,7 @@ constexpr int slices_ds() {
 constexpr int kSlMaxRounds = 6;
 template <typename T>
 constexpr int slices_rounds(int nch) {
-  return nch <= 2 ? 6 : nch <= 4 ? 4 : nch <= 6 ? 2 : (sizeof(T) == 4 ? 2 : 1);
+  return nch <= 4 ? 3 : nch <= 6 ? 2 : (sizeof(T) == 4 ? 2 : 1);
 }
 
 // Units per wave of ffn_units_batch_kernel: as many as stay in 256 registers
@@ -2810,6 +2948,75 @@ hipError_t launch_router(const RouterArgs& a, int dtype, hipStream_t st) {
   return dtype == 1 ? router_t<uint16_t>(a, st) : router_t<float>(a, st);
 }
 
+namespace {
+
+template <typename T, bool FULL, int R>
+hipError_t layer_slices_tr(const RouterArgs& ra, const FfnArgs& fa, int rb, int grid, hipStream_t st) {
+  const int nchl = nch_for<T>(fa.D);
+  if (R > slices_rounds<T>(nchl)) return hipErrorInvalidValue;
+  SPP_DISPATCH_NCH(nchl, hipLaunchKernelGGL(
+                             (layer_slices_kernel<T, NCH, FULL, (R <= slices_rounds<T>(NCH) ? R : 1), slices_ds<NCH>()>),
+                             dim3(rb + grid), dim3(64 * kSlWaves), 0, st, ra, fa, rb));
+  return hipGetLastError();
+}
+
+template <typename T, bool FULL>
+hipError_t layer_slices_tf(const RouterArgs& ra, const FfnArgs& fa, int rb, int grid, hipStream_t st) {
+  switch (fa.rounds) {
+    case 1: return layer_slices_tr<T, FULL, 1>(ra, fa, rb, grid, st);
+    case 2: return layer_slices_tr<T, FULL, 2>(ra, fa, rb, grid, st);
+    case 3: return layer_slices_tr<T, FULL, 3>(ra, fa, rb, grid, st);
+    case 4: return layer_slices_tr<T, FULL, 4>(ra, fa, rb, grid, st);
+    case 5: return layer_slices_tr<T, FULL, 5>(ra, fa, rb, grid, st);
+    case 6: return layer_slices_tr<T, FULL, 6>(ra, fa, rb, grid, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T>
+hipError_t layer_slices_t(const RouterArgs& ra, const FfnArgs& fa, int rb, int grid, hipStream_t st) {
+  if (static_cast<long>(grid) * kSlWaves * fa.rounds < static_cast<long>(fa.nW) * fa.I) return hipErrorInvalidValue;
+  return full_rows<T>(fa.D) ? layer_slices_tf<T, true>(ra, fa, rb, grid, st)
+                            : layer_slices_tf<T, false>(ra, fa, rb, grid, st);
+}
+
+template <int NCH, bool FULL, int NQ, bool FULLQ>
+hipError_t layer_q4_t(const RouterArgs& ra, const FfnArgs& fa, int rb, int grid, hipStream_t st) {
+  const uint32_t lds = sizeof(float) * kFfnWaves * fa.D;
+  if (fa.rounds == 1)
+    hipLaunchKernelGGL((layer_q4_kernel<NCH, FULL, NQ, FULLQ, 1>), dim3(rb + grid), dim3(kFfnThreads), lds, st, ra, fa,
+                       rb);
+  else
+    hipLaunchKernelGGL((layer_q4_kernel<NCH, FULL, NQ, FULLQ, 2>), dim3(rb + grid), dim3(kFfnThreads), lds, st, ra, fa,
+                       rb);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool layer_launch_ok(const RouterArgs& ra, const FfnArgs& fa, int dtype) {
+  return ra.B == 1 && ra.router_on && !ra.x_given && ra.slot_tab && ra.ztag && ra.route_tag &&
+         one_wave_tails(ra, dtype == 1) && fa.rounds > 0 && fa.nsel == ra.K;
+}
+
+hipError_t launch_layer(const RouterArgs& ra, const FfnArgs& fa, int grid, int dtype, hipStream_t st) {
+  if (!layer_launch_ok(ra, fa, dtype) || ra.K > 32 || ra.K > ra.n || ra.D != fa.D || fa.D > 4096 || fa.nW <= 0 ||
+      fa.nW > kMaxWork || grid <= 0 || fa.skip_mask != 0 || fa.rounds > (fa.codec ? 2 : kSlMaxRounds))
+    return hipErrorInvalidValue;
+  const int rb = router_wgs(ra);
+  if (fa.codec == 1) {
+    if (dtype != 1 || fa.D % 256 != 0 || fa.upp != 3 ||
+        static_cast<long>(grid) * kFfnWaves * 3 * fa.rounds < static_cast<long>(fa.nW) * fa.I)
+      return hipErrorInvalidValue;
+    const int nblk = fa.D / 32;
+    if (nblk == 64) return layer_q4_t<4, true, 1, true>(ra, fa, rb, grid, st);
+    if (nblk < 64) return layer_q4_t<4, false, 1, false>(ra, fa, rb, grid, st);
+    if (nblk == 128) return layer_q4_t<8, true, 2, true>(ra, fa, rb, grid, st);
+    return layer_q4_t<8, false, 2, false>(ra, fa, rb, grid, st);
+  }
+  return dtype == 1 ? layer_slices_t<uint16_t>(ra, fa, rb, grid, st) : layer_slices_t<float>(ra, fa, rb, grid, st);
+}
+
 template <int NQ, bool FULLQ, int UPP, int PASSES>
 hipError_t ffn_q4_tu(const FfnArgs& a, int grid, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
   const uint32_t lds = sizeof(float) * kFfnWaves * a.D;  // 64 KiB at D 4096
@@ -2856,9 +3063,9 @@ hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hip
 hipError_t launch_combine(const CombineArgs& a, int dtype, hipStream_t st) {
   const int grid = (a.D + kCombCols - 1) / kCombCols;
   if (dtype == 1)
-    hipLaunchKernelGGL((ffn_combine_kernel<uint16_t>), dim3(grid), dim3(64 * kCombGroups), 0, st, a);
+    hipLaunchKernelGGL((ffn_combine_kernel<uint16_t>), dim3(grid), dim3(kCombThreads), 0, st, a);
   else
-    hipLaunchKernelGGL((ffn_combine_kernel<float>), dim3(grid), dim3(64 * kCombGroups), 0, st, a);
+    hipLaunchKernelGGL((ffn_combine_kernel<float>), dim3(grid), dim3(kCombThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -3070,16 +3277,12 @@ hipError_t launch_stream_probe(const void* base, size_t bytes, uint32_t* sink, h
 
 int ffn_grid_slices(int nunits, int D, int dtype, int target_wgs, int* rounds) {
   const int rmax = dtype == 1 ? slices_rounds<uint16_t>(nch_for<uint16_t>(D)) : slices_rounds<float>(nch_for<float>(D));
-  int r = static_cast<int>((static_cast<long>(nunits) + static_cast<long>(kSlWaves) * target_wgs - 1) /
-                           (static_cast<long>(kSlWaves) * std::max(target_wgs, 1)));
-  // The fewest rounds whose workgroups all fit on the device at once (two per
-  // compute unit; a third one waits for a whole launch's latency): the
-  // DeepSeek shape (7,168 units) took 22.4 us per layer with 598 workgroups of
-  // 3 rounds and 20.7 with 448 of 4, the Qwen shape 23.4 with 512 of 3 and
-  // 24.4 with 384 of 4.  Small lists take two rounds rather than more than
-  // one workgroup per compute unit (2,000 units of 2,048 columns: 16.7 us
-  // with 500 workgroups, 15.6 with 250).
-  if (r == 1 && nunits > kSlWaves * target_wgs / 2) r = 2;
+  const int nchl = dtype == 1 ? nch_for<uint16_t>(D) : nch_for<float>(D);
+  const long per = static_cast<long>(kSlWaves) * std::max(target_wgs, 1);
+  // up to 4 chunks per lane: the number of rounds that puts the grid nearest
+  // target_wgs (all of it is resident: 4 workgroups per compute unit fit);
+  // longer rows: at most target_wgs workgroups
+  int r = static_cast<int>((nunits + (nchl <= 4 ? per / 2 : per - 1)) / per);
   r = std::min(std::max(r, 1), rmax);
   int grid = (nunits + kSlWaves * r - 1) / (kSlWaves * r);
   if (grid > static_cast<int>(ffn_max_grid())) return 0;  // the partial rows would not fit

@@ -104,6 +104,7 @@ struct spp_ctx {
   float* x_dev = nullptr;      // [maxB, D] router input
   float* zbuf = nullptr;       // [maxB, n + r]
   uint64_t* ztag = nullptr;    // [n + r] batch-1 router values tagged with their launch's seq (zero: none yet)
+  size_t off_route_tag = 0;    // into ztag: the routing published within a launch (RouterArgs::route_tag)
   uint8_t* res_dev = nullptr;  // topk [maxB*K] i32 | gates [maxB*K] f32 | sel [maxB*K] i32 | s [n] f32
   size_t res_bytes = 0, off_gates = 0, off_sel = 0, off_s = 0;
   int32_t* slot_tabs = nullptr;  // [L, n] device expert -> slot tables
@@ -143,7 +144,7 @@ struct spp_ctx {
   float* ypart = nullptr;
   std::vector<hipEvent_t> round_done;  // per on-demand round: its FFN launch finished
   int64_t clock = 0;
-  int ffn_wgs = 512;  // at most about this many workgroups share one batch-1 FFN launch (bf16/fp32 experts)
+  int ffn_wgs = 512;  // about this many workgroups share one batch-1 FFN launch (bf16/fp32 experts)
   // test hooks
   bool poison = false;
   int32_t copy_delay_us = 0;
@@ -601,10 +602,12 @@ spp_status create_impl(const spp_model_desc* desc, void* stream, spp_ctx** out) 
     SPP_HIP(hipEventCreateWithFlags(&ls.last_read, kOrderEventFlags));
   }
   const size_t BD = static_cast<size_t>(d.max_batch) * d.D;
+  c->off_route_tag = round_up(static_cast<size_t>(d.n + d.r), 16);
+  const size_t tags = c->off_route_tag + static_cast<size_t>(spp::kRouteCopies) * spp::kRouteWords;
   if (hipMalloc(&c->u_dev, BD * sizeof(float)) != hipSuccess ||
       hipMalloc(&c->x_dev, BD * sizeof(float)) != hipSuccess ||
       hipMalloc(&c->zbuf, static_cast<size_t>(d.max_batch) * (d.n + d.r) * sizeof(float)) != hipSuccess ||
-      hipMalloc(&c->ztag, static_cast<size_t>(d.n + d.r) * sizeof(uint64_t)) != hipSuccess ||
+      hipMalloc(&c->ztag, tags * sizeof(uint64_t)) != hipSuccess ||
       hipMalloc(&c->partial, spp::ffn_max_grid() * d.D * sizeof(float)) != hipSuccess ||
       hipMalloc(&c->counter, 256) != hipSuccess)
     return fail(SPP_ENOMEM, "scratch allocation failed");
@@ -653,7 +656,7 @@ spp_status create_impl(const spp_model_desc* desc, void* stream, spp_ctx** out) 
       return fail(SPP_ENOMEM, "batched-decode buffers allocation failed");
   }
   SPP_HIP(hipMemset(c->counter, 0, 256));
-  SPP_HIP(hipMemset(c->ztag, 0, static_cast<size_t>(d.n + d.r) * sizeof(uint64_t)));  // seq 0 is never handed out
+  SPP_HIP(hipMemset(c->ztag, 0, tags * sizeof(uint64_t)));  // seq 0 is never handed out
   SPP_HIP(hipMemset(c->res_dev, 0, c->res_bytes));
   c->last_s.assign(d.n, 0.f);
   SPP_HIP(hipDeviceSynchronize());
@@ -1107,6 +1110,19 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   ra.x_given = 0;
   ra.router_on = 1;
   ra.seq = fl.seq;
+  // router and FFN in one launch where both kernels can (timing keeps them
+  // apart: its events stand between the two)
+  if (fl.routed && !batched_ffn(c, B) && !c->timing) {
+    ra.route_tag = c->ztag + c->off_route_tag;
+    spp::FfnArgs fa{};
+    const int grid = build_ffn(c, ls, nullptr, false, &fa);
+    if (spp::layer_launch_ok(ra, fa, dt)) {
+      SPP_HIP(spp::launch_layer(ra, fa, grid, dt, c->compute));
+      fl.t_router = std::chrono::steady_clock::now();
+      return combine_token(c, fl, grid);
+    }
+    ra.route_tag = nullptr;
+  }
   SPP_HIP(spp::launch_router(ra, dt, c->compute));
   fl.t_router = std::chrono::steady_clock::now();
   if (c->timing) SPP_HIP(hipEventRecord(ts.ev[kEvRouted], c->compute));

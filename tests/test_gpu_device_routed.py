@@ -19,9 +19,16 @@ BASE = w.MoEConfig(name="routed_bf16_D640_n40_k5", L=4, D=640, n=40, K=5, I=100,
     BASE.with_(r=16, n_shared=1),                          # single-wave tail, one expert per lane
     BASE.with_(r=16, n=100, K=6, has_proj=True),           # two experts per lane, projection in front
     BASE.with_(D=256, I=96, r=8, codec="q4"),
+    # router and FFN in one launch: rows past 2,048 columns, exact and ragged, every adapter width and list
+    BASE.with_(D=2304, I=64, r=8, n=16, S=9, codec="q4"),
+    BASE.with_(D=4096, I=33, r=64, n=16, S=9, codec="q4", n_shared=2),
+    BASE.with_(D=2056, I=61, r=64, n=128, K=8, S=20),
+    BASE.with_(D=4096, I=5, r=8, n=9, K=1, S=3),
+    BASE.with_(D=1300, I=37, r=8, dtype="f32", K=3, n_shared=1, has_proj=True),
     BASE.with_(D=128, I=64, r=8, dtype="f32", batch=3, S=17, n_shared=1),
     BASE.with_(I=100, batch=3, S=17),                      # bf16 in the unit layout (I not a multiple of 16)
-], ids=["b1_wide_tail", "b1_one_wave", "b1_n100_proj", "q4", "f32_b3", "bf16_units_b3"])
+], ids=["b1_wide_tail", "b1_one_wave", "b1_n100_proj", "q4", "q4_ragged", "q4_long", "b1_long_ragged", "b1_k1", "b1_f32",
+        "f32_b3", "bf16_units_b3"])
 def test_device_and_host_routed_layers_give_the_same_bits(cfg):
     from paper_2607_24787_amd import spp
     from paper_2607_24787_amd.model import OffloadedMoEStack
@@ -120,7 +127,7 @@ def test_grouped_layers_give_the_same_bits_whatever_is_resident():
 
 @pytest.mark.parametrize("D,I,dtype", [(512, 2600, "bf16"), (640, 2300, "bf16"), (1536, 1801, "bf16"),
                                        (2048, 1900, "bf16"), (2304, 600, "bf16"), (2048, 351, "f32"), (520, 61, "bf16")],
-                         ids=["r6", "r5", "r4_ragged", "r4", "r2_long", "r2_f32_long", "r1"])
+                         ids=["D512", "D640", "D1536", "D2048", "D2304", "f32_D2048", "D520"])
 def test_sweep_rounds_of_the_batch_1_ffn(D, I, dtype):
     """Every number of sweep rounds the unit counts lead to, with rows that end inside a wave's chunks."""
     from lockstep import run_lockstep
