@@ -311,9 +311,10 @@ const char* spp_last_error(void);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * adapter_predict computation, s = sum over the B tokens of
  * softmax(B^l A^l x_b), on explicit device weights and without a context.
- * Its scratch (two completion counters and B * (n + r) floats of adapter
- * hidden units and per-token distributions) is one fixed device array inside
- * the library, 256 + 4 * SPP_STATIC_SCRATCH_FLOATS bytes (328 KiB), which
+ * Its scratch (two completion counters, a count of completed launches, one
+ * call's tagged hidden units and B * (n + r) floats of adapter hidden units
+ * and per-token distributions) is one fixed device array inside
+ * the library, 1792 + 4 * SPP_STATIC_SCRATCH_FLOATS bytes (330 KiB), which
  * each device the library runs on holds until the process ends; B * (n + r)
  * may not exceed SPP_STATIC_SCRATCH_FLOATS (e.g. 64 tokens with n 1024 and
  * r 256).  Allocates nothing: no hipMalloc or hipFree, no host waits.
@@ -325,7 +326,8 @@ const char* spp_last_error(void);
  * enqueued on hip_stream (NULL: the null stream) and the call returns
  * without waiting; s_out_dev is complete when the stream reaches that point.
  * Every call on a device shares that device's scratch, which keeps the last
- * call's contents (the counters are cleared at the start of each call):
+ * call's contents (each call clears the counters, or tags its values with a
+ * count that no earlier call used):
  * calls that overlap on one device race, so a caller keeps them on one
  * stream.  Errors: EINVAL (NULL or misaligned pointer, bad shape, B * (n + r)
  * above the limit; nothing enqueued), EHIP. */

@@ -51,6 +51,8 @@ struct RouterArgs {
                         // records of a token are one contiguous store per wave, not K
   uint64_t* s_rec;      // [n]: priority s_e (fp32 bits)
   unsigned* counter;    // [2] zero between launches (router rows, adapter rows)
+  int clear;            // B > 1: the rows launch clears `counter` first
+  unsigned* epoch;      // completed launches, in place of seq (adapter_by_epoch calls with ztag only), or nullptr
   unsigned seq;         // this launch's sequence number (never 0)
   int B, D, n, K, r;
   float eps;
@@ -129,6 +131,9 @@ struct ProjArgs {
 };
 
 hipError_t launch_router(const RouterArgs& a, int dtype, hipStream_t st);
+// Whether an adapter call hands its rows over by tags (RouterArgs::epoch can
+// then stand in for the counters and for seq).
+bool adapter_by_epoch(int n, int r, int B, int dtype);
 // start/stop (nullable) are stamped with the kernel's own begin/end times.
 hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop);
 // Router and FFN of one token in one launch: the FFN's workgroups take the

@@ -531,6 +531,10 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
   const bool has_row = row < rows;
   const T* wrow = reinterpret_cast<const T*>(adapter_wg ? a.A : a.Wr) + static_cast<size_t>(min(row, rows - 1)) * D;
   const int zcol = adapter_wg ? n + row : row;
+  // a caller without launch numbers (its launches may be replays of a graph):
+  // one past the count of completed launches, which the tail moves on after
+  // every row's tag, so after every read here that is used
+  const unsigned seq = a.epoch ? __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u : a.seq;
   uint4 w[NCH];
   load_chunks<NCH, FULL>(wrow, lane, has_row ? nch : 0, w);
   const bool staged = na && n * r <= kBStage;
@@ -604,7 +608,7 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
     acc = wave_sum(acc);
     if (lane == 0) {
       st_agent(a.zbuf + zcol, acc);
-      if (EPL && a.ztag) st_tag(a.ztag + zcol, a.seq, acc);
+      if (EPL && a.ztag) st_tag(a.ztag + zcol, seq, acc);
     }
   }
 
@@ -620,7 +624,7 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
     if (a.ztag) {
       if (wave != 0 || bid != (adapter_wg ? nblocks : gr) - 1) return;
       // a poll that runs out leaves this launch's records unwritten: the host reports it
-      if (!(adapter_wg ? poll_tags<1>(a.ztag + n, na, lane, a.seq, zv) : poll_tags<Q>(a.ztag, n, lane, a.seq, zv)))
+      if (!(adapter_wg ? poll_tags<1>(a.ztag + n, na, lane, seq, zv) : poll_tags<Q>(a.ztag, n, lane, seq, zv)))
         return;
     } else {
       wait_own_stores();  // release this wave's value
@@ -699,6 +703,7 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
       return;
     }
     if constexpr (sizeof(T) == 4) return;  // fp32 adapters take the general tail
+    if (a.epoch && lane == 0) __hip_atomic_store(a.epoch, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // adapter distribution pi_hat = softmax(B a)
     const float av = lane < na ? zv[0] : 0.f;
     float zh[Q];
@@ -2528,6 +2533,8 @@ struct Raw8<float> {
 // TU: element type of u (float, or T when the layer input itself is read)
 template <typename T, typename TU, int KSW>
 __global__ __launch_bounds__(64 * kRowWaves) void router_rows_kernel(RouterArgs a) {
+  // for the selection that follows, where no earlier launch vouches for them
+  if (a.clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) a.counter[threadIdx.x] = 0u;
   __shared__ f32x4 s_acc[kRowWaves][64];
   __shared__ float s_ss[kRowWaves][16];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -2942,6 +2949,14 @@ hipError_t proj_t(const ProjArgs& a, hipStream_t st) {
 }
 
 }  // namespace
+
+bool adapter_by_epoch(int n, int r, int B, int dtype) {
+  RouterArgs a{};
+  a.A = &a;  // an adapter is there
+  a.n = n;
+  a.r = r;
+  return B == 1 && one_wave_tails(a, dtype == 1);
+}
 
 hipError_t launch_router(const RouterArgs& a, int dtype, hipStream_t st) {
   if (a.n > kMaxExpertsTopK || a.r > 256 || a.K > 32 || a.K > a.n) return hipErrorInvalidValue;

@@ -1,6 +1,7 @@
 // adapter_predict_static: the adapter priorities of section "Expert
 // Prediction Adapter" on explicit device weights, for callers that cannot
-// allocate device memory.  Its scratch -- two completion counters and the
+// allocate device memory.  Its scratch -- two completion counters, a count of
+// completed launches, the tagged hidden units of a one-token call and the
 // per-token adapter hidden units / distributions -- lives in one file-scope
 // device array of fixed size instead of a context's allocation.  Each device
 // the library runs on holds its own copy of the array (at its own address,
@@ -16,18 +17,24 @@
 
 namespace {
 
-constexpr int kCounterWords = 64;  // 256 bytes; the router kernels use the first two
+constexpr int kCounterWords = 64;  // 256 bytes; the router kernels use the first two, the third counts launches
+constexpr int kEpochWord = 2;
+constexpr int kTags = 128 + 64;    // one-wave tails: n <= 128 (unused here), r <= 64
 constexpr size_t kScratchFloats = SPP_STATIC_SCRATCH_FLOATS;
 
-// [counters: kCounterWords u32][hidden units / distributions: B * (n + r) floats]
-static __device__ __align__(256) float scratch[kCounterWords + kScratchFloats];
+// [counters: kCounterWords u32][tags: kTags u64][hidden units / distributions: B * (n + r) floats]
+static __device__ __align__(256) float scratch[kCounterWords + 2 * kTags + kScratchFloats];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
 void* g_scratch[kMaxDevices] = {};  // device address of `scratch` on each device, once looked up
 
-// The counters must start at zero; a kernel clears them (no memset node in a
-// captured graph).
+// The counters must start at zero.  A one-token call with one-wave tails
+// needs none (its rows are tagged with the launch count), a batch's first
+// launch clears them, and for the rest a kernel does (no memset node in a
+// captured graph).  Bound by launches and one round of cold loads: 128 experts,
+// r 64, D 2048, one token 7.9 us (11.1 with the clearing launch in front and
+// counters for the hand-over).
 __global__ void clear_counters(unsigned* p, int n) {
   const int i = static_cast<int>(threadIdx.x);
   if (i < n) p[i] = 0u;
@@ -79,14 +86,21 @@ extern "C" spp_status adapter_predict_static(const void* adapter_a, const void* 
   if (e != hipSuccess) return spp::set_error(SPP_EHIP, hipGetErrorString(e));
   const hipStream_t st = static_cast<hipStream_t>(hip_stream);
   unsigned* counter = static_cast<unsigned*>(base);
-  hipLaunchKernelGGL(clear_counters, dim3(1), dim3(64), 0, st, counter, 2);
-  e = hipGetLastError();
-  if (e != hipSuccess) return spp::set_error(SPP_EHIP, hipGetErrorString(e));
   spp::RouterArgs ra{};
+  if (spp::adapter_by_epoch(n, r, B, dtype)) {
+    ra.ztag = reinterpret_cast<uint64_t*>(counter + kCounterWords);
+    ra.epoch = counter + kEpochWord;
+  } else if (B > 1) {
+    ra.clear = 1;
+  } else {
+    hipLaunchKernelGGL(clear_counters, dim3(1), dim3(64), 0, st, counter, 2);
+    e = hipGetLastError();
+    if (e != hipSuccess) return spp::set_error(SPP_EHIP, hipGetErrorString(e));
+  }
   ra.u = x_dev;           // the router inputs themselves (no normalisation)
   ra.A = adapter_a;
   ra.Bm = adapter_b;
-  ra.zbuf = static_cast<float*>(base) + kCounterWords;
+  ra.zbuf = static_cast<float*>(base) + kCounterWords + 2 * kTags;
   ra.s = s_out_dev;
   ra.counter = counter;
   ra.B = B;

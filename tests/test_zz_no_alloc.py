@@ -69,3 +69,41 @@ def test_static_scratch_entry_point_matches_adapter_predict(torch_cuda, cfg):
             assert e.value.status == spp.SPP_EINVAL
     finally:
         st.close()
+
+
+@pytest.mark.parametrize("n,r,D,dtype", [(12, 8, 256, "bf16"), (128, 64, 2048, "bf16"), (72, 5, 256, "bf16"),
+                                         (33, 16, 640, "f32")], ids=["one_wave", "two_per_lane", "wide_tail", "f32"])
+@pytest.mark.parametrize("B", [1, 3])
+def test_static_scratch_replays_of_a_graph(torch_cuda, n, r, D, dtype, B):
+    """Replays with new inputs, eager calls of other sizes between them: every one gives the eager result."""
+    import torch
+    from paper_2607_24787_amd import spp
+    dt, code = (torch.bfloat16, spp.DTYPE_BF16) if dtype == "bf16" else (torch.float32, spp.DTYPE_F32)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.empty((r, D), device="cuda").normal_(0, 0.05, generator=g).to(dt)
+    Bm = torch.empty((n, r), device="cuda").normal_(0, 0.5, generator=g).to(dt)
+    x, out, eager = (torch.zeros(s, device="cuda") for s in ((B, D), (n,), (n,)))
+    x2 = torch.empty((5, D), device="cuda").normal_(generator=g)
+
+    def call(xs, b, dst):
+        spp.adapter_predict_static(A.data_ptr(), Bm.data_ptr(), code, D, n, r, xs.data_ptr(), b, dst.data_ptr(),
+                                   torch.cuda.current_stream().cuda_stream)
+
+    call(x, B, eager)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(x, B, out)
+        call(x, B, out)
+    for t in range(6):
+        _log(f"[static graph] n={n} r={r} B={B} replay {t}")
+        x.normal_(generator=g)
+        out.fill_(float("nan"))
+        graph.replay()
+        call(x, B, eager)
+        if t % 2:
+            call(x2, 5 if t == 3 else 1, torch.empty_like(eager))
+        torch.cuda.synchronize()
+        want = torch.softmax(x.double() @ A.double().T @ Bm.double().T, dim=-1).sum(0)
+        assert torch.equal(out, eager), t
+        assert torch.allclose(out.double(), want, rtol=1e-5, atol=2e-6), t
