@@ -2378,8 +2378,12 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_units_batch_kernel(GroupArg
 // every wave of a full workgroup a run (59 ranges of 4 pairs in one run each
 // would wait for four rounds of loads).
 constexpr int kCombWaves = 16;
-constexpr int kCombRanges = 16;  // range loads of one pair in flight per pass
-template <typename T>
+constexpr int kCombRanges = 16;  // range loads of one pair in flight per pass, at most
+// RG: loads per pass, the smallest of 1, 2, 4, 8 and kCombRanges that holds a
+// run (loads past a run's end re-read its last range: 16 of them per pair
+// where a pair has 2 ranges took 19.4 us at 256 tokens of 8 Qwen-shaped
+// experts each, 2 of them 10.3 us, at 64 tokens 6.1 and 4.8).
+template <typename T, int RG>
 __global__ __launch_bounds__(64 * kCombWaves) void ffn_combine_batched_kernel(CombineBArgs a) {
   __shared__ float4 s_v[kMaxWork][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
@@ -2393,13 +2397,13 @@ __global__ __launch_bounds__(64 * kCombWaves) void ffn_combine_batched_kernel(Co
     const int pair = p < a.K ? b * a.K + p : a.B * a.K + b * a.n_shared + (p - a.K);
     const float* base = a.ypart + static_cast<size_t>(pair) * a.nsplit * a.D + c;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int r0 = rb; r0 < re; r0 += kCombRanges) {
-      float4 w[kCombRanges];
+    for (int r0 = rb; r0 < re; r0 += RG) {
+      float4 w[RG];
 #pragma unroll
-      for (int q = 0; q < kCombRanges; ++q)
+      for (int q = 0; q < RG; ++q)
         w[q] = *SPP_GLOBAL(float4, base + static_cast<size_t>(min(r0 + q, re - 1)) * a.D);
 #pragma unroll
-      for (int q = 0; q < kCombRanges; ++q) {
+      for (int q = 0; q < RG; ++q) {
         if (r0 + q < re) {  // ranges in order
           v.x += w[q].x;
           v.y += w[q].y;
@@ -3165,10 +3169,24 @@ hipError_t launch_combine_batched(const CombineBArgs& args, int dtype, hipStream
   a.parts = std::max(1, std::min(kCombWaves / npairs, (a.nsplit + kCombRanges - 1) / kCombRanges));
   const dim3 grid((a.D / 4 + 63) / 64, a.B);
   const dim3 block(64 * min(npairs * a.parts, kCombWaves));
-  if (dtype == 1)
-    hipLaunchKernelGGL((ffn_combine_batched_kernel<uint16_t>), grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL((ffn_combine_batched_kernel<float>), grid, block, 0, st, a);
+  const int per = (a.nsplit + a.parts - 1) / a.parts;
+#define SPP_COMBINE(RG)                                                                       \
+  if (dtype == 1)                                                                             \
+    hipLaunchKernelGGL((ffn_combine_batched_kernel<uint16_t, RG>), grid, block, 0, st, a);    \
+  else                                                                                        \
+    hipLaunchKernelGGL((ffn_combine_batched_kernel<float, RG>), grid, block, 0, st, a)
+  if (per <= 1) {
+    SPP_COMBINE(1);
+  } else if (per <= 2) {
+    SPP_COMBINE(2);
+  } else if (per <= 4) {
+    SPP_COMBINE(4);
+  } else if (per <= 8) {
+    SPP_COMBINE(8);
+  } else {
+    SPP_COMBINE(kCombRanges);
+  }
+#undef SPP_COMBINE
   return hipGetLastError();
 }
 
