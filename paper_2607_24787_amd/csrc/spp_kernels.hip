@@ -1345,6 +1345,15 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
 
 // Router and FFN of one token in one launch (device-routed layers): the first
 // `rb` workgroups are router_adapter_body's, the others ffn_slices_body's.
+// The FFN's workgroups are already resident and hold x when the routing
+// appears, and the router's stores to the host leave the critical path; as a
+// launch of its own the FFN started only after those stores, a launch's
+// latency and a load of x.  They wait only for workgroups of lower index,
+// which are dispatched before them.  Qwen-shaped: router 6.5 + FFN 14.8 us ->
+// 19.1 in one launch, the layer 24.2 -> 22.1; 4-bit 6.5 + 9.8 -> 13.8, the
+// layer 18.0 -> 16.9; 1,024 units of 256 fp32 columns 5.1 + 3.8 -> 6.0.  The
+// same for a batch (selection and FFN in one launch, every workgroup waiting
+// for the pairs' tagged words) gained 0.3 to 1.4% and was not kept.
 template <typename T, int NCH, bool FULL, int R, int DS>
 __global__ __launch_bounds__(64 * kSlWaves) void layer_slices_kernel(RouterArgs ra, FfnArgs fa, int rb) {
   static_assert(kSlWaves == kWaves, "one workgroup size for both parts");
@@ -1828,7 +1837,7 @@ __global__ __launch_bounds__(kFfnThreads) void read_probe_q4_kernel(FfnArgs a, u
 // kCombGroups groups split the partial rows: group g adds rows g*kCombRows..
 // of every pass in order, then the groups are added in order.  A thread holds 4
 // columns of one group; a pass's loads (512 rows) all go out before the first
-// add, 128 contiguous bytes per row and workgroup.  Latency bound: @@ us for
+// add, 128 contiguous bytes per row and workgroup.  Latency bound: 3.9 us for
 // 512 rows of 2048 columns (4.05 with a column per thread, 64 per workgroup).
 constexpr int kCombGroups = 16;
 constexpr int kCombRows = 32;
@@ -2885,9 +2894,12 @@ constexpr int slices_ds() {
   return NCH <= 4 ? 1 : 2;
 }
 
-// Most sweep rounds whose loads stay in registers (2 NCH + 4 DS chunks of 4
-// registers each per round, beside x).
-constexpr int kSlMaxRounds = 6;
+// Most sweep rounds: what stays in registers beside x (2 NCH + 4 DS chunks of
+// 4 registers each per round).  Up to 4 chunks per lane no more than 3: which
+// units share a partial row is part of a stack's rounding, and 4 rounds on 448
+// workgroups, although faster over 7,168 units (17.3 against 18.4 us), turn
+// near-ties of later layers' routers.
+constexpr int kSlMaxRounds = 3;
 template <typename T>
 constexpr int slices_rounds(int nch) {
   return nch <= 4 ? 3 : nch <= 6 ? 2 : (sizeof(T) == 4 ? 2 : 1);
@@ -2921,9 +2933,6 @@ hipError_t ffn_slices_tf(const FfnArgs& a, int grid, hipStream_t st, hipEvent_t 
     case 1: return ffn_slices_tr<T, FULL, 1>(a, grid, st, start, stop);
     case 2: return ffn_slices_tr<T, FULL, 2>(a, grid, st, start, stop);
     case 3: return ffn_slices_tr<T, FULL, 3>(a, grid, st, start, stop);
-    case 4: return ffn_slices_tr<T, FULL, 4>(a, grid, st, start, stop);
-    case 5: return ffn_slices_tr<T, FULL, 5>(a, grid, st, start, stop);
-    case 6: return ffn_slices_tr<T, FULL, 6>(a, grid, st, start, stop);
     default: return hipErrorInvalidValue;
   }
 }
@@ -2985,9 +2994,6 @@ hipError_t layer_slices_tf(const RouterArgs& ra, const FfnArgs& fa, int rb, int 
     case 1: return layer_slices_tr<T, FULL, 1>(ra, fa, rb, grid, st);
     case 2: return layer_slices_tr<T, FULL, 2>(ra, fa, rb, grid, st);
     case 3: return layer_slices_tr<T, FULL, 3>(ra, fa, rb, grid, st);
-    case 4: return layer_slices_tr<T, FULL, 4>(ra, fa, rb, grid, st);
-    case 5: return layer_slices_tr<T, FULL, 5>(ra, fa, rb, grid, st);
-    case 6: return layer_slices_tr<T, FULL, 6>(ra, fa, rb, grid, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -3290,10 +3296,7 @@ hipError_t launch_read_probe(const FfnArgs& a, int grid, uint32_t* sink, hipStre
   switch (a.rounds) {
     case 1: SPP_PROBE(1); break;
     case 2: SPP_PROBE(2); break;
-    case 3: SPP_PROBE(3); break;
-    case 4: SPP_PROBE(4); break;
-    case 5: SPP_PROBE(5); break;
-    default: SPP_PROBE(6); break;
+    default: SPP_PROBE(3); break;
   }
 #undef SPP_PROBE
   return hipGetLastError();
@@ -3309,12 +3312,13 @@ hipError_t launch_stream_probe(const void* base, size_t bytes, uint32_t* sink, h
 }
 
 int ffn_grid_slices(int nunits, int D, int dtype, int target_wgs, int* rounds) {
-  const int rmax = dtype == 1 ? slices_rounds<uint16_t>(nch_for<uint16_t>(D)) : slices_rounds<float>(nch_for<float>(D));
   const int nchl = dtype == 1 ? nch_for<uint16_t>(D) : nch_for<float>(D);
+  const int rmax = dtype == 1 ? slices_rounds<uint16_t>(nchl) : slices_rounds<float>(nchl);
   const long per = static_cast<long>(kSlWaves) * std::max(target_wgs, 1);
-  // up to 4 chunks per lane: the number of rounds that puts the grid nearest
-  // target_wgs (all of it is resident: 4 workgroups per compute unit fit);
-  // longer rows: at most target_wgs workgroups
+  // Up to 4 chunks per lane: the number of rounds that puts the grid nearest
+  // target_wgs (see slices_rounds).  Longer rows: the fewest with at most
+  // target_wgs workgroups, two per compute unit (3,600 units of 2,304 columns:
+  // 25.4 us with 900 workgroups of one round, 21.3 with 450 of two).
   int r = static_cast<int>((nunits + (nchl <= 4 ? per / 2 : per - 1)) / per);
   r = std::min(std::max(r, 1), rmax);
   int grid = (nunits + kSlWaves * r - 1) / (kSlWaves * r);
