@@ -816,7 +816,7 @@ __global__ __launch_bounds__(kThreads) void router_select_kernel(RouterArgs a) {
   float z[kEQ];
 #pragma unroll
   for (int q = 0; q < kEQ; ++q) z[q] = zrow[min(tid + kThreads * q, n - 1)];
-  const float hid = zrow[n + min(tid, max(na - 1, 0))];
+  const float hid = tid < na ? zrow[n + tid] : 0.f;  // without an adapter the row may end at its n logits
 #pragma unroll
   for (int q = 0; q < kEQ; ++q) {
     const int e = tid + kThreads * q;

@@ -108,6 +108,24 @@ def test_grouped_layers_against_the_oracle(cfg, resident):
     assert len(rep.exempt) <= 1
 
 
+@pytest.mark.parametrize("cfg", [
+    GROUPED.with_(n=140, K=3, I=48, batch=7, r=0, S=140),
+    GROUPED.with_(n=140, K=3, I=25, batch=3, r=0, S=140, dtype="f32", D=272),
+], ids=["tiled", "units_f32"])
+def test_batched_selection_without_an_adapter(cfg):
+    """The workgroup-wide selection (more than 128 experts) of a full batch where a row of the logit buffer holds
+    nothing behind its n logits: its last row ends the buffer."""
+    from lockstep import run_lockstep
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    st = OffloadedMoEStack(cfg)
+    try:
+        rep = run_lockstep(st, cfg, cfg.tokens, -1)
+    finally:
+        st.close()
+    assert rep.max_ulp_h <= 1.0 + 1e-9 and rep.max_err_g <= 1e-5
+    assert len(rep.exempt) <= 1
+
+
 def test_grouped_layers_give_the_same_bits_whatever_is_resident():
     from paper_2607_24787_amd.model import OffloadedMoEStack
     cfg = GROUPED.with_(n=24, K=4, I=208, batch=21, n_shared=0)
