@@ -2026,6 +2026,47 @@ __device__ __forceinline__ void grp_load_down(const GroupArgs& a, const uint16_t
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Non-finite outputs of the three-term products, formed again as one product per
+// unit in unit order: a term of h that is 0 times an infinite weight is a NaN
+// where h times the weight is infinite.  Reached only by a wave that stored such
+// an output (the loop above it keeps the largest magnitude of its outputs, one
+// maximum per value); each lane reads back what it stored itself.
+template <int W, int TT>
+__device__ __forceinline__ void grp_nonfinite(const GroupArgs& a, const uint16_t* down, int i0, int nu, int m, int split,
+                                           int wave, int lane, const uint16_t* s_h, int hrow, const int* s_pair) {
+  const int D = a.D;
+#pragma unroll 1
+  for (int slab = wave; slab < D / 128; slab += W) {
+    const int d0 = 128 * slab + 8 * (lane & 15);
+    const uint16_t* p = down + (static_cast<size_t>(slab >> 1) * a.I + i0) * kGrpBlk + (slab & 1) * 128 + 8 * (lane & 15);
+#pragma unroll 1
+    for (int q = 0; q < 4 * TT; ++q) {
+      const int t = 16 * (q >> 2) + 4 * (lane >> 4) + (q & 3);
+      if (t >= m) continue;
+      float* dst = a.ypart + (static_cast<size_t>(s_pair[t]) * a.nsplit + split) * D + d0;
+      bool bad = false;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) bad = bad || !isfinite(dst[c]);
+      if (!bad) continue;
+      float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int u = 0; u < nu; ++u) {
+        const uint16_t* hp = s_h + t * hrow + grp_h_pos(u);
+        float h = 0.f;  // the lowest term first: every sum is exact
+#pragma unroll
+        for (int k = 2; k >= 0; --k) h += __uint_as_float(static_cast<uint32_t>(hp[k * kGroupTokens * hrow]) << 16);
+        float w[8];
+        unpack<uint16_t>(ld16(p + static_cast<size_t>(u) * kGrpBlk), w);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) y[c] = fmaf(h, w[c], y[c]);
+      }
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (!isfinite(dst[c])) dst[c] = y[c];
+    }
+  }
+}
+
 // r0 holds the loads of the wave's first step.
 template <int W, int TT>
 __device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* down, int i0, int nu, int m, int split,
@@ -2051,6 +2092,7 @@ __device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* 
     }
   };
   int slab = wave, st = 0;  // of the next multiply
+  uint32_t top = 0;         // largest magnitude stored (bits of a non-negative float)
   auto mul = [&](u32x4 (&r)[8]) {
     if (32 * st + 32 > nu)  // nu is a multiple of 16: the upper half of the step is past the range
 #pragma unroll
@@ -2088,6 +2130,8 @@ __device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* 
             float* dst = a.ypart + (static_cast<size_t>(s_pair[t]) * a.nsplit + split) * D + d0;
             reinterpret_cast<f32x4*>(dst)[0] = f32x4{acc[tt][0][j], acc[tt][1][j], acc[tt][2][j], acc[tt][3][j]};
             reinterpret_cast<f32x4*>(dst)[1] = f32x4{acc[tt][4][j], acc[tt][5][j], acc[tt][6][j], acc[tt][7][j]};
+#pragma unroll
+            for (int c = 0; c < 8; ++c) top = max(top, __float_as_uint(acc[tt][c][j]) & 0x7fffffffu);
           }
         }
 #pragma unroll
@@ -2112,6 +2156,7 @@ __device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* 
     }
     if (it + 1 < total) mul(r1);
   }
+  if (__any(top >= 0x7f800000u)) grp_nonfinite<W, TT>(a, down, i0, nu, m, split, wave, lane, s_h, hrow, s_pair);
 }
 
 // The group of this workgroup: its blob, its token count m and, in LDS, its

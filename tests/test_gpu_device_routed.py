@@ -5,7 +5,9 @@ whenever a layer changes from one to the other."""
 import numpy as np
 import pytest
 
+import oracle as o
 import workload as w
+from paper_2607_24787_amd import spp
 from workload import gen
 
 pytestmark = pytest.mark.gpu
@@ -30,7 +32,6 @@ BASE = w.MoEConfig(name="routed_bf16_D640_n40_k5", L=4, D=640, n=40, K=5, I=100,
 ], ids=["b1_wide_tail", "b1_one_wave", "b1_n100_proj", "q4", "q4_ragged", "q4_long", "b1_long_ragged", "b1_k1", "b1_f32",
         "f32_b3", "bf16_units_b3"])
 def test_device_and_host_routed_layers_give_the_same_bits(cfg):
-    from paper_2607_24787_amd import spp
     from paper_2607_24787_amd.model import OffloadedMoEStack
     h0 = gen.hidden_states(cfg, tokens=cfg.tokens)
     host = OffloadedMoEStack(cfg)                # S < n: every layer decided on the host
@@ -141,6 +142,55 @@ def test_grouped_layers_give_the_same_bits_whatever_is_resident():
         finally:
             st.close()
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("I", [80, 400], ids=["one_range", "ranges"])
+def test_grouped_layers_with_non_finite_down_weights(monkeypatch, I):
+    """An infinite down weight gives the infinity of h's sign (h has 24 significant bits, of which the products take 8
+    at a time: a part that is 0 must not turn the output into a NaN), a NaN weight a NaN, and every other output the
+    bits it has with zeros in those places."""
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    cfg = GROUPED.with_(L=1, I=I)
+    per = 60                                       # columns of each expert with an infinite weight, and one with a NaN
+    n_all = cfg.n + cfg.n_shared
+    cols = np.random.default_rng(7).permutation(cfg.D)[:n_all * (per + 1)].reshape(n_all, per + 1)
+    units = np.random.default_rng(8).integers(0, I, size=(n_all, per + 1))
+    routed, shared = gen.expert_weights, gen.shared_expert_weights
+
+    def planted(bits):
+        def put(ws, e):
+            g, u, d = ws
+            d = d.copy()
+            d[cols[e, :per], units[e, :per]] = bits[0]
+            d[cols[e, per], units[e, per]] = bits[1]
+            return g, u, d
+        monkeypatch.setattr(gen, "expert_weights", lambda c, l, e: put(routed(c, l, e), e))
+        monkeypatch.setattr(gen, "shared_expert_weights", lambda c, l, j: put(shared(c, l, j), cfg.n + j))
+
+    h0 = gen.hidden_states(cfg, tokens=1)
+    outs = []
+    for bits in ((0x7f80, 0x7fc0), (0, 0)):
+        planted(bits)
+        st = OffloadedMoEStack(cfg)
+        try:
+            topk = st.decode_step_from(_in(st, h0[0]), -1)[0][0]
+            outs.append(o.decode(st.download(st.hbuf[0]), cfg.dtype))
+            x = spp.spp_get_last_router_input(st.ctx, cfg.batch, cfg.D).astype(np.float64)
+        finally:
+            st.close()
+    got, plain = outs
+    want = plain.copy()
+    for e in range(n_all):
+        g, u, _ = routed(cfg, 0, e) if e < cfg.n else shared(cfg, 0, e - cfg.n)
+        g, u = o.decode(g, cfg.dtype), o.decode(u, cfg.dtype)
+        for b in range(cfg.batch):
+            if e < cfg.n and e not in topk[b]:
+                continue
+            a = x[b] @ g.T.astype(np.float64)
+            h = a / (1 + np.exp(-a)) * (x[b] @ u.T.astype(np.float64))
+            want[b, cols[e, :per]] = np.copysign(np.inf, h[units[e, :per]])
+            want[b, cols[e, per]] = np.nan
+    np.testing.assert_array_equal(got, want)
 
 
 @pytest.mark.parametrize("D,I,dtype", [(512, 2600, "bf16"), (640, 2300, "bf16"), (1536, 1801, "bf16"),
