@@ -174,6 +174,8 @@ typedef struct {
    * nothing to host_decide_us */
   double host_route_us;
   double host_decide_us;
+  /* batch-1 layer calls whose router and FFN went out as one launch */
+  int64_t layer_launches;
 } spp_run_stats;
 
 /* ---------------------------------------------------------------- lifecycle */
@@ -492,6 +494,11 @@ spp_status spp_set_tier_delay(spp_ctx* ctx, int32_t delay_us);
  * Outputs are unchanged by both. */
 spp_status spp_debug_set_poison(spp_ctx* ctx, int32_t enabled);
 spp_status spp_debug_set_copy_delay(spp_ctx* ctx, int32_t delay_us);
+
+/* Test hook for layer calls whose router and FFN share a launch: the polls
+ * after which an FFN workgroup that has not seen the routing forms it itself
+ * (0: at once; -1: the default).  Outputs are unchanged.  EINVAL below -1. */
+spp_status spp_debug_set_route_polls(spp_ctx* ctx, int32_t polls);
 
 /* ------------------------------------- host replacement policy (no device) */
 

@@ -22,6 +22,9 @@ constexpr int kMaxExpertsTopK = 1024;
 // bits), each tagged (seq << 32) | payload.
 constexpr int kRouteWords = 64;
 constexpr int kRouteCopies = 8;
+// Polls (about a microsecond each) after which such a workgroup forms the
+// routing itself.
+constexpr unsigned kRoutePolls = 256;
 
 // Router + adapter (one launch).  Rows [0, n) are router logits (if
 // router_on), rows [n, n+r) adapter hidden units (if A != nullptr).
@@ -38,6 +41,7 @@ struct RouterArgs {
   uint64_t* ztag;       // [n + r] the same values tagged (seq << 32) | fp32 bits, for the batch-1
                         // single-wave tails (polled instead of a completion counter), or nullptr
   uint64_t* route_tag;  // [kRouteCopies, kRouteWords], or nullptr (no FFN in this launch)
+  unsigned route_polls; // with route_tag: polls before an FFN workgroup forms the routing itself
   int32_t* topk;        // [B, K]
   float* gates;         // [B, K]
   const int32_t* slot_tab;  // [n] slot of each expert, or nullptr (the host decides the slots)
@@ -137,8 +141,8 @@ bool adapter_by_epoch(int n, int r, int B, int dtype);
 // start/stop (nullable) are stamped with the kernel's own begin/end times.
 hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop);
 // Router and FFN of one token in one launch: the FFN's workgroups take the
-// routing from ra.route_tag as soon as the router's publish it, and form x
-// themselves.  layer_launch_ok: whether this router and this FFN can share a
+// routing from ra.route_tag as soon as the router's publish it (or form it
+// themselves after ra.route_polls polls), and form x themselves.  layer_launch_ok: whether this router and this FFN can share a
 // launch (slots named on the device, single-wave router tails, sweep order).
 bool layer_launch_ok(const RouterArgs& ra, const FfnArgs& fa, int dtype);
 hipError_t launch_layer(const RouterArgs& ra, const FfnArgs& fa, int grid, int dtype, hipStream_t st);

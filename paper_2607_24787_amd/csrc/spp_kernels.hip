@@ -276,9 +276,10 @@ __device__ __forceinline__ void st_tag(uint64_t* p, unsigned seq, float v) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Bound on the polls of one wait (each at least one device-memory round trip,
-// so about a second): every workgroup of a launch this small is resident at
-// once, so the bound is only reached if the launch cannot make progress.
+// Bound on the polls of a router tail (each at least one device-memory round
+// trip, so about a second).  One wave per kind of row waits, for workgroups
+// that were dispatched before its own and wait for nothing, so the bound is
+// only reached where other work keeps those off the device that long.
 constexpr unsigned kPollMax = 1u << 20;
 
 // Lane l's values p[l + 64 q] (q < Q; indices >= cnt are not waited for) once
@@ -300,17 +301,19 @@ __device__ __forceinline__ bool poll_tags(const uint64_t* p, int cnt, int lane, 
   return false;
 }
 
-// The routing that the router workgroups of this launch publish: lane k < K
-// returns the slot of the k-th selected expert, lane 32 + k its gate.  If the
-// bound runs out (the router's records are then missing too, or the output
-// shows it): slot 0 and a NaN gate.
-__device__ __forceinline__ uint32_t poll_route(const uint64_t* p, int K, int lane, unsigned seq) {
-  for (unsigned it = 0; it < kPollMax; ++it) {
+// The routing that the router workgroups of this launch publish, if it appears
+// within `polls` polls: lane k < K gets the slot of the k-th selected expert,
+// lane 32 + k its gate.
+__device__ __forceinline__ bool poll_route(const uint64_t* p, int K, int lane, unsigned seq, unsigned polls,
+                                           uint32_t* word) {
+  *word = 0;
+  for (unsigned it = 0; it < polls; ++it) {
     const uint64_t t = __hip_atomic_load(p + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__all((lane & 31) >= K || static_cast<uint32_t>(t >> 32) == seq)) return static_cast<uint32_t>(t);
+    *word = static_cast<uint32_t>(t);
+    if (__all((lane & 31) >= K || static_cast<uint32_t>(t >> 32) == seq)) return true;
     __builtin_amdgcn_s_sleep(1);
   }
-  return lane < 32 ? 0u : 0x7fc00000u;
+  return false;
 }
 
 // Token b's host records from wave 0 after select_topk (lane k < K: expert
@@ -479,6 +482,77 @@ struct BStage {
   }
 };
 
+// A router (or adapter) row times x, summed over the wave.
+template <typename T, int NCH>
+__device__ __forceinline__ float row_dot(const uint4 (&w)[NCH], const float (&xv)[NCH][Vec<T>::N]) {
+  float acc = 0.f;
+#pragma unroll
+  for (int j = 0; j < NCH; ++j) {
+    float wf[Vec<T>::N];
+    unpack<T>(w[j], wf);
+#pragma unroll
+    for (int v = 0; v < Vec<T>::N; ++v) acc += wf[v] * xv[j][v];
+  }
+  return wave_sum(acc);
+}
+
+// One token's routing in one wave (n <= 64 Q, K <= 32): zv[q] the logit and
+// slt[q] the slot of expert lane + 64 q.  Lane k < K returns the gate of the
+// k-th selected expert, with its id and slot.
+template <int Q>
+__device__ __forceinline__ float select_wave(const float (&zv)[Q], const int (&slt)[Q], int n, int K, int lane,
+                                             int* isel_out, int* slot_out) {
+  uint32_t u[Q];
+  bool av[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    av[q] = lane + 64 * q < n;
+    u[q] = logit_order(zv[q]);
+  }
+  float zsel = 0.f;
+  int isel = 0;
+  for (int k = 0; k < K; ++k) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) c = max(c, av[q] ? u[q] : 0u);
+    const uint32_t m = wave_max_u32(c);
+    int e = -1;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const uint64_t hit = __ballot(av[q] && u[q] == m);
+      if (e < 0 && hit) e = 64 * q + __builtin_ctzll(hit);
+    }
+    if (lane == (e & 63)) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (q == (e >> 6)) av[q] = false;
+    }
+    if (lane == k) {
+      zsel = order_logit(m);
+      isel = e;
+    }
+  }
+  const float m0 = lane_value(zsel, 0);
+  const float v = lane < K ? expf(zsel - m0) : 0.f;
+  const float sum = wave_sum(v);
+  int slot = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int t = __shfl(slt[q], isel & 63);
+    slot = q == (isel >> 6) ? t : slot;
+  }
+  *isel_out = isel;
+  *slot_out = slot;
+  return v / sum;
+}
+
+// The routing of select_wave as the words of RouterArgs::route_tag: lane k < K
+// the slot, lane 32 + k the gate.
+__device__ __forceinline__ uint32_t route_word(int slot, float gk, int lane) {
+  const uint32_t gl = __float_as_uint(__shfl(gk, lane & 31));
+  return lane < 32 ? static_cast<uint32_t>(slot) : gl;
+}
+
 // ---------------------------------------------------------------------------
 // Router for one token, one launch.  Workgroups [0, gr) hold the router rows,
 // the rest the adapter-A rows, one wave per weight row.  Each kind hands off
@@ -597,15 +671,7 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
     }
   }
   if (has_row) {
-    float acc = 0.f;
-#pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-      float wf[V];
-      unpack<T>(w[j], wf);
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc += wf[v] * xv[j][v];
-    }
-    acc = wave_sum(acc);
+    const float acc = row_dot<T, NCH>(w, xv);
     if (lane == 0) {
       st_agent(a.zbuf + zcol, acc);
       if (EPL && a.ztag) st_tag(a.ztag + zcol, seq, acc);
@@ -643,55 +709,15 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
       }
     }
     if (!adapter_wg) {
-      uint32_t u[Q];
-      bool av[Q];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        av[q] = lane + 64 * q < n;
-        u[q] = logit_order(zv[q]);
-      }
-      float zsel = 0.f;
-      int isel = 0;
-      for (int k = 0; k < a.K; ++k) {
-        uint32_t c = 0;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) c = max(c, av[q] ? u[q] : 0u);
-        const uint32_t m = wave_max_u32(c);
-        int e = -1;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const uint64_t hit = __ballot(av[q] && u[q] == m);
-          if (e < 0 && hit) e = 64 * q + __builtin_ctzll(hit);
-        }
-        if (lane == (e & 63)) {
-#pragma unroll
-          for (int q = 0; q < Q; ++q)
-            if (q == (e >> 6)) av[q] = false;
-        }
-        if (lane == k) {
-          zsel = order_logit(m);
-          isel = e;
-        }
-      }
-      const bool on = lane < a.K;
-      const float m0 = lane_value(zsel, 0);
-      const float v = on ? expf(zsel - m0) : 0.f;
-      const float sum = wave_sum(v);
-      int slot = 0;
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const int t = __shfl(slt[q], isel & 63);
-        slot = q == (isel >> 6) ? t : slot;
-      }
-      const float gk = v / sum;
+      int isel, slot;
+      const float gk = select_wave<Q>(zv, slt, n, a.K, lane, &isel, &slot);
       if (a.route_tag) {  // first: the FFN workgroups of this launch wait for it
-        const float gl = __shfl(gk, lane & 31);
-        const float word = lane < 32 ? __int_as_float(slot) : gl;
+        const float word = __uint_as_float(route_word(slot, gk, lane));
         if ((lane & 31) < a.K)
 #pragma unroll
           for (int c = 0; c < kRouteCopies; ++c) st_tag(a.route_tag + c * kRouteWords + lane, a.seq, word);
       }
-      if (on) {
+      if (lane < a.K) {
         a.topk[lane] = isel;
         a.gates[lane] = gk;
         if (a.slot_tab) a.sel[lane] = slot;
@@ -1207,10 +1233,37 @@ __device__ __forceinline__ void route_x(const RouterArgs& ra, int lane, int nch,
     for (int v = 0; v < Vec<T>::N; ++v) xv[j][v] *= inv;
 }
 
-// Wave 0 of a workgroup polls for the routing, the others get it through LDS.
-__device__ __forceinline__ uint32_t route_words(const RouterArgs& ra, int bid, int lane, int wave) {
+// The words of RouterArgs::route_tag formed by one wave from x and the router's
+// rows: the router's own operations, so the same bits.
+template <typename T, int NCH, bool FULL>
+__device__ __forceinline__ uint32_t route_self(const RouterArgs& ra, const float (&xv)[NCH][Vec<T>::N], int lane) {
+  const int n = ra.n, nch = ra.D / Vec<T>::N;
+  float zv[2] = {0.f, 0.f};
+  int slt[2], isel, slot;
+#pragma unroll 1
+  for (int row = 0; row < n; ++row) {
+    uint4 w[NCH];
+    load_chunks<NCH, FULL>(reinterpret_cast<const T*>(ra.Wr) + static_cast<size_t>(row) * ra.D, lane, nch, w);
+    const float z = row_dot<T, NCH>(w, xv);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) zv[q] = row == lane + 64 * q ? z : zv[q];
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) slt[q] = ra.slot_tab[min(lane + 64 * q, n - 1)];
+  const float gk = select_wave<2>(zv, slt, n, ra.K, lane, &isel, &slot);
+  return route_word(slot, gk, lane);
+}
+
+// Wave 0 of a workgroup polls for the routing, or else calls self() for the
+// words; the other waves get them through LDS.
+template <typename F>
+__device__ __forceinline__ uint32_t route_words(const RouterArgs& ra, int bid, int lane, int wave, F&& self) {
   __shared__ uint32_t s_route[kRouteWords];
-  if (wave == 0) s_route[lane] = poll_route(ra.route_tag + (bid % kRouteCopies) * kRouteWords, ra.K, lane, ra.seq);
+  if (wave == 0) {
+    uint32_t w;
+    if (!poll_route(ra.route_tag + (bid % kRouteCopies) * kRouteWords, ra.K, lane, ra.seq, ra.route_polls, &w)) w = self();
+    s_route[lane] = w;
+  }
   __syncthreads();
   return s_route[lane];
 }
@@ -1252,7 +1305,7 @@ __device__ __forceinline__ void ffn_slices_body(const FfnArgs& a, const RouterAr
   Items<ROUTED> items;
   if constexpr (ROUTED) {
     route_x<T, NCH, FULL>(*ra, lane, nch, xv);
-    items.words = route_words(*ra, bid, lane, wave);
+    items.words = route_words(*ra, bid, lane, wave, [&]() { return route_self<T, NCH, FULL>(*ra, xv, lane); });
   } else {
     load_row_f32<T, NCH, FULL>(a.x, lane, nch, xv);
   }
@@ -1348,8 +1401,12 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
 // The FFN's workgroups are already resident and hold x when the routing
 // appears, and the router's stores to the host leave the critical path; as a
 // launch of its own the FFN started only after those stores, a launch's
-// latency and a load of x.  They wait only for workgroups of lower index,
-// which are dispatched before them.  Qwen-shaped: router 6.5 + FFN 14.8 us ->
+// latency and a load of x.  The wait is a hint, never a dependence: these grids
+// exceed what is resident at once and each XCD dispatches on its own, so two
+// launches on two streams could hold each other's routers off the device.  A
+// workgroup whose first wave does not see the routing within ra.route_polls polls (some 5
+// are usual) forms it from the router's rows itself, with the same bits, and
+// no workgroup's end waits for another's start.  Qwen-shaped: router 6.5 + FFN 14.8 us ->
 // 19.1 in one launch, the layer 24.2 -> 22.1; 4-bit 6.5 + 9.8 -> 13.8, the
 // layer 18.0 -> 16.9; 1,024 units of 256 fp32 columns 5.1 + 3.8 -> 6.0.  The
 // same for a batch (selection and FFN in one launch, every workgroup waiting
@@ -1641,7 +1698,12 @@ __device__ __forceinline__ void ffn_q4_body(const FfnArgs& a, const RouterArgs* 
     if ((tid & 3) == 0) s_eb[bq] = ldexpf(1.f, e - 18);
   }
   if constexpr (ROUTED) {
-    items.words = route_words(*ra, bid, lane, wave);  // its barrier also publishes the digit words
+    items.words = route_words(*ra, bid, lane, wave, [&]() {  // its barrier also publishes the digit words
+      constexpr int NCH = 4 * NQ;
+      float xv[NCH][8];
+      route_x<uint16_t, NCH, FULLQ>(*ra, lane, D / 8, xv);
+      return route_self<uint16_t, NCH, FULLQ>(*ra, xv, lane);
+    });
     q4_pass_loads<NQ, FULLQ, UPP>(a, items, ub0, ustride, u1, lane, cg, cu, cd, sg, su, sd, gate);
     __builtin_amdgcn_sched_barrier(0);
   } else {

@@ -146,6 +146,7 @@ struct spp_ctx {
   int64_t clock = 0;
   int ffn_wgs = 512;  // about this many workgroups share one batch-1 FFN launch (bf16/fp32 experts)
   // test hooks
+  uint32_t route_polls = spp::kRoutePolls;
   bool poison = false;
   int32_t copy_delay_us = 0;
   bool tier_serial = false;  // storage emulation: every expert read through the copy streams' one queue
@@ -1114,10 +1115,12 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   // apart: its events stand between the two)
   if (fl.routed && !batched_ffn(c, B) && !c->timing) {
     ra.route_tag = c->ztag + c->off_route_tag;
+    ra.route_polls = c->route_polls;
     spp::FfnArgs fa{};
     const int grid = build_ffn(c, ls, nullptr, false, &fa);
     if (spp::layer_launch_ok(ra, fa, dt)) {
       SPP_HIP(spp::launch_layer(ra, fa, grid, dt, c->compute));
+      c->stats.layer_launches += 1;
       fl.t_router = std::chrono::steady_clock::now();
       return combine_token(c, fl, grid);
     }
@@ -1872,6 +1875,13 @@ spp_status spp_probe_stream_read(spp_ctx* c, int32_t reps, double* us_out, doubl
 spp_status spp_debug_set_poison(spp_ctx* c, int32_t enabled) {
   if (spp_status s = check_ctx(c)) return s;
   c->poison = enabled != 0;
+  return SPP_OK;
+}
+
+spp_status spp_debug_set_route_polls(spp_ctx* c, int32_t polls) {
+  if (spp_status s = check_ctx(c)) return s;
+  if (polls < -1) return fail(SPP_EINVAL, "polls must be >= -1");
+  c->route_polls = polls < 0 ? spp::kRoutePolls : static_cast<uint32_t>(polls);
   return SPP_OK;
 }
 

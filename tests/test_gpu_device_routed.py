@@ -67,6 +67,94 @@ def test_device_and_host_routed_layers_give_the_same_bits(cfg):
         full.close()
 
 
+ONE_LAUNCH = [
+    BASE.with_(r=16, n_shared=1),
+    BASE.with_(r=16, n=100, K=6, has_proj=True),
+    BASE.with_(D=256, I=96, r=8, codec="q4"),
+    BASE.with_(D=4096, I=33, r=64, n=16, K=2, codec="q4", n_shared=2, has_proj=True),
+    BASE.with_(D=2056, I=61, r=64, n=128, K=8),
+    BASE.with_(D=4096, I=5, r=8, n=9, K=1),
+    BASE.with_(D=1300, I=37, r=8, dtype="f32", K=3, n_shared=1),
+]
+
+
+@pytest.mark.parametrize("cfg", ONE_LAUNCH, ids=["n40", "n100_proj", "q4", "q4_long_proj", "long_ragged", "k1", "f32"])
+def test_ffn_workgroups_that_do_not_see_the_routing_form_it(cfg):
+    """A launch's FFN workgroups must not depend on its router's being on the device: with no polls every one of them
+    forms the routing itself, and with one poll some do.  Same bits."""
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    st = OffloadedMoEStack(cfg, S=cfg.n)
+    h0 = gen.hidden_states(cfg, tokens=4)
+    runs = []
+    one = sum(1 for l in range(cfg.L) if cfg.dtype == "bf16" or l == cfg.L - 1)  # fp32 adapters take two launches
+    try:
+        for polls in (-1, 0, 1):
+            print(f"[route polls] {cfg.D} {cfg.codec} {cfg.dtype} polls={polls}", flush=True)
+            spp.spp_debug_set_route_polls(st.ctx, polls)
+            spp.spp_reset_run_stats(st.ctx)
+            st.reset()
+            runs.append([])
+            for t in range(4):
+                out = st.decode_step_from(_in(st, h0[t]), 0)
+                runs[-1] += [a for l in out for a in l[:2]] + [st.download(st.hbuf[0])]
+            assert spp.spp_get_run_stats(st.ctx).layer_launches == 4 * one
+    finally:
+        st.close()
+    for other in runs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(runs[0], other))
+
+
+def test_two_contexts_decode_on_two_streams():
+    """Two contexts that fill the device from two threads, each on a stream of its own: what each gives alone."""
+    import threading
+
+    import torch
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    cfg = w.MoEConfig(name="two_streams", L=6, D=1280, n=64, K=6, I=896, r=32, S=64, windows=(1,), tokens=24, n_shared=2,
+                      expert_layers=1, seed=53)
+    h0 = gen.hidden_states(cfg, tokens=cfg.tokens)
+    torch.cuda.set_device(0)
+    stacks = []
+    for _ in range(2):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            stacks.append(OffloadedMoEStack(cfg))
+    h_in = [[torch.from_numpy(h.reshape(-1).view(np.uint8).copy()).to("cuda:0") for h in h0] for _ in stacks]
+    outs = [[torch.empty_like(h) for h in hs] for hs in h_in]
+    errors = []
+
+    def run(k):
+        try:
+            st = stacks[k]
+            for h, out in zip(h_in[k], outs[k]):
+                spp.spp_decode_step(st.ctx, cfg.L, h.data_ptr(), out.data_ptr(), st.hbuf[1].data_ptr(), 1, cfg.K, 1)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    try:
+        torch.cuda.synchronize()
+        run(0)
+        torch.cuda.synchronize()
+        want = [out.clone() for out in outs[0]]
+        for rep in range(4):
+            print(f"[two streams] pass {rep}", flush=True)
+            for o_ in outs:
+                for out in o_:
+                    out.zero_()
+            torch.cuda.synchronize()
+            threads = [threading.Thread(target=run, args=(k,)) for k in range(2)]
+            for th in threads:
+                th.start()
+            for th in threads:
+                th.join()
+            torch.cuda.synchronize()
+            assert not errors, errors
+            for k in range(2):
+                assert all(torch.equal(a, b) for a, b in zip(outs[k], want)), (rep, k)
+    finally:
+        for st in stacks:
+            st.close()
+
+
 def _in(st, h):
     """A device copy of stored hidden states that outlives the step."""
     st.h_in = st.torch.from_numpy(np.ascontiguousarray(h).reshape(-1).view(np.uint8).copy()).to(st.device)
