@@ -2088,13 +2088,12 @@ __device__ __forceinline__ void grp_load_down(const GroupArgs& a, const uint16_t
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// Non-finite outputs of the three-term products, formed again as one product per
-// unit in unit order: a term of h that is 0 times an infinite weight is a NaN
-// where h times the weight is infinite.  Reached only by a wave that stored such
-// an output (the loop above it keeps the largest magnitude of its outputs, one
-// maximum per value); each lane reads back what it stored itself.
+// NaN outputs of the three-term products, formed again as one product per unit
+// in unit order: a term of h that is 0 times an infinite weight is a NaN where
+// h times the weight is infinite.  Reached only by a wave whose outputs add up to
+// a NaN (one addition per value); each lane reads back what it stored itself.
 template <int W, int TT>
-__device__ __forceinline__ void grp_nonfinite(const GroupArgs& a, const uint16_t* down, int i0, int nu, int m, int split,
+__device__ __forceinline__ void grp_nan_outputs(const GroupArgs& a, const uint16_t* down, int i0, int nu, int m, int split,
                                            int wave, int lane, const uint16_t* s_h, int hrow, const int* s_pair) {
   const int D = a.D;
 #pragma unroll 1
@@ -2108,7 +2107,7 @@ __device__ __forceinline__ void grp_nonfinite(const GroupArgs& a, const uint16_t
       float* dst = a.ypart + (static_cast<size_t>(s_pair[t]) * a.nsplit + split) * D + d0;
       bool bad = false;
 #pragma unroll
-      for (int c = 0; c < 8; ++c) bad = bad || !isfinite(dst[c]);
+      for (int c = 0; c < 8; ++c) bad = bad || isnan(dst[c]);
       if (!bad) continue;
       float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
@@ -2124,7 +2123,7 @@ __device__ __forceinline__ void grp_nonfinite(const GroupArgs& a, const uint16_t
       }
 #pragma unroll
       for (int c = 0; c < 8; ++c)
-        if (!isfinite(dst[c])) dst[c] = y[c];
+        if (isnan(dst[c])) dst[c] = y[c];
     }
   }
 }
@@ -2154,7 +2153,7 @@ __device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* 
     }
   };
   int slab = wave, st = 0;  // of the next multiply
-  uint32_t top = 0;         // largest magnitude stored (bits of a non-negative float)
+  float sum = 0.f;          // of the values stored: a NaN if one of them is
   auto mul = [&](u32x4 (&r)[8]) {
     if (32 * st + 32 > nu)  // nu is a multiple of 16: the upper half of the step is past the range
 #pragma unroll
@@ -2193,7 +2192,7 @@ __device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* 
             reinterpret_cast<f32x4*>(dst)[0] = f32x4{acc[tt][0][j], acc[tt][1][j], acc[tt][2][j], acc[tt][3][j]};
             reinterpret_cast<f32x4*>(dst)[1] = f32x4{acc[tt][4][j], acc[tt][5][j], acc[tt][6][j], acc[tt][7][j]};
 #pragma unroll
-            for (int c = 0; c < 8; ++c) top = max(top, __float_as_uint(acc[tt][c][j]) & 0x7fffffffu);
+            for (int c = 0; c < 8; ++c) sum += acc[tt][c][j];
           }
         }
 #pragma unroll
@@ -2218,7 +2217,7 @@ __device__ __forceinline__ void grp_phase_b(const GroupArgs& a, const uint16_t* 
     }
     if (it + 1 < total) mul(r1);
   }
-  if (__any(top >= 0x7f800000u)) grp_nonfinite<W, TT>(a, down, i0, nu, m, split, wave, lane, s_h, hrow, s_pair);
+  if (__any(isnan(sum))) grp_nan_outputs<W, TT>(a, down, i0, nu, m, split, wave, lane, s_h, hrow, s_pair);
 }
 
 // The group of this workgroup: its blob, its token count m and, in LDS, its
