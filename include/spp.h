@@ -313,11 +313,10 @@ const char* spp_last_error(void);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * adapter_predict computation, s = sum over the B tokens of
  * softmax(B^l A^l x_b), on explicit device weights and without a context.
- * Its scratch (two completion counters, a count of completed launches, one
- * call's tagged hidden units and B * (n + r) floats of adapter hidden units
- * and per-token distributions) is one fixed device array inside
- * the library, 1792 + 4 * SPP_STATIC_SCRATCH_FLOATS bytes (330 KiB), which
- * each device the library runs on holds until the process ends; B * (n + r)
+ * Its scratch (two completion counters, the tickets and tagged hidden units
+ * of one-token calls and B * (n + r) floats of adapter hidden units and
+ * per-token distributions) is one fixed device array inside the library,
+ * 4352 + 4 * SPP_STATIC_SCRATCH_FLOATS bytes (324.25 KiB), which each device the library runs on holds until the process ends; B * (n + r)
  * may not exceed SPP_STATIC_SCRATCH_FLOATS (e.g. 64 tokens with n 1024 and
  * r 256).  Allocates nothing: no hipMalloc or hipFree, no host waits.
  * adapter_a: dev [r, D], adapter_b: dev [n, r], in dtype (SPP_DTYPE_F32 or
@@ -329,9 +328,9 @@ const char* spp_last_error(void);
  * without waiting; s_out_dev is complete when the stream reaches that point.
  * Every call on a device shares that device's scratch, which keeps the last
  * call's contents (each call clears the counters, or tags its values with a
- * count that no earlier call used):
- * calls that overlap on one device race, so a caller keeps them on one
- * stream.  Errors: EINVAL (NULL or misaligned pointer, bad shape, B * (n + r)
+ * number that the calls before it did not use): calls that overlap on one
+ * device race, so a caller keeps them on one stream; a call that follows such
+ * a race is not affected by it.  Errors: EINVAL (NULL or misaligned pointer, bad shape, B * (n + r)
  * above the limit; nothing enqueued), EHIP. */
 spp_status adapter_predict_static(const void* adapter_a, const void* adapter_b, int32_t dtype, int32_t D,
                                   int32_t n, int32_t r, const float* x_dev, int32_t B, float* s_out_dev,
@@ -495,10 +494,11 @@ spp_status spp_set_tier_delay(spp_ctx* ctx, int32_t delay_us);
 spp_status spp_debug_set_poison(spp_ctx* ctx, int32_t enabled);
 spp_status spp_debug_set_copy_delay(spp_ctx* ctx, int32_t delay_us);
 
-/* Test hook for layer calls whose router and FFN share a launch: the polls
- * after which an FFN workgroup that has not seen the routing forms it itself
- * (0: at once; -1: the default).  Outputs are unchanged.  EINVAL below -1. */
-spp_status spp_debug_set_route_polls(spp_ctx* ctx, int32_t polls);
+/* Test hook for the waits between workgroups of a one-token launch: the polls
+ * after which an FFN workgroup that has not seen the routing forms it itself,
+ * and the adapter's tail the hidden units where no FFN shares its launch (0:
+ * at once; -1: the default).  Outputs are unchanged.  EINVAL below -1. */
+spp_status spp_debug_set_self_polls(spp_ctx* ctx, int32_t polls);
 
 /* ------------------------------------- host replacement policy (no device) */
 

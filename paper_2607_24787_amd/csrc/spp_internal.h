@@ -23,8 +23,8 @@ constexpr int kMaxExpertsTopK = 1024;
 constexpr int kRouteWords = 64;
 constexpr int kRouteCopies = 8;
 // Polls (about a microsecond each) after which such a workgroup forms the
-// routing itself.
-constexpr unsigned kRoutePolls = 256;
+// routing itself, and the adapter's tail of a launch of its own the hidden units.
+constexpr unsigned kSelfPolls = 256;
 
 // Router + adapter (one launch).  Rows [0, n) are router logits (if
 // router_on), rows [n, n+r) adapter hidden units (if A != nullptr).
@@ -38,10 +38,12 @@ struct RouterArgs {
   uint16_t* xh;         // [B, D] the same as bf16 pairs x = xh + xl (nullptr: skip)
   uint16_t* xl;
   float* zbuf;          // [B, n + r] logits then adapter hidden units
-  uint64_t* ztag;       // [n + r] the same values tagged (seq << 32) | fp32 bits, for the batch-1
+  uint64_t* ztag;       // [n] the router's values tagged (seq << 32) | fp32 bits, for the batch-1
                         // single-wave tails (polled instead of a completion counter), or nullptr
+  uint64_t* atag;       // [r] the adapter's, with ztag
   uint64_t* route_tag;  // [kRouteCopies, kRouteWords], or nullptr (no FFN in this launch)
-  unsigned route_polls; // with route_tag: polls before an FFN workgroup forms the routing itself
+  unsigned polls;       // with tags: polls before an FFN workgroup forms the routing itself, and the adapter's
+                        // tail of a launch without FFN the hidden units
   int32_t* topk;        // [B, K]
   float* gates;         // [B, K]
   const int32_t* slot_tab;  // [n] slot of each expert, or nullptr (the host decides the slots)
@@ -56,7 +58,8 @@ struct RouterArgs {
   uint64_t* s_rec;      // [n]: priority s_e (fp32 bits)
   unsigned* counter;    // [2] zero between launches (router rows, adapter rows)
   int clear;            // B > 1: the rows launch clears `counter` first
-  unsigned* epoch;      // completed launches, in place of seq (adapter_by_epoch calls with ztag only), or nullptr
+  unsigned* tickets;    // in place of seq (adapter_by_tickets calls): drawn by every workgroup, by launches of
+                        // this many workgroups only; or nullptr
   unsigned seq;         // this launch's sequence number (never 0)
   int B, D, n, K, r;
   float eps;
@@ -135,14 +138,14 @@ struct ProjArgs {
 };
 
 hipError_t launch_router(const RouterArgs& a, int dtype, hipStream_t st);
-// Whether an adapter call hands its rows over by tags (RouterArgs::epoch can
+// Whether an adapter call hands its rows over by tags (RouterArgs::tickets can
 // then stand in for the counters and for seq).
-bool adapter_by_epoch(int n, int r, int B, int dtype);
+bool adapter_by_tickets(int n, int r, int B, int dtype);
 // start/stop (nullable) are stamped with the kernel's own begin/end times.
 hipError_t launch_ffn(const FfnArgs& a, int grid, int dtype, hipStream_t st, hipEvent_t start, hipEvent_t stop);
 // Router and FFN of one token in one launch: the FFN's workgroups take the
 // routing from ra.route_tag as soon as the router's publish it (or form it
-// themselves after ra.route_polls polls), and form x themselves.  layer_launch_ok: whether this router and this FFN can share a
+// themselves after ra.polls polls), and form x themselves.  layer_launch_ok: whether this router and this FFN can share a
 // launch (slots named on the device, single-wave router tails, sweep order).
 bool layer_launch_ok(const RouterArgs& ra, const FfnArgs& fa, int dtype);
 hipError_t launch_layer(const RouterArgs& ra, const FfnArgs& fa, int grid, int dtype, hipStream_t st);

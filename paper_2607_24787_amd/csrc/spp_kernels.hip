@@ -283,10 +283,10 @@ __device__ __forceinline__ void st_tag(uint64_t* p, unsigned seq, float v) {
 constexpr unsigned kPollMax = 1u << 20;
 
 // Lane l's values p[l + 64 q] (q < Q; indices >= cnt are not waited for) once
-// every one carries seq; false if the bound ran out first.
+// every one carries seq; false if `polls` polls did not see that.
 template <int Q>
-__device__ __forceinline__ bool poll_tags(const uint64_t* p, int cnt, int lane, unsigned seq, float* v) {
-  for (unsigned it = 0; it < kPollMax; ++it) {
+__device__ __forceinline__ bool poll_tags(const uint64_t* p, int cnt, int lane, unsigned seq, unsigned polls, float* v) {
+  for (unsigned it = 0; it < polls; ++it) {
     bool ok = true;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -482,6 +482,22 @@ struct BStage {
   }
 };
 
+// One token's x: the router's input, normalised unless it is x already.
+template <typename T, int NCH, bool FULL>
+__device__ __forceinline__ void input_x(const RouterArgs& a, int lane, int nch, float (&xv)[NCH][Vec<T>::N]) {
+  if (a.u) {
+    load_row_f32<T, NCH, FULL>(a.u, lane, nch, xv);
+  } else {
+    load_row_storage<T, NCH, FULL>(reinterpret_cast<const T*>(a.h), lane, nch, xv);
+  }
+  if (a.x_given) return;
+  const float inv = rms_scale<T, NCH>(xv, a.D, a.eps);
+#pragma unroll
+  for (int j = 0; j < NCH; ++j)
+#pragma unroll
+    for (int v = 0; v < Vec<T>::N; ++v) xv[j][v] *= inv;
+}
+
 // A router (or adapter) row times x, summed over the wave.
 template <typename T, int NCH>
 __device__ __forceinline__ float row_dot(const uint4 (&w)[NCH], const float (&xv)[NCH][Vec<T>::N]) {
@@ -578,8 +594,9 @@ __device__ __forceinline__ uint32_t route_word(int slot, float gk, int lane) {
 // than the last-arriver handoff, same outputs).  Without one (a caller with no
 // sequence numbers), the last workgroup through the counter takes it.
 // ---------------------------------------------------------------------------
-// `nblocks` workgroups take part; `bid` is this one's index among them.
-template <typename T, int NCH, bool FULL, int EPL>
+// `nblocks` workgroups take part; `bid` is this one's index among them.  ALONE:
+// no other work shares the launch.
+template <typename T, int NCH, bool FULL, int EPL, bool ALONE>
 __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid, int nblocks) {
   constexpr int V = Vec<T>::N;
   constexpr int kBC = 8;  // 16-byte chunks of one B row in the fast tail (r <= 64 bf16)
@@ -605,10 +622,13 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
   const bool has_row = row < rows;
   const T* wrow = reinterpret_cast<const T*>(adapter_wg ? a.A : a.Wr) + static_cast<size_t>(min(row, rows - 1)) * D;
   const int zcol = adapter_wg ? n + row : row;
-  // a caller without launch numbers (its launches may be replays of a graph):
-  // one past the count of completed launches, which the tail moves on after
-  // every row's tag, so after every read here that is used
-  const unsigned seq = a.epoch ? __hip_atomic_load(a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u : a.seq;
+  // A caller without launch numbers (its launches may be replays of a graph):
+  // every workgroup draws a ticket, and each launch draws nblocks of them, so
+  // launches in order get numbers of their own whatever became of the ones
+  // before -- also after launches that overlapped and mixed their tickets.
+  constexpr unsigned kLaunches = 1u << 20;  // numbers before they repeat (every launch rewrites all its tags)
+  unsigned ticket = 0;
+  if (ALONE && EPL && a.tickets && tid == 0) ticket = atomicInc(a.tickets, nblocks * kLaunches - 1u);
   uint4 w[NCH];
   load_chunks<NCH, FULL>(wrow, lane, has_row ? nch : 0, w);
   const bool staged = na && n * r <= kBStage;
@@ -639,18 +659,7 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
     slt[q] = EPL && !adapter_wg && wave == 0 && a.slot_tab ? a.slot_tab[min(lane + 64 * q, n - 1)] : 0;
 
   float xv[NCH][V];
-  if (a.u) {
-    load_row_f32<T, NCH, FULL>(a.u, lane, nch, xv);
-  } else {
-    load_row_storage<T, NCH, FULL>(reinterpret_cast<const T*>(a.h), lane, nch, xv);
-  }
-  if (!a.x_given) {
-    const float inv = rms_scale<T, NCH>(xv, D, a.eps);
-#pragma unroll
-    for (int j = 0; j < NCH; ++j)
-#pragma unroll
-      for (int v = 0; v < V; ++v) xv[j][v] *= inv;
-  }
+  input_x<T, NCH, FULL>(a, lane, nch, xv);
   // x goes out from the last wave of the last workgroup: never a tail wave,
   // whose first wait would otherwise include these stores
   if (bid == nblocks - 1 && wave == kWaves - 1 && a.x_out) {
@@ -670,11 +679,18 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
       }
     }
   }
+  unsigned seq = a.seq;
+  if (ALONE && EPL && a.tickets) {
+    __shared__ unsigned s_seq;
+    if (tid == 0) s_seq = ticket / static_cast<unsigned>(nblocks) + 1u;
+    __syncthreads();
+    seq = s_seq;
+  }
   if (has_row) {
     const float acc = row_dot<T, NCH>(w, xv);
     if (lane == 0) {
       st_agent(a.zbuf + zcol, acc);
-      if (EPL && a.ztag) st_tag(a.ztag + zcol, seq, acc);
+      if (EPL && a.ztag) st_tag((adapter_wg ? a.atag : a.ztag) + row, seq, acc);
     }
   }
 
@@ -690,8 +706,22 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
     if (a.ztag) {
       if (wave != 0 || bid != (adapter_wg ? nblocks : gr) - 1) return;
       // a poll that runs out leaves this launch's records unwritten: the host reports it
-      if (!(adapter_wg ? poll_tags<1>(a.ztag + n, na, lane, seq, zv) : poll_tags<Q>(a.ztag, n, lane, seq, zv)))
-        return;
+      if (!adapter_wg) {
+        if (!poll_tags<Q>(a.ztag, n, lane, seq, kPollMax, zv)) return;
+      } else {
+        if constexpr (sizeof(T) == 4) return;  // fp32 adapters take the general tail
+        if (!poll_tags<1>(a.atag, na, lane, seq, ALONE ? a.polls : kPollMax, zv)) {
+          if constexpr (!ALONE) return;
+          // rows that are late, or that an overlapping launch numbered: form them here, with the same operations
+          input_x<T, NCH, FULL>(a, lane, nch, xv);
+#pragma unroll 1
+          for (int j = 0; j < na; ++j) {
+            load_chunks<NCH, FULL>(reinterpret_cast<const T*>(a.A) + static_cast<size_t>(j) * D, lane, nch, w);
+            const float z = row_dot<T, NCH>(w, xv);
+            zv[0] = lane == j ? z : zv[0];
+          }
+        }
+      }
     } else {
       wait_own_stores();  // release this wave's value
       __syncthreads();
@@ -728,8 +758,6 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
       }
       return;
     }
-    if constexpr (sizeof(T) == 4) return;  // fp32 adapters take the general tail
-    if (a.epoch && lane == 0) __hip_atomic_store(a.epoch, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // adapter distribution pi_hat = softmax(B a)
     const float av = lane < na ? zv[0] : 0.f;
     float zh[Q];
@@ -811,7 +839,7 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
 
 template <typename T, int NCH, bool FULL, int EPL>
 __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) {
-  router_adapter_body<T, NCH, FULL, EPL>(a, blockIdx.x, gridDim.x);
+  router_adapter_body<T, NCH, FULL, EPL, true>(a, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1217,22 +1245,6 @@ __global__ __launch_bounds__(kFfnThreads) void ffn_units_kernel(FfnArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kSlWaves = 4;
 
-// Input of the FFN from the layer's input: x = the router's normalised row,
-// formed as router_adapter_body forms it (same operations, same bits).
-template <typename T, int NCH, bool FULL>
-__device__ __forceinline__ void route_x(const RouterArgs& ra, int lane, int nch, float (&xv)[NCH][Vec<T>::N]) {
-  if (ra.u) {
-    load_row_f32<T, NCH, FULL>(ra.u, lane, nch, xv);
-  } else {
-    load_row_storage<T, NCH, FULL>(reinterpret_cast<const T*>(ra.h), lane, nch, xv);
-  }
-  const float inv = rms_scale<T, NCH>(xv, ra.D, ra.eps);
-#pragma unroll
-  for (int j = 0; j < NCH; ++j)
-#pragma unroll
-    for (int v = 0; v < Vec<T>::N; ++v) xv[j][v] *= inv;
-}
-
 // The words of RouterArgs::route_tag formed by one wave from x and the router's
 // rows: the router's own operations, so the same bits.
 template <typename T, int NCH, bool FULL>
@@ -1261,7 +1273,7 @@ __device__ __forceinline__ uint32_t route_words(const RouterArgs& ra, int bid, i
   __shared__ uint32_t s_route[kRouteWords];
   if (wave == 0) {
     uint32_t w;
-    if (!poll_route(ra.route_tag + (bid % kRouteCopies) * kRouteWords, ra.K, lane, ra.seq, ra.route_polls, &w)) w = self();
+    if (!poll_route(ra.route_tag + (bid % kRouteCopies) * kRouteWords, ra.K, lane, ra.seq, ra.polls, &w)) w = self();
     s_route[lane] = w;
   }
   __syncthreads();
@@ -1304,7 +1316,7 @@ __device__ __forceinline__ void ffn_slices_body(const FfnArgs& a, const RouterAr
   float xv[NCH][V];
   Items<ROUTED> items;
   if constexpr (ROUTED) {
-    route_x<T, NCH, FULL>(*ra, lane, nch, xv);
+    input_x<T, NCH, FULL>(*ra, lane, nch, xv);
     items.words = route_words(*ra, bid, lane, wave, [&]() { return route_self<T, NCH, FULL>(*ra, xv, lane); });
   } else {
     load_row_f32<T, NCH, FULL>(a.x, lane, nch, xv);
@@ -1404,7 +1416,7 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
 // latency and a load of x.  The wait is a hint, never a dependence: these grids
 // exceed what is resident at once and each XCD dispatches on its own, so two
 // launches on two streams could hold each other's routers off the device.  A
-// workgroup whose first wave does not see the routing within ra.route_polls polls (some 5
+// workgroup whose first wave does not see the routing within ra.polls polls (some 5
 // are usual) forms it from the router's rows itself, with the same bits, and
 // no workgroup's end waits for another's start.  Qwen-shaped: router 6.5 + FFN 14.8 us ->
 // 19.1 in one launch, the layer 24.2 -> 22.1; 4-bit 6.5 + 9.8 -> 13.8, the
@@ -1416,7 +1428,7 @@ __global__ __launch_bounds__(64 * kSlWaves) void layer_slices_kernel(RouterArgs 
   static_assert(kSlWaves == kWaves, "one workgroup size for both parts");
   const int b = blockIdx.x;
   if (b < rb)
-    router_adapter_body<T, NCH, FULL, 2>(ra, b, rb);
+    router_adapter_body<T, NCH, FULL, 2, false>(ra, b, rb);
   else
     ffn_slices_body<T, NCH, FULL, R, DS, true>(fa, &ra, b - rb, static_cast<int>(gridDim.x) - rb);
 }
@@ -1701,7 +1713,7 @@ __device__ __forceinline__ void ffn_q4_body(const FfnArgs& a, const RouterArgs* 
     items.words = route_words(*ra, bid, lane, wave, [&]() {  // its barrier also publishes the digit words
       constexpr int NCH = 4 * NQ;
       float xv[NCH][8];
-      route_x<uint16_t, NCH, FULLQ>(*ra, lane, D / 8, xv);
+      input_x<uint16_t, NCH, FULLQ>(*ra, lane, D / 8, xv);
       return route_self<uint16_t, NCH, FULLQ>(*ra, xv, lane);
     });
     q4_pass_loads<NQ, FULLQ, UPP>(a, items, ub0, ustride, u1, lane, cg, cu, cd, sg, su, sd, gate);
@@ -1817,7 +1829,7 @@ template <int NCH, bool FULL, int NQ, bool FULLQ, int PASSES>
 __global__ __launch_bounds__(kFfnThreads) void layer_q4_kernel(RouterArgs ra, FfnArgs fa, int rb) {
   const int b = blockIdx.x;
   if (b < rb)
-    router_adapter_body<uint16_t, NCH, FULL, 2>(ra, b, rb);
+    router_adapter_body<uint16_t, NCH, FULL, 2, false>(ra, b, rb);
   else
     ffn_q4_body<NQ, FULLQ, 3, PASSES, true>(fa, &ra, b - rb, static_cast<int>(gridDim.x) - rb);
 }
@@ -3069,7 +3081,7 @@ hipError_t proj_t(const ProjArgs& a, hipStream_t st) {
 
 }  // namespace
 
-bool adapter_by_epoch(int n, int r, int B, int dtype) {
+bool adapter_by_tickets(int n, int r, int B, int dtype) {
   RouterArgs a{};
   a.A = &a;  // an adapter is there
   a.n = n;

@@ -146,7 +146,7 @@ struct spp_ctx {
   int64_t clock = 0;
   int ffn_wgs = 512;  // about this many workgroups share one batch-1 FFN launch (bf16/fp32 experts)
   // test hooks
-  uint32_t route_polls = spp::kRoutePolls;
+  uint32_t self_polls = spp::kSelfPolls;
   bool poison = false;
   int32_t copy_delay_us = 0;
   bool tier_serial = false;  // storage emulation: every expert read through the copy streams' one queue
@@ -1093,6 +1093,8 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   ra.xl = c->xl_dev;
   ra.zbuf = c->zbuf;
   ra.ztag = c->ztag;
+  ra.atag = c->ztag + d.n;
+  ra.polls = c->self_polls;
   ra.topk = reinterpret_cast<int32_t*>(c->res_dev);
   ra.gates = reinterpret_cast<float*>(c->res_dev + c->off_gates);
   ra.slot_tab = fl.routed ? ls.slot_tab : nullptr;
@@ -1115,7 +1117,6 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   // apart: its events stand between the two)
   if (fl.routed && !batched_ffn(c, B) && !c->timing) {
     ra.route_tag = c->ztag + c->off_route_tag;
-    ra.route_polls = c->route_polls;
     spp::FfnArgs fa{};
     const int grid = build_ffn(c, ls, nullptr, false, &fa);
     if (spp::layer_launch_ok(ra, fa, dt)) {
@@ -1580,6 +1581,8 @@ spp_status adapter_predict(spp_ctx* c, int32_t l, const float* x_dev, int32_t B,
   ra.Bm = ls.Bm;
   ra.zbuf = c->zbuf;
   ra.ztag = c->ztag;
+  ra.atag = c->ztag + d.n;
+  ra.polls = c->self_polls;
   ra.s = reinterpret_cast<float*>(c->res_dev + c->off_s);
   ra.counter = c->counter;
   ra.B = B;
@@ -1878,10 +1881,10 @@ spp_status spp_debug_set_poison(spp_ctx* c, int32_t enabled) {
   return SPP_OK;
 }
 
-spp_status spp_debug_set_route_polls(spp_ctx* c, int32_t polls) {
+spp_status spp_debug_set_self_polls(spp_ctx* c, int32_t polls) {
   if (spp_status s = check_ctx(c)) return s;
   if (polls < -1) return fail(SPP_EINVAL, "polls must be >= -1");
-  c->route_polls = polls < 0 ? spp::kRoutePolls : static_cast<uint32_t>(polls);
+  c->self_polls = polls < 0 ? spp::kSelfPolls : static_cast<uint32_t>(polls);
   return SPP_OK;
 }
 

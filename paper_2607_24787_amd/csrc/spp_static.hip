@@ -1,9 +1,9 @@
 // adapter_predict_static: the adapter priorities of section "Expert
 // Prediction Adapter" on explicit device weights, for callers that cannot
-// allocate device memory.  Its scratch -- two completion counters, a count of
-// completed launches, the tagged hidden units of a one-token call and the
-// per-token adapter hidden units / distributions -- lives in one file-scope
-// device array of fixed size instead of a context's allocation.  Each device
+// allocate device memory.  Its scratch -- two completion counters, the tickets
+// and tagged hidden units of one-token calls and the per-token adapter hidden
+// units / distributions -- lives in one file-scope device array of fixed size
+// instead of a context's allocation.  Each device
 // the library runs on holds its own copy of the array (at its own address,
 // looked up once per device) until the process ends; every call on a device
 // shares it.
@@ -17,9 +17,12 @@
 
 namespace {
 
-constexpr int kCounterWords = 64;  // 256 bytes; the router kernels use the first two, the third counts launches
-constexpr int kEpochWord = 2;
-constexpr int kTags = 128 + 64;    // one-wave tails: n <= 128 (unused here), r <= 64
+constexpr int kCounterWords = 64;  // 256 bytes; the router kernels use the first two
+// One-wave tails (r = 8, 16, ..., 64): tickets and tags of their own for each
+// r, whose launches all have the same number of workgroups and rewrite all r
+// tags, so that a launch's number differs from every tag it may find.
+constexpr int kTicketWord = 8;     // words kTicketWord + r / 8 - 1
+constexpr int kTags = 8 * 64;      // tags 64 (r / 8 - 1) ...
 constexpr size_t kScratchFloats = SPP_STATIC_SCRATCH_FLOATS;
 
 // [counters: kCounterWords u32][tags: kTags u64][hidden units / distributions: B * (n + r) floats]
@@ -30,10 +33,10 @@ std::mutex g_mu;
 void* g_scratch[kMaxDevices] = {};  // device address of `scratch` on each device, once looked up
 
 // The counters must start at zero.  A one-token call with one-wave tails
-// needs none (its rows are tagged with the launch count), a batch's first
+// needs none (its rows are tagged with the launch's number), a batch's first
 // launch clears them, and for the rest a kernel does (no memset node in a
 // captured graph).  Bound by launches and one round of cold loads: 128 experts,
-// r 64, D 2048, one token 7.9 us (11.1 with the clearing launch in front and
+// r 64, D 2048, one token 8.3 us (11.7 with the clearing launch in front and
 // counters for the hand-over).
 __global__ void clear_counters(unsigned* p, int n) {
   const int i = static_cast<int>(threadIdx.x);
@@ -87,9 +90,11 @@ extern "C" spp_status adapter_predict_static(const void* adapter_a, const void* 
   const hipStream_t st = static_cast<hipStream_t>(hip_stream);
   unsigned* counter = static_cast<unsigned*>(base);
   spp::RouterArgs ra{};
-  if (spp::adapter_by_epoch(n, r, B, dtype)) {
-    ra.ztag = reinterpret_cast<uint64_t*>(counter + kCounterWords);
-    ra.epoch = counter + kEpochWord;
+  if (spp::adapter_by_tickets(n, r, B, dtype)) {
+    ra.ztag = reinterpret_cast<uint64_t*>(counter + kCounterWords);  // no router rows: not written
+    ra.atag = ra.ztag + 64 * (r / 8 - 1);
+    ra.tickets = counter + kTicketWord + r / 8 - 1;
+    ra.polls = spp::kSelfPolls;
   } else if (B > 1) {
     ra.clear = 1;
   } else {

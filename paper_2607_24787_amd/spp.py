@@ -109,7 +109,7 @@ _SIGS = {
     "spp_set_prefetch_parallel": (c_int32, [c_void_p, c_int32]),
     "spp_debug_set_poison": (c_int32, [c_void_p, c_int32]),
     "spp_debug_set_copy_delay": (c_int32, [c_void_p, c_int32]),
-    "spp_debug_set_route_polls": (c_int32, [c_void_p, c_int32]),
+    "spp_debug_set_self_polls": (c_int32, [c_void_p, c_int32]),
     "spp_policy_create": (c_int32, [c_int32, c_int32, POINTER(c_int32), c_int32, POINTER(c_void_p)]),
     "spp_policy_destroy": (c_int32, [c_void_p]),
     "spp_policy_on_demand": (c_int32, [c_void_p, POINTER(c_int32), c_int32, c_int64, POINTER(c_int32),
@@ -430,8 +430,8 @@ def spp_debug_set_copy_delay(ctx, delay_us: int):
     _check(lib().spp_debug_set_copy_delay(c_void_p(ctx), delay_us))
 
 
-def spp_debug_set_route_polls(ctx, polls: int):
-    _check(lib().spp_debug_set_route_polls(c_void_p(ctx), polls))
+def spp_debug_set_self_polls(ctx, polls: int):
+    _check(lib().spp_debug_set_self_polls(c_void_p(ctx), polls))
 
 
 # ------------------------------------------------------- host policy (no GPU)

@@ -80,23 +80,26 @@ ONE_LAUNCH = [
 
 @pytest.mark.parametrize("cfg", ONE_LAUNCH, ids=["n40", "n100_proj", "q4", "q4_long_proj", "long_ragged", "k1", "f32"])
 def test_ffn_workgroups_that_do_not_see_the_routing_form_it(cfg):
-    """A launch's FFN workgroups must not depend on its router's being on the device: with no polls every one of them
-    forms the routing itself, and with one poll some do.  Same bits."""
+    """A launch's FFN workgroups must not depend on its router's being on the device, nor the adapter's tail on its
+    rows': with no polls every one of them forms the routing (the hidden units) itself, and with one poll some do.
+    Same bits."""
     from paper_2607_24787_amd.model import OffloadedMoEStack
     st = OffloadedMoEStack(cfg, S=cfg.n)
     h0 = gen.hidden_states(cfg, tokens=4)
+    x = st.torch.randn(cfg.D, device=st.device, generator=st.torch.Generator(st.device).manual_seed(3))
     runs = []
     one = sum(1 for l in range(cfg.L) if cfg.dtype == "bf16" or l == cfg.L - 1)  # fp32 adapters take two launches
     try:
         for polls in (-1, 0, 1):
             print(f"[route polls] {cfg.D} {cfg.codec} {cfg.dtype} polls={polls}", flush=True)
-            spp.spp_debug_set_route_polls(st.ctx, polls)
+            spp.spp_debug_set_self_polls(st.ctx, polls)
             spp.spp_reset_run_stats(st.ctx)
             st.reset()
             runs.append([])
             for t in range(4):
                 out = st.decode_step_from(_in(st, h0[t]), 0)
                 runs[-1] += [a for l in out for a in l[:2]] + [st.download(st.hbuf[0])]
+                runs[-1].append(spp.adapter_predict(st.ctx, 0, x.data_ptr(), 1, cfg.n))
             assert spp.spp_get_run_stats(st.ctx).layer_launches == 4 * one
     finally:
         st.close()

@@ -107,3 +107,36 @@ def test_static_scratch_replays_of_a_graph(torch_cuda, n, r, D, dtype, B):
         want = torch.softmax(x.double() @ A.double().T @ Bm.double().T, dim=-1).sum(0)
         assert torch.equal(out, eager), t
         assert torch.allclose(out.double(), want, rtol=1e-5, atol=2e-6), t
+
+
+def test_static_scratch_after_calls_that_overlapped(torch_cuda):
+    """Calls that overlap on one device race for the scratch; a call after them, in order, must give its own result.
+    Ordered calls of several ranks in turn, after batches of overlapping ones on two streams."""
+    import torch
+    from paper_2607_24787_amd import spp
+    n, D = 128, 2048
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.empty((64, D), device="cuda").normal_(0, 0.05, generator=g).to(torch.bfloat16)
+    Bm = {r: torch.empty((n, r), device="cuda").normal_(0, 0.5, generator=g).to(torch.bfloat16) for r in (64, 24, 8)}
+    xs = torch.empty((8, D), device="cuda").normal_(generator=g)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    sink = torch.empty((2, n), device="cuda")
+    out = torch.empty(n, device="cuda")
+    torch.cuda.synchronize()
+
+    def call(r, x, dst, stream):
+        spp.adapter_predict_static(A.data_ptr(), Bm[r].data_ptr(), spp.DTYPE_BF16, D, n, r, x.data_ptr(), 1,
+                                   dst.data_ptr(), stream.cuda_stream)
+
+    for t in range(12):
+        _log(f"[static overlap] round {t}")
+        for k in range(20):
+            call((64, 24)[(k + t) % 2 if t % 3 else 0], xs[k % 8], sink[k % 2], streams[k % 2])
+        torch.cuda.synchronize()
+        for r in (64, 24, 8, 64):
+            x = xs[(t + r) % 8]
+            out.fill_(float("nan"))
+            call(r, x, out, torch.cuda.current_stream())
+            torch.cuda.synchronize()
+            want = torch.softmax(x.double() @ A[:r].double().T @ Bm[r].double().T, dim=-1)
+            assert torch.allclose(out.double(), want, rtol=1e-5, atol=2e-6), (t, r)
