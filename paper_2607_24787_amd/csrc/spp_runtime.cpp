@@ -1664,11 +1664,14 @@ spp_status spp_decode_step(spp_ctx* c, const void* h_in_dev, void* h_out_dev, vo
       if (spp_status s = begin(l, &cur)) return s;
     }
     ahead = cur.routed && l + 1 < L && c->timing_level < 2 && device_routable(c, c->layers[l + 1], B);
+    spp_status refused = SPP_OK;  // of layer l + 1: layer l still runs to its end
+    std::string why;
     if (ahead) {
       next = Flight{};
-      if (spp_status s = begin(l + 1, &next)) {
-        layer_drop(c, cur);
-        return s;
+      refused = begin(l + 1, &next);
+      if (refused) {
+        ahead = false;
+        why = g_err;
       }
     }
     if (spp_status s = layer_finish(c, cur, topk_out ? topk_out + l * BK : nullptr,
@@ -1676,6 +1679,7 @@ spp_status spp_decode_step(spp_ctx* c, const void* h_in_dev, void* h_out_dev, vo
       if (ahead) layer_drop(c, next);
       return s;
     }
+    if (refused) return fail(refused, why);
     if (ahead) cur = std::move(next);
   }
   return SPP_OK;
