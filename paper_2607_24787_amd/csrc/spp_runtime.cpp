@@ -502,6 +502,16 @@ spp_status sync_all(spp_ctx* c) {
 }
 
 
+// The device copy of a layer's slot table, for launches that name the slots
+// themselves.  Enqueued where the table is set, so that the first call after it
+// need not; a layer that gets its last expert by a load leaves it to its call.
+spp_status upload_slot_table(spp_ctx* c, LayerState& ls) {
+  if (ls.slot_tab_version == ls.policy->version()) return SPP_OK;
+  SPP_HIP(spp::launch_set_table(ls.slot_tab, ls.policy->expert_slots().data(), c->d.n, c->compute));
+  ls.slot_tab_version = ls.policy->version();
+  return SPP_OK;
+}
+
 // Synchronous fill of slots from the host store according to the policy table.
 spp_status fill_slots(spp_ctx* c, LayerState& ls, const std::vector<int32_t>& before) {
   const auto& table = ls.policy->slot_experts();
@@ -513,7 +523,7 @@ spp_status fill_slots(spp_ctx* c, LayerState& ls, const std::vector<int32_t>& be
                       ls.host_store + static_cast<size_t>(table[j]) * c->stride, c->blob_bytes,
                       hipMemcpyHostToDevice));
   }
-  return SPP_OK;
+  return ls.policy->all_available() ? upload_slot_table(c, ls) : SPP_OK;
 }
 
 void free_ctx(spp_ctx* c) {
@@ -1061,10 +1071,8 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   fl.predict = fl.adapter_on || (fl.naive && l < d.L - 1 && M_max >= 0);
   if (fl.predict && M_max > 0 && !c->layers[l + 1].bound) return fail(SPP_ESTATE, "next layer not bound");
   fl.routed = device_routable(c, ls, B);
-  if (fl.routed && ls.slot_tab_version != ls.policy->version()) {
-    SPP_HIP(spp::launch_set_table(ls.slot_tab, ls.policy->expert_slots().data(), d.n, c->compute));
-    ls.slot_tab_version = ls.policy->version();
-  }
+  if (fl.routed)
+    if (spp_status s = upload_slot_table(c, ls)) return s;
   fl.tau = ++c->clock;
   const int dt = d.dtype;
   TimingSet& ts = fl.ts;
