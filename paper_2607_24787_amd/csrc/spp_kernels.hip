@@ -2385,11 +2385,23 @@ __global__ __launch_bounds__(64 * W, 2) void ffn_grouped_kernel(GroupArgs a) {
 // ffn_slices_kernel a wave holds the gate and up rows of its own R units and
 // its D-slice of all the down columns:
 //   1. per token, h of the wave's units into LDS (the next token's x loads
-//      beside it); one barrier;
+//      beside it, see batch_x_ahead); one barrier;
 //   2. per token, the wave's slice of sum_u h_u down_u to the partial row.
-// A launch per token read every expert once per token and paid two launches
+// A launch per token reads every expert once per token and pays two launches
 // each: 6 fp32 tokens over 32 experts (D 1024, I 704) took 6 x (8.0 + 4.1) us.
+// A few tokens that share hardly an expert take it all the same, see
+// token_launches.
 // ---------------------------------------------------------------------------
+// Whether a second row of x fits beside the weights.  Rows of 7 or 8 chunks (8
+// in fp32) then need more than 256 registers, one workgroup per compute unit
+// instead of two: 6 tokens over 32 experts of 705 units of 3,104 columns, 4 per
+// token, 121.6 us the layer with it, 92.8 without; 64 tokens 636 and 482; 16
+// tokens over 704 units of 2,048 fp32 columns 150.9 and 129.1.
+template <typename T>
+constexpr bool batch_x_ahead(int nch) {
+  return nch <= (sizeof(T) == 2 ? 6 : 7);
+}
+
 template <typename T, int NCH, bool FULL, int R, int DS>
 __global__ __launch_bounds__(64 * kSlWaves) void ffn_units_batch_kernel(GroupArgs a) {
   constexpr int V = Vec<T>::N;
@@ -2433,9 +2445,13 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_units_batch_kernel(GroupArg
       }
     }
   }
+  constexpr bool kAhead = batch_x_ahead<T>(NCH);
   for (int t = 0; t < m; ++t) {
     float xn[NCH][V];
-    load_row_f32<T, NCH, FULL>(xrow(min(t + 1, m - 1)), lane, nch, xn);
+    if constexpr (kAhead)
+      load_row_f32<T, NCH, FULL>(xrow(min(t + 1, m - 1)), lane, nch, xn);
+    else if (t > 0)
+      load_row_f32<T, NCH, FULL>(xrow(t), lane, nch, xv);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -2455,10 +2471,11 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_units_batch_kernel(GroupArg
       const float uv = wave_sum(us);
       if (lane == 0) s_h[t][r * W + wave] = gv / (1.f + expf(-gv)) * uv;
     }
+    if constexpr (kAhead)
 #pragma unroll
-    for (int j = 0; j < NCH; ++j)
+      for (int j = 0; j < NCH; ++j)
 #pragma unroll
-      for (int v = 0; v < V; ++v) xv[j][v] = xn[j][v];
+        for (int v = 0; v < V; ++v) xv[j][v] = xn[j][v];
   }
   __syncthreads();
   for (int t = 0; t < m; ++t) {
@@ -3024,7 +3041,7 @@ constexpr int slices_rounds(int nch) {
 }
 
 // Units per wave of ffn_units_batch_kernel: as many as stay in 256 registers
-// beside two rows of x (bf16 rows hold twice the columns per chunk).
+// beside two rows of x (one where batch_x_ahead says so).
 template <typename T>
 constexpr int batch_rounds(int nch) {
   return sizeof(T) == 2 ? (nch <= 3 ? 3 : nch == 4 ? 2 : 1) : (nch <= 4 ? 3 : 2);
