@@ -231,6 +231,35 @@ size_t expert_bytes(const spp_model_desc& d) {
   return static_cast<size_t>(3) * d.I * d.D * (d.dtype == SPP_DTYPE_BF16 ? 2 : 4);
 }
 
+// Unit layout: whether the FFN of B tokens goes out as a launch per token, which
+// reads an expert once per token, or as one batched launch, which reads it once
+// but spends about 6 us of every workgroup's life on finding its group.  The
+// cheaper of two estimates (us).  Per token: two launches' latency and its
+// experts' bytes at the batch-1 kernel's rate; batched: rounds of workgroups,
+// each 6 us and the weights of the workgroups beside it at a compute unit's
+// rate.  Over 302 shapes of 2 to 8 tokens (D 256 to 4,096, 16 to 128 experts),
+// resident and decided on the host, the choice costs up to 17% over the better
+// one where it errs (5% or more on 14).  64 experts of 1,601 units of 2,064
+// columns, 8 per token: 2 tokens 92.8 us the layer per token, 144 batched, 4
+// tokens 174 and 216; 32 experts of 705 units of 528 columns, 4 per token: 2
+// tokens 24.9 batched, 26.3 per token.  A function of the shape and the batch
+// alone, so that a layer gives the same bits whichever of its experts are
+// resident.
+bool token_launches(const spp_model_desc& d, int32_t B, int num_cu) {
+  if (B == 1) return true;
+  if (B > 8) return false;
+  const bool bf16 = d.dtype == SPP_DTYPE_BF16;
+  const double row = static_cast<double>(d.D) * (bf16 ? 2 : 4) / 1e6;  // MB
+  const double per_token = B * (7.0 + (d.K + d.n_shared) * 3.0 * d.I * row / (bf16 ? 4.4 : 5.7));
+  const double distinct = d.n * (1.0 - std::pow(1.0 - static_cast<double>(d.K) / d.n, B)) + d.n_shared;
+  int nsplit = 0, upw = 0;
+  spp::batch_units_split(d.I, d.D, d.dtype, &nsplit, &upw);
+  const int chunks = (d.D * (bf16 ? 2 : 4) + 1023) / 1024;
+  const double wgs_per_cu = bf16 ? (chunks == 1 ? 4 : 2) : std::max(2, 6 - chunks);  // by the kernel's registers
+  const double batched = 12.0 + distinct * nsplit / (num_cu * wgs_per_cu) * (6.0 + wgs_per_cu * 3e3 * upw * row / 25.0);
+  return per_token < batched;
+}
+
 bool desc_ok(const spp_model_desc* d, std::string* why) {
   if (!d) return *why = "desc is NULL", false;
   if (d->dtype != SPP_DTYPE_F32 && d->dtype != SPP_DTYPE_BF16) return *why = "dtype must be 0 (f32) or 1 (bf16)", false;
@@ -953,8 +982,8 @@ spp_status grouped_ffn(spp_ctx* c, LayerState& ls, int32_t B, const void* h_in, 
 }
 
 // The batched kernels read the tiled layout at any batch, the unit layout
-// above one token.
-bool batched_ffn(const spp_ctx* c, int32_t B) { return c->grouped || B > 1; }
+// where token_launches does not say otherwise.
+bool batched_ffn(const spp_ctx* c, int32_t B) { return c->grouped || !token_launches(c->d, B, c->num_cu); }
 
 // A layer call between its launches and its host side.
 struct Flight {
@@ -989,21 +1018,21 @@ bool device_routable(spp_ctx* c, LayerState& ls, int32_t B) {
   return true;
 }
 
-// The batch-1 FFN's work list: routed experts in T order, then the shared
-// ones.  T: the routing on the host, or nullptr (the device copy).
-int build_ffn(spp_ctx* c, const LayerState& ls, const int32_t* T, bool split_ok, spp::FfnArgs* fa) {
+// Token b's FFN work list: routed experts in T order, then the shared ones.
+// T: the routing on the host, or nullptr (the device copy).
+int build_ffn(spp_ctx* c, const LayerState& ls, const int32_t* T, int32_t b, bool split_ok, spp::FfnArgs* fa) {
   const spp_model_desc& d = c->d;
   *fa = spp::FfnArgs{};
   int nW = 0;
   if (!T) {
-    fa->sel = reinterpret_cast<const int32_t*>(c->res_dev + c->off_sel);
+    fa->sel = reinterpret_cast<const int32_t*>(c->res_dev + c->off_sel) + b * d.K;
     fa->nsel = d.K;
     fa->slots = ls.slots;
     fa->stride = c->stride;
   }
   for (int32_t k = 0; k < d.K; ++k) {
-    if (T) fa->blob[nW] = ls.slots + static_cast<size_t>(ls.policy->slot_of(T[k])) * c->stride;
-    fa->gate_idx[nW] = k;
+    if (T) fa->blob[nW] = ls.slots + static_cast<size_t>(ls.policy->slot_of(T[b * d.K + k])) * c->stride;
+    fa->gate_idx[nW] = b * d.K + k;
     ++nW;
   }
   for (int32_t j = 0; j < d.n_shared; ++j) {
@@ -1015,7 +1044,7 @@ int build_ffn(spp_ctx* c, const LayerState& ls, const int32_t* T, bool split_ok,
   fa->I = d.I;
   fa->D = d.D;
   fa->codec = d.expert_codec;
-  fa->x = c->x_dev;
+  fa->x = c->x_dev + static_cast<size_t>(b) * d.D;
   fa->gates = reinterpret_cast<const float*>(c->res_dev + c->off_gates);
   fa->partial = c->partial;
   // sweep order, except under the FFN split, whose two launches need every
@@ -1034,15 +1063,16 @@ int build_ffn(spp_ctx* c, const LayerState& ls, const int32_t* T, bool split_ok,
   return spp::ffn_grid_for(nW * d.I, c->ffn_wgs, &fa->upw);
 }
 
-// The batch-1 combine of `grid` partial rows.
-spp_status combine_token(spp_ctx* c, const Flight& fl, int grid) {
+// The combine of token b's `grid` partial rows.
+spp_status combine_token(spp_ctx* c, const Flight& fl, int32_t b, int grid) {
+  const size_t row = static_cast<size_t>(b) * c->d.D;
   spp::CombineArgs ca{};
   ca.partial = c->partial;
   ca.nparts = grid;
   ca.D = c->d.D;
-  ca.res_h = fl.h_in;
-  ca.res_u = c->d.has_proj ? c->u_dev : nullptr;
-  ca.out = fl.h_out;
+  ca.res_h = static_cast<const uint8_t*>(fl.h_in) + row * c->elem;
+  ca.res_u = c->d.has_proj ? c->u_dev + row : nullptr;
+  ca.out = static_cast<uint8_t*>(fl.h_out) + row * c->elem;
   SPP_HIP(spp::launch_combine(ca, c->d.dtype, c->compute));
   c->stats.ffn_launches += 1;
   return SPP_OK;
@@ -1123,15 +1153,15 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   ra.seq = fl.seq;
   // router and FFN in one launch where both kernels can (timing keeps them
   // apart: its events stand between the two)
-  if (fl.routed && !batched_ffn(c, B) && !c->timing) {
+  if (fl.routed && B == 1 && !c->grouped && !c->timing) {
     ra.route_tag = c->ztag + c->off_route_tag;
     spp::FfnArgs fa{};
-    const int grid = build_ffn(c, ls, nullptr, false, &fa);
+    const int grid = build_ffn(c, ls, nullptr, 0, false, &fa);
     if (spp::layer_launch_ok(ra, fa, dt)) {
       SPP_HIP(spp::launch_layer(ra, fa, grid, dt, c->compute));
       c->stats.layer_launches += 1;
       fl.t_router = std::chrono::steady_clock::now();
-      return combine_token(c, fl, grid);
+      return combine_token(c, fl, 0, grid);
     }
     ra.route_tag = nullptr;
   }
@@ -1146,12 +1176,13 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
     for (int k : {kEvWaitA, kEvLoaded, kEvWaitB}) SPP_HIP(hipEventRecord(ts.ev[k], c->compute));
   if (batched_ffn(c, B)) {
     if (spp_status e = launch_batch(c, ls, B, ls.slot_tab, d.n, h_in, h_out, ts)) return e;
-  } else {
+  }
+  for (int32_t b = 0; b < B && !batched_ffn(c, B); ++b) {
     spp::FfnArgs fa{};
-    const int grid = build_ffn(c, ls, nullptr, false, &fa);
-    SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, c->timing ? ts.ev[kEvFfnBegin] : nullptr,
-                            c->timing ? ts.ev[kEvFfnEnd] : nullptr));
-    if (spp_status e = combine_token(c, fl, grid)) return e;
+    const int grid = build_ffn(c, ls, nullptr, b, false, &fa);
+    SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, c->timing && b == 0 ? ts.ev[kEvFfnBegin] : nullptr,
+                            c->timing && b + 1 == B ? ts.ev[kEvFfnEnd] : nullptr));
+    if (spp_status e = combine_token(c, fl, b, grid)) return e;
   }
   // no last_read event: while every expert holds a slot nothing is copied
   // into one, and a change of the table waits for the stream
@@ -1268,7 +1299,7 @@ spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_o
     uint32_t late = 0, all_items = 0;
     bool split = false;
     if (split_ok) {
-      grid0 = build_ffn(c, ls, T, true, &fa0);
+      grid0 = build_ffn(c, ls, T, 0, true, &fa0);
       all_items = fa0.nW >= 32 ? 0xFFFFFFFFu : ((1u << fa0.nW) - 1u);
       if (d.I % fa0.upw == 0) {
         for (int32_t k = 0; k < d.K; ++k) {
@@ -1298,16 +1329,16 @@ spp_status layer_finish(spp_ctx* c, Flight& fl, int32_t* topk_out, float* gate_o
     if (batched) {
       if (spp_status e = grouped_ffn(c, ls, B, h_in, h_out, rounds, c->last_loads, &st, ts)) return e;
     }
-    if (!batched) {
+    for (int32_t b = 0; b < B && !batched; ++b) {
       spp::FfnArgs fa{};
-      const int grid = split_ok ? grid0 : build_ffn(c, ls, T, false, &fa);
+      const int grid = split_ok ? grid0 : build_ffn(c, ls, T, b, false, &fa);
       if (split_ok) fa = fa0;
       if (split) fa.skip_mask = all_items & ~late;
-      SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, c->timing ? ts.ev[kEvFfnBegin] : nullptr,
-                              c->timing ? ts.ev[kEvFfnEnd] : nullptr));
-      t_ffn = std::chrono::steady_clock::now();
+      SPP_HIP(spp::launch_ffn(fa, grid, dt, c->compute, c->timing && b == 0 ? ts.ev[kEvFfnBegin] : nullptr,
+                              c->timing && b + 1 == B ? ts.ev[kEvFfnEnd] : nullptr));
+      if (b == 0) t_ffn = std::chrono::steady_clock::now();
       if (split && hipEventQuery(c->hits_done) != hipSuccess) SPP_HIP(hipStreamWaitEvent(c->compute, c->hits_done, 0));
-      if (spp_status e = combine_token(c, fl, grid)) return e;
+      if (spp_status e = combine_token(c, fl, b, grid)) return e;
     }
     SPP_HIP(hipEventRecord(ls.last_read, c->compute));
     ls.last_read_valid = true;

@@ -218,6 +218,42 @@ def test_batched_selection_without_an_adapter(cfg):
     assert len(rep.exempt) <= 1
 
 
+@pytest.mark.parametrize("cfg,per_token", [
+    (GROUPED.with_(D=2064, n=24, K=8, I=200, batch=2, n_shared=1, S=20), True),
+    (GROUPED.with_(D=2064, n=48, K=8, I=400, batch=3, n_shared=0, S=30), True),
+    (GROUPED.with_(D=1040, n=24, K=8, I=400, batch=2, n_shared=0, S=20, dtype="f32", has_proj=True), True),
+    (GROUPED.with_(D=528, n=24, K=4, I=70, batch=2, n_shared=0, S=20), False),
+    (GROUPED.with_(D=3104, n=24, K=3, I=41, batch=5, n_shared=0, S=20), False),   # one row of x at a time
+    (GROUPED.with_(D=2048, n=24, K=3, I=41, batch=7, n_shared=1, S=23, dtype="f32"), False),
+], ids=["b2", "b3", "f32_b2", "batched_b2", "batched_long", "batched_f32_long"])
+def test_few_tokens_in_the_unit_layout(cfg, per_token):
+    """A launch per token or one for the batch: both against the oracle, with the same bits whether the layers are
+    resident, decided on the host or timed."""
+    from lockstep import run_lockstep
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    h0 = gen.hidden_states(cfg, tokens=cfg.tokens)
+    outs = []
+    for S in (cfg.n, cfg.S):
+        st = OffloadedMoEStack(cfg, S=S)
+        try:
+            rep = run_lockstep(st, cfg, cfg.tokens, 1)
+            assert rep.max_ulp_h <= 1.0 + 1e-9 and rep.max_err_g <= 1e-5 and len(rep.exempt) <= 1
+            for timing in (0, 1):
+                st.reset()
+                spp.spp_set_timing(st.ctx, timing)
+                spp.spp_reset_run_stats(st.ctx)
+                for t in range(cfg.tokens):
+                    st.decode_step_from(_in(st, h0[t]), 1)
+                    outs.append(st.download(st.hbuf[0]))
+                stats = spp.spp_get_run_stats(st.ctx)
+                assert stats.ffn_launches == cfg.tokens * cfg.L * (cfg.batch if per_token else 1)
+                assert stats.layer_launches == 0 and (stats.ffn_us > 0) == bool(timing)
+        finally:
+            st.close()
+    for k, out in enumerate(outs):
+        assert np.array_equal(out, outs[k % cfg.tokens])
+
+
 def test_grouped_layers_give_the_same_bits_whatever_is_resident():
     from paper_2607_24787_amd.model import OffloadedMoEStack
     cfg = GROUPED.with_(n=24, K=4, I=208, batch=21, n_shared=0)
