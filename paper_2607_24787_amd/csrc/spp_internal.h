@@ -34,13 +34,13 @@ struct RouterArgs {
   const void* Wr;       // [n, D]
   const void* A;        // [r, D] or nullptr
   const void* Bm;       // [n, r]
-  float* x_out;         // [B, D] router input written by block 0 (nullptr: skip)
+  float* x_out;         // [B, D] router input (nullptr: skip)
   uint16_t* xh;         // [B, D] the same as bf16 pairs x = xh + xl (nullptr: skip)
   uint16_t* xl;
   float* zbuf;          // [B, n + r] logits then adapter hidden units
   uint64_t* ztag;       // [n] the router's values tagged (seq << 32) | fp32 bits, for the batch-1
-                        // single-wave tails (polled instead of a completion counter), or nullptr
-  uint64_t* atag;       // [r] the adapter's, with ztag
+                        // single-wave tails (polled instead of a completion counter)
+  uint64_t* atag;       // [r] the adapter's
   uint64_t* route_tag;  // [kRouteCopies, kRouteWords], or nullptr (no FFN in this launch)
   unsigned polls;       // with tags: polls before an FFN workgroup forms the routing itself, and the adapter's
                         // tail of a launch without FFN the hidden units

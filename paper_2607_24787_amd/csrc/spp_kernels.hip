@@ -579,7 +579,7 @@ __device__ __forceinline__ uint32_t route_word(int slot, float gk, int lane) {
 // EPL = 0: the general tails (any n up to kMaxExpertsTopK, K <= 32, any r),
 // run by the whole workgroup through LDS; adapter workgroups fetch B together
 // with their rows, so the scoring tail starts with B in registers.
-// EPL = 1 or 2 (bf16, n <= 64 * EPL, K <= 64, r <= 64 and a multiple of 8):
+// EPL = 1 or 2 (n <= 64 * EPL; with an adapter: bf16, r <= 64 and a multiple of 8):
 // the tails run in wave 0 alone, with no barrier -- lane l holds experts
 // l + 64 q (q < EPL).  Top-K: K rounds of a wave maximum over the 32-bit
 // order of the available logits, the lowest index taking a tie (the same
@@ -587,12 +587,11 @@ __device__ __forceinline__ uint32_t route_word(int slot, float gk, int lane) {
 // experts in registers; the hidden unit a_j is broadcast from lane j.  Both
 // give the bits of the general tails: the same products in the same order, and
 // the distribution's sum as the sum of the per-64-expert wave sums in expert
-// order.  With a tag buffer (a.ztag) every row's value is also stored tagged
-// with the launch's seq, and wave 0 of the last workgroup of each kind takes
-// that kind's tail as soon as its poll sees every value tagged: the writers
-// neither wait for their stores nor pass a counter (1.0 us less per launch
-// than the last-arriver handoff, same outputs).  Without one (a caller with no
-// sequence numbers), the last workgroup through the counter takes it.
+// order.  Every row's value is also stored tagged with the launch's number, and
+// wave 0 of the last workgroup of each kind takes that kind's tail as soon as
+// its poll sees every value tagged: the writers neither wait for their stores
+// nor pass a counter (1.0 us less per launch than EPL = 0's handoff to the last
+// workgroup through a completion counter, same outputs).
 // ---------------------------------------------------------------------------
 // `nblocks` workgroups take part; `bid` is this one's index among them.  ALONE:
 // no other work shares the launch.
@@ -636,9 +635,9 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
   uint4 rbf[EPL ? EPL : 1][kBC];
   if (EPL == 0) {
     bst.load(a, tid, adapter_wg && staged);
-  } else if (sizeof(T) == 2 && adapter_wg && wave == 0 && (!a.ztag || bid == nblocks - 1)) {
-    // B rows of this lane's experts (in the workgroup that may take the tail) (a chunk past r, or a row past n, re-reads
-    // the first chunk of B and is dropped)
+  } else if (sizeof(T) == 2 && adapter_wg && wave == 0 && bid == nblocks - 1) {
+    // B rows of the tail's lanes' experts (a chunk past r, or a row past n,
+    // re-reads the first chunk of B and is dropped)
     const int rc = r / 8;
 #pragma unroll
     for (int q = 0; q < (EPL ? EPL : 1); ++q) {
@@ -690,52 +689,31 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
     const float acc = row_dot<T, NCH>(w, xv);
     if (lane == 0) {
       st_agent(a.zbuf + zcol, acc);
-      if (EPL && a.ztag) st_tag((adapter_wg ? a.atag : a.ztag) + row, seq, acc);
+      if (EPL) st_tag((adapter_wg ? a.atag : a.ztag) + row, seq, acc);
     }
   }
 
-  const int kind = adapter_wg ? 1 : 0;
-  const unsigned total = adapter_wg ? nblocks - gr : gr;
   if (EPL) {
     constexpr int Q = EPL ? EPL : 1;
-    // Handoff.  Tagged values: wave 0 of its kind's last workgroup polls
-    // them (it waits only for workgroups dispatched before it).  Otherwise
-    // the last workgroup to pass the completion counter takes the tail
-    // (after releasing its own values), and resets it.
+    // Handoff: wave 0 of its kind's last workgroup polls the tagged values (it
+    // waits only for workgroups dispatched before it)
+    if (wave != 0 || bid != (adapter_wg ? nblocks : gr) - 1) return;
     float zv[Q];
-    if (a.ztag) {
-      if (wave != 0 || bid != (adapter_wg ? nblocks : gr) - 1) return;
-      // a poll that runs out leaves this launch's records unwritten: the host reports it
-      if (!adapter_wg) {
-        if (!poll_tags<Q>(a.ztag, n, lane, seq, kPollMax, zv)) return;
-      } else {
-        if constexpr (sizeof(T) == 4) return;  // fp32 adapters take the general tail
-        if (!poll_tags<1>(a.atag, na, lane, seq, ALONE ? a.polls : kPollMax, zv)) {
-          if constexpr (!ALONE) return;
-          // rows that are late, or that an overlapping launch numbered: form them here, with the same operations
-          input_x<T, NCH, FULL>(a, lane, nch, xv);
-#pragma unroll 1
-          for (int j = 0; j < na; ++j) {
-            load_chunks<NCH, FULL>(reinterpret_cast<const T*>(a.A) + static_cast<size_t>(j) * D, lane, nch, w);
-            const float z = row_dot<T, NCH>(w, xv);
-            zv[0] = lane == j ? z : zv[0];
-          }
-        }
-      }
+    // a poll that runs out leaves this launch's records unwritten: the host reports it
+    if (!adapter_wg) {
+      if (!poll_tags<Q>(a.ztag, n, lane, seq, kPollMax, zv)) return;
     } else {
-      wait_own_stores();  // release this wave's value
-      __syncthreads();
-      if (wave != 0) return;
-      unsigned prev = 0;
-      if (lane == 0) prev = __hip_atomic_fetch_add(a.counter + kind, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      prev = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(prev)));
-      if (prev != total - 1) return;
-      if (lane == 0) __hip_atomic_store(a.counter + kind, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (adapter_wg) {
-        zv[0] = ld_agent(a.zbuf + n + min(lane, na - 1));
-      } else {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) zv[q] = ld_agent(a.zbuf + min(lane + 64 * q, n - 1));
+      if constexpr (sizeof(T) == 4) return;  // fp32 adapters take the general tail
+      if (!poll_tags<1>(a.atag, na, lane, seq, ALONE ? a.polls : kPollMax, zv)) {
+        if constexpr (!ALONE) return;
+        // rows that are late, or that an overlapping launch numbered: form them here, with the same operations
+        input_x<T, NCH, FULL>(a, lane, nch, xv);
+#pragma unroll 1
+        for (int j = 0; j < na; ++j) {
+          load_chunks<NCH, FULL>(reinterpret_cast<const T*>(a.A) + static_cast<size_t>(j) * D, lane, nch, w);
+          const float z = row_dot<T, NCH>(w, xv);
+          zv[0] = lane == j ? z : zv[0];
+        }
       }
     }
     if (!adapter_wg) {
@@ -794,6 +772,8 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
     }
     return;
   }
+  const int kind = adapter_wg ? 1 : 0;
+  const unsigned total = adapter_wg ? nblocks - gr : gr;
   wait_own_stores();  // release this wave's value
   __syncthreads();
   if (tid == 0) {
@@ -925,8 +905,8 @@ __global__ __launch_bounds__(kThreads) void router_select_kernel(RouterArgs a) {
   if (tid == 0) __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Selection for B > 1 tokens with one wave per token (n <= 64 EPL, K <= 64;
-// with an adapter: bf16, r <= 64 and a multiple of 8): lane l holds experts l + 64 q.  Top-K
+// Selection for B > 1 tokens with one wave per token (n <= 64 EPL; with an
+// adapter: bf16, r <= 64 and a multiple of 8): lane l holds experts l + 64 q.  Top-K
 // by K rounds of a wave maximum over the 32-bit logit order (the lowest index
 // taking a tie), the gates, and the adapter distribution from B's rows of the
 // lane's experts in registers -- the products, maxima and sums of
@@ -2959,7 +2939,7 @@ int router_wgs(const RouterArgs& a) {
   return ((a.router_on ? a.n : 0) + kWaves - 1) / kWaves + ((a.A ? a.r : 0) + kWaves - 1) / kWaves;
 }
 
-// Batch 1, single-wave tails: n <= 128, K <= 32 (checked at launch), an
+// Single-wave tails: n <= 128, K <= 32 (checked at launch), an
 // adapter in bf16 with r <= 64 and a multiple of 8.
 bool one_wave_tails(const RouterArgs& a, bool bf16) {
   return a.n <= 128 && (!a.A || (bf16 && a.r <= 64 && a.r % 8 == 0));
@@ -2974,6 +2954,7 @@ hipError_t router_tf(const RouterArgs& a, hipStream_t st) {
   if (a.B == 1) {
     const int g1 = router_wgs(a);
     const bool fast = one_wave_tails(a, sizeof(T) == 2);
+    if (fast && ((a.router_on && !a.ztag) || (a.A && !a.atag))) return hipErrorInvalidValue;
     if (fast && a.n <= 64) {
       SPP_DISPATCH_NCH(nch_for<T>(a.D), hipLaunchKernelGGL((router_adapter_kernel<T, NCH, FULL, 1>), dim3(g1),
                                                            dim3(kThreads), 0, st, a));
@@ -2992,10 +2973,9 @@ hipError_t router_tf(const RouterArgs& a, hipStream_t st) {
   else
     router_rows_t<T, T>(a, rows, st);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  // one wave per token: n <= 128, K <= 64, an adapter in bf16 with r <= 64 and
-  // a multiple of 8 (as the batch-1 one-wave tails); 3.3 us against 3.9 for a
-  // workgroup per token (6 fp32 tokens over 32 experts)
-  const bool wave1 = a.n <= 128 && a.K <= 64 && (!a.A || (sizeof(T) == 2 && a.r <= 64 && a.r % 8 == 0));
+  // one wave per token under the conditions of the batch-1 one-wave tails; 3.3 us
+  // against 3.9 for a workgroup per token (6 fp32 tokens over 32 experts)
+  const bool wave1 = one_wave_tails(a, sizeof(T) == 2);
   if (wave1 && a.n <= 64)
     hipLaunchKernelGGL((router_select_wave_kernel<1>), dim3(a.B), dim3(64), 0, st, a);
   else if (wave1)
@@ -3029,8 +3009,10 @@ constexpr int slices_ds() {
   return NCH <= 4 ? 1 : 2;
 }
 
-// Most sweep rounds: what stays in registers beside x (2 NCH + 4 DS chunks of
-// 4 registers each per round).  Up to 4 chunks per lane no more than 3: which
+// Most sweep rounds: what stays in 256 registers beside x (2 NCH + 4 DS chunks
+// of 4 registers each per round), so that two workgroups share a compute unit
+// (231 registers at 6 ragged chunks, 241 at 8 of fp32, alone; 221 and 233 in
+// the launch with the router).  Up to 4 chunks per lane no more than 3: which
 // units share a partial row is part of a stack's rounding, and 4 rounds on 448
 // workgroups, although faster over 7,168 units (17.3 against 18.4 us), turn
 // near-ties of later layers' routers.
@@ -3452,8 +3434,10 @@ int ffn_grid_slices(int nunits, int D, int dtype, int target_wgs, int* rounds) {
   const long per = static_cast<long>(kSlWaves) * std::max(target_wgs, 1);
   // Up to 4 chunks per lane: the number of rounds that puts the grid nearest
   // target_wgs (see slices_rounds).  Longer rows: the fewest with at most
-  // target_wgs workgroups, two per compute unit (3,600 units of 2,304 columns:
-  // 25.4 us with 900 workgroups of one round, 21.3 with 450 of two).
+  // target_wgs workgroups, two per compute unit, which is what two rounds leave
+  // resident.  One round against two, the layer in us: 3,600 units of 2,304
+  // columns 23.7 and 20.0, of 2,816 25.9 and 21.5, of 1,900 fp32 columns 28.9
+  // and 24.1; 2,400 units 18.9 and 18.0, 20.4 and 19.3, 22.4 and 21.5.
   int r = static_cast<int>((nunits + (nchl <= 4 ? per / 2 : per - 1)) / per);
   r = std::min(std::max(r, 1), rmax);
   int grid = (nunits + kSlWaves * r - 1) / (kSlWaves * r);

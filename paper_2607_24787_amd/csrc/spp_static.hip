@@ -91,8 +91,7 @@ extern "C" spp_status adapter_predict_static(const void* adapter_a, const void* 
   unsigned* counter = static_cast<unsigned*>(base);
   spp::RouterArgs ra{};
   if (spp::adapter_by_tickets(n, r, B, dtype)) {
-    ra.ztag = reinterpret_cast<uint64_t*>(counter + kCounterWords);  // no router rows: not written
-    ra.atag = ra.ztag + 64 * (r / 8 - 1);
+    ra.atag = reinterpret_cast<uint64_t*>(counter + kCounterWords) + 64 * (r / 8 - 1);
     ra.tickets = counter + kTicketWord + r / 8 - 1;
     ra.polls = spp::kSelfPolls;
   } else if (B > 1) {
