@@ -174,7 +174,10 @@ typedef struct {
    * nothing to host_decide_us */
   double host_route_us;
   double host_decide_us;
-  /* batch-1 layer calls whose router and FFN went out as one launch */
+  /* layer calls whose FFN followed the routing on the device (every expert
+   * held a slot), and of those the batch-1 ones whose router and FFN went out
+   * as one launch */
+  int64_t device_routed_calls;
   int64_t layer_launches;
 } spp_run_stats;
 
@@ -499,6 +502,12 @@ spp_status spp_debug_set_copy_delay(spp_ctx* ctx, int32_t delay_us);
  * and the adapter's tail the hidden units where no FFN shares its launch (0:
  * at once; -1: the default).  Outputs are unchanged.  EINVAL below -1. */
 spp_status spp_debug_set_self_polls(spp_ctx* ctx, int32_t polls);
+
+/* Test hook for batched contexts in the unit layout: a batched FFN launch
+ * takes at most `tokens` tokens (1 up to what the context's partial rows hold,
+ * which is the default).  Outputs are unchanged.  EINVAL outside the range or
+ * for another layout. */
+spp_status spp_debug_set_batch_tokens(spp_ctx* ctx, int32_t tokens);
 
 /* ------------------------------------- host replacement policy (no device) */
 

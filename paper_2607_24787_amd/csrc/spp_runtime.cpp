@@ -141,6 +141,7 @@ struct spp_ctx {
   int32_t* round_tab = nullptr;  // [n] slots of one round's experts (host-decided batched layers)
   int32_t batch_tokens = 1;      // tokens of one batched FFN launch: max_batch, unless its partial rows
                                  // would exceed kMaxPartialBytes
+  int32_t batch_tokens_max = 1;  // what ypart holds
   float* ypart = nullptr;
   std::vector<hipEvent_t> round_done;  // per on-demand round: its FFN launch finished
   int64_t clock = 0;
@@ -691,6 +692,7 @@ spp_status create_impl(const spp_model_desc* desc, void* stream, spp_ctx** out) 
       batch_split(d, B, c->num_cu, &ns, &upw);
       rows = std::max(rows, static_cast<size_t>(B) * (d.K + d.n_shared) * ns);
     }
+    c->batch_tokens_max = c->batch_tokens;
     if (hipMalloc(&c->round_tab, d.n * sizeof(int32_t)) != hipSuccess ||
         hipMalloc(&c->ypart, rows * d.D * sizeof(float)) != hipSuccess)
       return fail(SPP_ENOMEM, "batched-decode buffers allocation failed");
@@ -1101,6 +1103,7 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   fl.predict = fl.adapter_on || (fl.naive && l < d.L - 1 && M_max >= 0);
   if (fl.predict && M_max > 0 && !c->layers[l + 1].bound) return fail(SPP_ESTATE, "next layer not bound");
   fl.routed = device_routable(c, ls, B);
+  c->stats.device_routed_calls += fl.routed ? 1 : 0;
   if (fl.routed)
     if (spp_status s = upload_slot_table(c, ls)) return s;
   fl.tau = ++c->clock;
@@ -1928,6 +1931,14 @@ spp_status spp_debug_set_self_polls(spp_ctx* c, int32_t polls) {
   if (spp_status s = check_ctx(c)) return s;
   if (polls < -1) return fail(SPP_EINVAL, "polls must be >= -1");
   c->self_polls = polls < 0 ? spp::kSelfPolls : static_cast<uint32_t>(polls);
+  return SPP_OK;
+}
+
+spp_status spp_debug_set_batch_tokens(spp_ctx* c, int32_t tokens) {
+  if (spp_status s = check_ctx(c)) return s;
+  if (tokens < 1 || tokens > c->batch_tokens_max || c->grouped)
+    return fail(SPP_EINVAL, "tokens must be in [1, the launch's capacity], in the unit layout");
+  c->batch_tokens = tokens;
   return SPP_OK;
 }
 

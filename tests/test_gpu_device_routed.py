@@ -48,8 +48,14 @@ def test_device_and_host_routed_layers_give_the_same_bits(cfg):
                     spp.spp_set_slot_table(full.ctx, l, part, np.zeros(cfg.n, np.int64))
             if t == 6:  # other slots than before
                 spp.spp_set_slot_table(full.ctx, 1, table[::-1].copy(), np.zeros(cfg.n, np.int64))
+            before = _paths(full)
             ref = host.decode_step_from(_in(host, h0[t]), 2)
             got = full.decode_step_from(_in(full, h0[t]), 2)
+            routed, one = (a - b for a, b in zip(_paths(full), before))
+            if t < 3:
+                assert routed == cfg.L and one == sum(_one_launch(cfg, l) for l in range(cfg.L))
+            elif t == 3:
+                assert routed == cfg.L - 2
             for l in range(cfg.L):
                 assert np.array_equal(got[l][0], ref[l][0]), (t, l)
                 assert np.array_equal(got[l][1], ref[l][1]), (t, l)
@@ -59,12 +65,24 @@ def test_device_and_host_routed_layers_give_the_same_bits(cfg):
                     assert got[l][2].hits == distinct and got[l][2].misses == 0 and got[l][2].prefetched == 0
             assert np.array_equal(full.download(full.hbuf[0]), host.download(host.hbuf[0])), t
         assert spp.spp_get_clock(full.ctx) == cfg.tokens * cfg.L
+        assert _paths(host) == (0, 0)
         _, stamps = spp.spp_get_slot_table(full.ctx, 0, cfg.n)
         last = set(got[0][0].ravel().tolist())
         assert [int(s) == (cfg.tokens - 1) * cfg.L + 1 for s in stamps] == [int(e) in last for e in table]
     finally:
         host.close()
         full.close()
+
+
+def _paths(st):
+    stats = spp.spp_get_run_stats(st.ctx)
+    return stats.device_routed_calls, stats.layer_launches
+
+
+def _one_launch(cfg, l):
+    """Whether a resident layer's router and FFN go out as one launch."""
+    adapter = l < cfg.L - 1 and cfg.r > 0
+    return cfg.batch == 1 and cfg.n <= 128 and (not adapter or (cfg.dtype == "bf16" and cfg.r <= 64 and cfg.r % 8 == 0))
 
 
 ONE_LAUNCH = [
@@ -88,7 +106,7 @@ def test_ffn_workgroups_that_do_not_see_the_routing_form_it(cfg):
     h0 = gen.hidden_states(cfg, tokens=4)
     x = st.torch.randn(cfg.D, device=st.device, generator=st.torch.Generator(st.device).manual_seed(3))
     runs = []
-    one = sum(1 for l in range(cfg.L) if cfg.dtype == "bf16" or l == cfg.L - 1)  # fp32 adapters take two launches
+    one = sum(_one_launch(cfg, l) for l in range(cfg.L))
     try:
         for polls in (-1, 0, 1):
             print(f"[route polls] {cfg.D} {cfg.codec} {cfg.dtype} polls={polls}", flush=True)
@@ -100,7 +118,7 @@ def test_ffn_workgroups_that_do_not_see_the_routing_form_it(cfg):
                 out = st.decode_step_from(_in(st, h0[t]), 0)
                 runs[-1] += [a for l in out for a in l[:2]] + [st.download(st.hbuf[0])]
                 runs[-1].append(spp.adapter_predict(st.ctx, 0, x.data_ptr(), 1, cfg.n))
-            assert spp.spp_get_run_stats(st.ctx).layer_launches == 4 * one
+            assert _paths(st) == (4 * cfg.L, 4 * one)
     finally:
         st.close()
     for other in runs[1:]:
@@ -170,27 +188,33 @@ GROUPED = w.MoEConfig(name="grouped_bf16_D512_n6_k2_I400", L=2, D=512, n=6, K=2,
                       tokens=2, batch=40, n_shared=1, seed=43)
 
 
-@pytest.mark.parametrize("cfg", [
-    GROUPED,
-    GROUPED.with_(n=4, K=1, I=1104, n_shared=2, batch=75),
-    GROUPED.with_(n=140, K=3, I=784, D=256, n_shared=0, batch=90, r=16),
-    GROUPED.with_(n=24, K=5, I=16, D=768, batch=3, has_proj=True),
-    GROUPED.with_(n=9, K=9, I=336, D=1280, batch=2),
+GROUPED_CFGS = {
+    "chunks": GROUPED,
+    "wide_ranges": GROUPED.with_(n=4, K=1, I=1104, n_shared=2, batch=75),
+    "n140": GROUPED.with_(n=140, K=3, I=784, D=256, n_shared=0, batch=90, r=16),
+    "one_tile": GROUPED.with_(n=24, K=5, I=16, D=768, batch=3, has_proj=True),
+    "k_eq_n": GROUPED.with_(n=9, K=9, I=336, D=1280, batch=2),
     # the unit layout: several 32-token chunks, one unit past whole workgroups, every chunk count and its tail
-    GROUPED.with_(I=49, D=272, batch=45),
-    GROUPED.with_(I=25, D=2048, batch=3, n=12),
-    GROUPED.with_(I=9, D=3104, batch=5, n_shared=0),
-    GROUPED.with_(I=61, D=1024, dtype="f32", batch=6),
-    GROUPED.with_(I=30, D=1296, dtype="f32", batch=40, has_proj=True),
-], ids=["chunks", "wide_ranges", "n140", "one_tile", "k_eq_n", "units_bf16", "units_bf16_full", "units_bf16_long",
-        "units_f32", "units_f32_long"])
-@pytest.mark.parametrize("resident", [True, False], ids=["resident", "rounds"])
+    "units_bf16": GROUPED.with_(I=49, D=272, batch=45),
+    "units_bf16_full": GROUPED.with_(I=25, D=2048, batch=3, n=12),
+    "units_bf16_long": GROUPED.with_(I=9, D=3104, batch=5, n_shared=0),
+    "units_f32": GROUPED.with_(I=61, D=1024, dtype="f32", batch=6),
+    "units_f32_long": GROUPED.with_(I=30, D=1296, dtype="f32", batch=40, has_proj=True),
+}
+
+
+def _fits_in_rounds(cfg):
+    """The tiled layout, and the unit layout where half the experts hold a batch's demand."""
+    tiled = cfg.dtype == "bf16" and cfg.D % 256 == 0 and cfg.I % 16 == 0
+    return tiled or cfg.K * cfg.batch < cfg.n
+
+
+@pytest.mark.parametrize("cfg,resident",
+                         [pytest.param(c, True, id=f"resident-{k}") for k, c in GROUPED_CFGS.items()]
+                         + [pytest.param(c, False, id=f"rounds-{k}") for k, c in GROUPED_CFGS.items() if _fits_in_rounds(c)])
 def test_grouped_layers_against_the_oracle(cfg, resident):
     from lockstep import run_lockstep
     from paper_2607_24787_amd.model import OffloadedMoEStack
-    tiled = cfg.dtype == "bf16" and cfg.D % 256 == 0 and cfg.I % 16 == 0
-    if not resident and not tiled and cfg.K * cfg.batch >= cfg.n:
-        pytest.skip("the unit layout needs a slot per expert here")
     st = OffloadedMoEStack(cfg, S=cfg.n if resident else max(cfg.n // 2, 1))
     try:
         rep = run_lockstep(st, cfg, cfg.tokens, 1)
@@ -252,6 +276,36 @@ def test_few_tokens_in_the_unit_layout(cfg, per_token):
             st.close()
     for k, out in enumerate(outs):
         assert np.array_equal(out, outs[k % cfg.tokens])
+
+
+@pytest.mark.parametrize("cfg", [
+    GROUPED.with_(I=49, D=272, batch=11),
+    GROUPED.with_(I=30, D=1296, dtype="f32", batch=40, has_proj=True, n_shared=2),
+], ids=["bf16", "f32_proj"])
+def test_unit_layout_batches_in_several_launches(cfg):
+    """A batch whose partial rows exceed the buffer goes out in runs of tokens, the last one shorter: the bits of one
+    launch, resident and decided on the host (every expert but one resident)."""
+    from paper_2607_24787_amd.model import OffloadedMoEStack
+    h0 = gen.hidden_states(cfg, tokens=2)
+    outs = []
+    for S, spare in ((cfg.n, 0), (cfg.n, 1)):
+        st = OffloadedMoEStack(cfg, S=S, resident=range(cfg.n - spare))
+        try:
+            for run in (cfg.batch, 4, 7, 1):
+                spp.spp_debug_set_batch_tokens(st.ctx, run)
+                st.reset()
+                spp.spp_reset_run_stats(st.ctx)
+                st.decode_step_from(_in(st, h0[0]), -1)
+                outs.append(st.download(st.hbuf[0]))
+                assert spp.spp_get_run_stats(st.ctx).ffn_launches == cfg.L * -(-cfg.batch // run)
+                assert (_paths(st)[0] == 0) == bool(spare)
+            for bad in (0, cfg.batch + 1):
+                with pytest.raises(spp.SppError) as e:
+                    spp.spp_debug_set_batch_tokens(st.ctx, bad)
+                assert e.value.status == spp.SPP_EINVAL
+        finally:
+            st.close()
+    assert all(np.array_equal(out, outs[0]) for out in outs)
 
 
 def test_grouped_layers_give_the_same_bits_whatever_is_resident():
