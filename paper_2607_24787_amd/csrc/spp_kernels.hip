@@ -1396,9 +1396,10 @@ __global__ __launch_bounds__(64 * kSlWaves) void ffn_slices_kernel(FfnArgs a) {
 // latency and a load of x.  The wait is a hint, never a dependence: these grids
 // exceed what is resident at once and each XCD dispatches on its own, so two
 // launches on two streams could hold each other's routers off the device.  A
-// workgroup whose first wave does not see the routing within ra.polls polls (some 5
-// are usual) forms it from the router's rows itself, with the same bits, and
-// no workgroup's end waits for another's start.  Qwen-shaped: router 6.5 + FFN 14.8 us ->
+// workgroup whose first wave does not see the routing within ra.polls polls
+// (about a microsecond each; the routing takes some 5 us) forms it from the
+// router's rows itself, with the same bits, and no workgroup's end waits for
+// another's start.  Qwen-shaped: router 6.5 + FFN 14.8 us ->
 // 19.1 in one launch, the layer 24.2 -> 22.1; 4-bit 6.5 + 9.8 -> 13.8, the
 // layer 18.0 -> 16.9; 1,024 units of 256 fp32 columns 5.1 + 3.8 -> 6.0.  The
 // same for a batch (selection and FFN in one launch, every workgroup waiting
