@@ -499,8 +499,8 @@ spp_status spp_debug_set_copy_delay(spp_ctx* ctx, int32_t delay_us);
 
 /* Test hook for the waits between workgroups of a one-token launch: the polls
  * after which an FFN workgroup that has not seen the routing forms it itself,
- * and the adapter's tail the hidden units where no FFN shares its launch (0:
- * at once; -1: the default).  Outputs are unchanged.  EINVAL below -1. */
+ * and the tail of adapter_predict the hidden units (0: at once; -1: the
+ * default).  Outputs are unchanged.  EINVAL below -1. */
 spp_status spp_debug_set_self_polls(spp_ctx* ctx, int32_t polls);
 
 /* Test hook for batched contexts in the unit layout: a batched FFN launch

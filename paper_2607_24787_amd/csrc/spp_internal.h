@@ -23,7 +23,7 @@ constexpr int kMaxExpertsTopK = 1024;
 constexpr int kRouteWords = 64;
 constexpr int kRouteCopies = 8;
 // Polls (about a microsecond each) after which such a workgroup forms the
-// routing itself, and the adapter's tail of a launch of its own the hidden units.
+// routing itself, and the tail of an adapter-only launch the hidden units.
 constexpr unsigned kSelfPolls = 256;
 
 // Router + adapter (one launch).  Rows [0, n) are router logits (if
@@ -42,8 +42,8 @@ struct RouterArgs {
                         // single-wave tails (polled instead of a completion counter)
   uint64_t* atag;       // [r] the adapter's
   uint64_t* route_tag;  // [kRouteCopies, kRouteWords], or nullptr (no FFN in this launch)
-  unsigned polls;       // with tags: polls before an FFN workgroup forms the routing itself, and the adapter's
-                        // tail of a launch without FFN the hidden units
+  unsigned polls;       // with tags: polls before an FFN workgroup forms the routing itself, and the tail of an
+                        // adapter-only launch the hidden units
   int32_t* topk;        // [B, K]
   float* gates;         // [B, K]
   const int32_t* slot_tab;  // [n] slot of each expert, or nullptr (the host decides the slots)

@@ -594,7 +594,8 @@ __device__ __forceinline__ uint32_t route_word(int slot, float gk, int lane) {
 // workgroup through a completion counter, same outputs).
 // ---------------------------------------------------------------------------
 // `nblocks` workgroups take part; `bid` is this one's index among them.  ALONE:
-// no other work shares the launch.
+// a launch of adapter rows alone, whose tail never fails (the other launches'
+// missing records tell the host).
 template <typename T, int NCH, bool FULL, int EPL, bool ALONE>
 __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid, int nblocks) {
   constexpr int V = Vec<T>::N;
@@ -819,7 +820,17 @@ __device__ __forceinline__ void router_adapter_body(const RouterArgs& a, int bid
 
 template <typename T, int NCH, bool FULL, int EPL>
 __global__ __launch_bounds__(kThreads) void router_adapter_kernel(RouterArgs a) {
-  router_adapter_body<T, NCH, FULL, EPL, true>(a, blockIdx.x, gridDim.x);
+  // one argument of each 64-byte line: the lines come together, not one by one
+  // as the code first needs them (0.25 us of 5.9)
+  static_assert(sizeof(RouterArgs) > 192 && sizeof(RouterArgs) <= 256, "four lines of arguments");
+  asm volatile("" ::"s"(a.h), "s"(a.atag), "s"(a.sel), "s"(a.n));
+  router_adapter_body<T, NCH, FULL, EPL, false>(a, blockIdx.x, gridDim.x);
+}
+
+// Adapter rows alone (bf16, one-wave tail).
+template <int NCH, bool FULL, int EPL>
+__global__ __launch_bounds__(kThreads) void adapter_kernel(RouterArgs a) {
+  router_adapter_body<uint16_t, NCH, FULL, EPL, true>(a, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -2956,7 +2967,14 @@ hipError_t router_tf(const RouterArgs& a, hipStream_t st) {
     const int g1 = router_wgs(a);
     const bool fast = one_wave_tails(a, sizeof(T) == 2);
     if (fast && ((a.router_on && !a.ztag) || (a.A && !a.atag))) return hipErrorInvalidValue;
-    if (fast && a.n <= 64) {
+    if (fast && a.router_on && a.tickets) return hipErrorInvalidValue;  // drawn by adapter_kernel only
+    if (fast && !a.router_on && a.n <= 64) {
+      SPP_DISPATCH_NCH(nch_for<T>(a.D),
+                       hipLaunchKernelGGL((adapter_kernel<NCH, FULL, 1>), dim3(g1), dim3(kThreads), 0, st, a));
+    } else if (fast && !a.router_on) {
+      SPP_DISPATCH_NCH(nch_for<T>(a.D),
+                       hipLaunchKernelGGL((adapter_kernel<NCH, FULL, 2>), dim3(g1), dim3(kThreads), 0, st, a));
+    } else if (fast && a.n <= 64) {
       SPP_DISPATCH_NCH(nch_for<T>(a.D), hipLaunchKernelGGL((router_adapter_kernel<T, NCH, FULL, 1>), dim3(g1),
                                                            dim3(kThreads), 0, st, a));
     } else if (fast) {

@@ -98,9 +98,9 @@ ONE_LAUNCH = [
 
 @pytest.mark.parametrize("cfg", ONE_LAUNCH, ids=["n40", "n100_proj", "q4", "q4_long_proj", "long_ragged", "k1", "f32"])
 def test_ffn_workgroups_that_do_not_see_the_routing_form_it(cfg):
-    """A launch's FFN workgroups must not depend on its router's being on the device, nor the adapter's tail on its
-    rows': with no polls every one of them forms the routing (the hidden units) itself, and with one poll some do.
-    Same bits."""
+    """A launch's FFN workgroups must not depend on its router's being on the device, nor the tail of an adapter-only
+    launch on its rows': with no polls every one of them forms the routing (the hidden units) itself, and with one poll
+    some do.  Same bits."""
     from paper_2607_24787_amd.model import OffloadedMoEStack
     st = OffloadedMoEStack(cfg, S=cfg.n)
     h0 = gen.hidden_states(cfg, tokens=4)
