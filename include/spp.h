@@ -123,7 +123,8 @@ typedef struct {
   int64_t copy_bytes, ffn_launches, window_samples;
   double router_us;   /* router+adapter kernel and result read-back */
   double exposed_us;  /* compute stream waiting on expert copies before the FFN */
-  double ffn_us;      /* routed-expert FFN main kernel (kernel begin/end stamps) */
+  double ffn_us;      /* routed-expert FFN main kernel (kernel begin/end stamps; of a call with several
+                       * launches the first one's begin and the last one's end) */
   double tail_us;     /* FFN combine/residual kernel */
   double span_us;     /* first layer start to last layer end */
   double window_us;   /* sum over layer pairs of W_l = t_exec(l+1) - t_pred(l) */
@@ -174,11 +175,6 @@ typedef struct {
    * nothing to host_decide_us */
   double host_route_us;
   double host_decide_us;
-  /* layer calls whose FFN followed the routing on the device (every expert
-   * held a slot), and of those the batch-1 ones whose router and FFN went out
-   * as one launch */
-  int64_t device_routed_calls;
-  int64_t layer_launches;
 } spp_run_stats;
 
 /* ---------------------------------------------------------------- lifecycle */
@@ -502,6 +498,12 @@ spp_status spp_debug_set_copy_delay(spp_ctx* ctx, int32_t delay_us);
  * and the tail of adapter_predict the hidden units (0: at once; -1: the
  * default).  Outputs are unchanged.  EINVAL below -1. */
 spp_status spp_debug_set_self_polls(spp_ctx* ctx, int32_t polls);
+
+/* The paths that layer calls took since spp_reset_run_stats (either may be
+ * NULL): calls whose FFN followed the routing on the device (every expert held
+ * a slot), and of those the batch-1 ones whose router and FFN went out as one
+ * launch. */
+spp_status spp_debug_get_paths(spp_ctx* ctx, int64_t* device_routed, int64_t* one_launch);
 
 /* Test hook for batched contexts in the unit layout: a batched FFN launch
  * takes at most `tokens` tokens (1 up to what the context's partial rows hold,

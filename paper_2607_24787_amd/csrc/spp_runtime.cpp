@@ -172,6 +172,7 @@ struct spp_ctx {
   bool have_prev = false;
   TimingSet prev{};
   spp_run_stats stats{};
+  int64_t device_routed = 0, one_launch = 0;  // spp_debug_get_paths
 };
 
 namespace {
@@ -1103,7 +1104,7 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
   fl.predict = fl.adapter_on || (fl.naive && l < d.L - 1 && M_max >= 0);
   if (fl.predict && M_max > 0 && !c->layers[l + 1].bound) return fail(SPP_ESTATE, "next layer not bound");
   fl.routed = device_routable(c, ls, B);
-  c->stats.device_routed_calls += fl.routed ? 1 : 0;
+  c->device_routed += fl.routed ? 1 : 0;
   if (fl.routed)
     if (spp_status s = upload_slot_table(c, ls)) return s;
   fl.tau = ++c->clock;
@@ -1162,7 +1163,7 @@ spp_status layer_begin(spp_ctx* c, int32_t l, const void* h_in, void* h_out, int
     const int grid = build_ffn(c, ls, nullptr, 0, false, &fa);
     if (spp::layer_launch_ok(ra, fa, dt)) {
       SPP_HIP(spp::launch_layer(ra, fa, grid, dt, c->compute));
-      c->stats.layer_launches += 1;
+      c->one_launch += 1;
       fl.t_router = std::chrono::steady_clock::now();
       return combine_token(c, fl, 0, grid);
     }
@@ -1816,6 +1817,7 @@ spp_status spp_reset_run_stats(spp_ctx* c) {
     c->have_prev = false;
   }
   c->stats = spp_run_stats{};
+  c->device_routed = c->one_launch = 0;
   c->pred_target = -1;
   std::fill(c->lt_calls.begin(), c->lt_calls.end(), 0);
   std::fill(c->lt_latency_calls.begin(), c->lt_latency_calls.end(), 0);
@@ -1931,6 +1933,13 @@ spp_status spp_debug_set_self_polls(spp_ctx* c, int32_t polls) {
   if (spp_status s = check_ctx(c)) return s;
   if (polls < -1) return fail(SPP_EINVAL, "polls must be >= -1");
   c->self_polls = polls < 0 ? spp::kSelfPolls : static_cast<uint32_t>(polls);
+  return SPP_OK;
+}
+
+spp_status spp_debug_get_paths(spp_ctx* c, int64_t* device_routed, int64_t* one_launch) {
+  if (spp_status s = check_ctx(c)) return s;
+  if (device_routed) *device_routed = c->device_routed;
+  if (one_launch) *one_launch = c->one_launch;
   return SPP_OK;
 }
 

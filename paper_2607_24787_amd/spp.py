@@ -52,8 +52,7 @@ class RunStats(ctypes.Structure):
                    ("demand_exceeds", c_int64 * 3), ("demand_hist", (c_int64 * 17) * 3),
                    ("ffn_split_launches", c_int64), ("exposed_shared_us", c_double), ("shared_calls", c_int64),
                    ("waited", c_int64), ("prefetch_hist", c_int64 * 17),
-                   ("host_route_us", c_double), ("host_decide_us", c_double), ("device_routed_calls", c_int64),
-                   ("layer_launches", c_int64)])
+                   ("host_route_us", c_double), ("host_decide_us", c_double)])
 
     def as_dict(self):
         out = {}
@@ -111,6 +110,7 @@ _SIGS = {
     "spp_debug_set_poison": (c_int32, [c_void_p, c_int32]),
     "spp_debug_set_copy_delay": (c_int32, [c_void_p, c_int32]),
     "spp_debug_set_self_polls": (c_int32, [c_void_p, c_int32]),
+    "spp_debug_get_paths": (c_int32, [c_void_p, POINTER(c_int64), POINTER(c_int64)]),
     "spp_debug_set_batch_tokens": (c_int32, [c_void_p, c_int32]),
     "spp_policy_create": (c_int32, [c_int32, c_int32, POINTER(c_int32), c_int32, POINTER(c_void_p)]),
     "spp_policy_destroy": (c_int32, [c_void_p]),
@@ -434,6 +434,13 @@ def spp_debug_set_copy_delay(ctx, delay_us: int):
 
 def spp_debug_set_self_polls(ctx, polls: int):
     _check(lib().spp_debug_set_self_polls(c_void_p(ctx), polls))
+
+
+def spp_debug_get_paths(ctx):
+    """(device-routed layer calls, those with router and FFN in one launch) since spp_reset_run_stats."""
+    a, b = c_int64(), c_int64()
+    _check(lib().spp_debug_get_paths(c_void_p(ctx), byref(a), byref(b)))
+    return a.value, b.value
 
 
 def spp_debug_set_batch_tokens(ctx, tokens: int):
